@@ -371,8 +371,7 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
     WL_HIP(hipMemsetAsync(S.bad, 0, sizeof(int32_t) * nv, s));
 
     // sources, |eta|^2, b', initial guess, first FP64 residual
-    WL_TRY(pack(S, eta, 0, cg.eta_e, s));
-    WL_TRY(pack(S, eta, 1, cg.eta_o, s));
+    WL_TRY(pack2(S, eta, cg.eta_e, cg.eta_o, s));
     WL_TRY(blas(S, BL_NORM2, P_F64, &cg.eta_e, 1, nullptr, red_spec(S, RED_STORE, S.scal(SC_ETA)), s));
     WL_TRY(blas(S, BL_NORM2, P_F64, &cg.eta_o, 1, nullptr, red_spec(S, RED_ACCUM, S.scal(SC_ETA)), s));
     // b' = eta_e + kappa D_eo A_oo^{-1} eta_o (xo holds A_oo^{-1} eta_o until psi_o is formed)
@@ -690,8 +689,7 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                red_spec(S, RED_STORE, S.scal(SC_RR)), s));
     WL_TRY(hop(S, P_F64, 18, false, 1, cg.t64, cg.xh, cg.epi(cg.c_tres, 2, cg.xo, cg.eta_o, EPI_CLOV_X0),
                red_spec(S, RED_ACCUM, S.scal(SC_RR)), s));
-    WL_TRY(unpack(S, x, 0, cg.xh, s));
-    WL_TRY(unpack(S, x, 1, cg.xo, s));
+    WL_TRY(unpack2(S, x, cg.xh, cg.xo, s));
     WL_HIP(hipMemcpyAsync(hp, S.scal(SC_RR), sizeof(double) * nv, hipMemcpyDeviceToHost, s));
     WL_HIP(hipStreamSynchronize(s));
     const double t1 = now_s();

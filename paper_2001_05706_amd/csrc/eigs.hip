@@ -195,9 +195,9 @@ wl_status defl_load(wl_gauge U, double kappa, int nev, const double *evecs, cons
     for (int p = 0; p < 2; ++p) {
         WL_TRY(D->E->field("defl_xi64_" + std::to_string(p), P_F64, &D->f64[p]));
         WL_TRY(D->E->field("defl_xi32_" + std::to_string(p), P_F32, &D->f32[p]));
-        WL_TRY(pack(*D->E, c, p, D->f64[p], s));
-        WL_TRY(pack(*D->E, c, p, D->f32[p], s));
     }
+    WL_TRY(pack2(*D->E, c, D->f64[0], D->f64[1], s));
+    WL_TRY(pack2(*D->E, c, D->f32[0], D->f32[1], s));
     return WL_OK;
 }
 
@@ -416,8 +416,8 @@ wl_status wl_hw_eigs(wl_gauge U, double rho, int32_t nev, int32_t nblock, int32_
         WL_TRY(E->field("eig_out" + std::to_string(p), P_F64, &Ef[p]));
         const size_t bytes = (size_t)nev * U->geom.stride * nchunks(P_F64) * chunk_bytes(P_F64);
         WL_HIP(hipMemcpyAsync(Ef[p].p, T[p].p, bytes, hipMemcpyDeviceToDevice, s));
-        WL_TRY(unpack(*E, out, p, Ef[p], s));
     }
+    WL_TRY(unpack2(*E, out, Ef[0], Ef[1], s));
     WL_HIP(hipStreamSynchronize(s));
     bool ok = true;
     for (int i = 0; i < nev; ++i) {

@@ -181,13 +181,18 @@ extern "C" wl_status wilson_dslash_noalloc(wl_gauge U, const double *in, double 
     ha.red.nv = 1;
     ha.one = nrhs == 1;
     // input slot k holds parity (parity < 0 ? k : 1 - parity); output slot k parity (parity < 0 ? k : parity)
-    for (int k = 0; k < nfield; ++k) {
-        const Field fi = field(0, k);
-        pa.parity = parity < 0 ? k : 1 - parity;
-        pa.f = fi.p;
-        pa.fn = fi.n;
-        WL_HIP(launch_pack_spinor(prec, pa, kNoAllocBlock, s));
+    const Field fi0 = field(0, 0);
+    pa.f = fi0.p;
+    pa.fn = fi0.n;
+    pa.parity = parity < 0 ? 0 : 1 - parity;
+    if (parity < 0) {
+        const Field fi1 = field(0, 1);
+        pa.both = 1;
+        pa.f2 = fi1.p;
+        pa.fn2 = fi1.n;
     }
+    WL_HIP(launch_pack_spinor(prec, pa, kNoAllocBlock, s));
+    pa.both = 0;
     for (int k = 0; k < nfield; ++k) {
         const int op = parity < 0 ? k : parity;  // output parity
         const Field fo = field(1, k), fin = field(0, parity < 0 ? 1 - k : 0);
@@ -204,19 +209,18 @@ extern "C" wl_status wilson_dslash_noalloc(wl_gauge U, const double *in, double 
         }
         WL_HIP(launch_hop(prec, recon, dagger != 0, false, kNoAllocVariant, ha, kNoAllocBlock, s));
     }
+    // both parities in one launch, or the output parity and zeros on the other
     pa.canon[0] = out;
-    for (int k = 0; k < nfield; ++k) {
-        const Field fo = field(1, k);
-        pa.parity = parity < 0 ? k : parity;
-        pa.f = fo.p;
-        pa.fn = fo.n;
-        WL_HIP(launch_unpack_spinor(prec, pa, kNoAllocBlock, s));
+    const Field f0 = field(1, 0);
+    pa.f = f0.p;
+    pa.fn = f0.n;
+    pa.parity = parity < 0 ? 0 : parity;
+    if (parity < 0) {
+        const Field f1 = field(1, 1);
+        pa.both = 1;
+        pa.f2 = f1.p;
+        pa.fn2 = f1.n;
     }
-    if (parity >= 0) {
-        pa.parity = 1 - parity;
-        pa.f = nullptr;
-        pa.fn = nullptr;
-        WL_HIP(launch_zero_canon(pa, kNoAllocBlock, s));
-    }
+    WL_HIP(launch_unpack_spinor(prec, pa, kNoAllocBlock, s));
     return WL_OK;
 }

@@ -183,10 +183,10 @@ wl_status overlap_dslash(wl_gauge U, const double *in, double *out, int32_t nrhs
     for (int p = 0; p < 2; ++p) {
         WL_TRY(S.field("ov_v" + std::to_string(p), prec, &v[p]));
         WL_TRY(S.field("ov_w" + std::to_string(p), prec, &w[p]));
-        WL_TRY(pack(S, cin, p, v[p], s));
     }
+    WL_TRY(pack2(S, cin, v[0], v[1], s));
     WL_TRY(ov_apply(O, prec, dagger != 0, w, v, 1.0, nullptr, 0.0, nullptr, 0.0, nullptr, s));
-    for (int p = 0; p < 2; ++p) WL_TRY(unpack(S, cout, p, w[p], s));
+    WL_TRY(unpack2(S, cout, w[0], w[1], s));
     WL_HIP(hipStreamSynchronize(s));
     return WL_OK;
 }
@@ -230,9 +230,9 @@ wl_status overlap_cg(wl_gauge U, const double *eta, double *x, int32_t nrhs, dou
         WL_TRY(S.field("oc_p" + t, P, &pp[p]));
         WL_TRY(S.field("oc_q" + t, P, &q[p]));
         WL_TRY(S.field("oc_s" + t, P, &sv[p]));
-        WL_TRY(pack(S, ceta, p, E[p], s));
-        WL_TRY(pack(S, cx, p, X[p], s));
     }
+    WL_TRY(pack2(S, ceta, E[0], E[1], s));
+    WL_TRY(pack2(S, cx, X[0], X[1], s));
     double *d_rr = S.scal(SC_RR), *d_qq = S.scal(SC_QQ), *d_gg = S.scal(SC_TMP), *d_eta = S.scal(SC_ETA);
     double *d_al = S.scal(SC_ALPHA), *d_be = S.scal(SC_BETA);
     std::vector<double> eta2, rr, qq, gg, gam(nv), al(nv), be(nv);
@@ -347,7 +347,7 @@ wl_status overlap_cg(wl_gauge U, const double *eta, double *x, int32_t nrhs, dou
     }
     std::vector<int32_t> all(nv, 1);
     WL_TRY(set_active(S, all, s));
-    for (int p = 0; p < 2; ++p) WL_TRY(unpack(S, cx, p, X[p], s));
+    WL_TRY(unpack2(S, cx, X[0], X[1], s));
     WL_HIP(hipStreamSynchronize(s));
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     bool ok = true;

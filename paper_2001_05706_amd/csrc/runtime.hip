@@ -1043,22 +1043,36 @@ wl_status pack(ExecSet &S, const double *const *canon, int parity, const Field &
     return WL_OK;
 }
 
-wl_status unpack(ExecSet &S, double *const *canon, int parity, const Field &f, hipStream_t s)
+wl_status pack2(ExecSet &S, const double *const *canon, const Field &even, const Field &odd, hipStream_t s)
 {
     PackArgs a;
-    WL_TRY(pack_args(S, (const void *const *)canon, parity, f, s, &a));
-    g_bytes_acc += blas_bytes(S, P_F64, 1, false) + blas_bytes(S, f.prec, 1, false);
-    WL_HIP(launch_unpack_spinor(f.prec, a, kBlasBlock, s));
+    WL_TRY(pack_args(S, (const void *const *)canon, 0, even, s, &a));
+    a.both = 1;
+    a.f2 = odd.p;
+    a.fn2 = odd.n;
+    g_bytes_acc += 2 * (blas_bytes(S, P_F64, 1, false) + blas_bytes(S, even.prec, 1, false));
+    WL_HIP(launch_pack_spinor(even.prec, a, kBlasBlock, s));
     return WL_OK;
 }
 
-wl_status zero_canon(ExecSet &S, double *const *canon, int parity, hipStream_t s)
+wl_status unpack2(ExecSet &S, double *const *canon, const Field &even, const Field &odd, hipStream_t s)
 {
     PackArgs a;
-    Field none;
-    WL_TRY(pack_args(S, (const void *const *)canon, parity, none, s, &a));
-    g_bytes_acc += blas_bytes(S, P_F64, 1, false);
-    WL_HIP(launch_zero_canon(a, kBlasBlock, s));
+    WL_TRY(pack_args(S, (const void *const *)canon, 0, even, s, &a));
+    a.both = 1;
+    a.f2 = odd.p;
+    a.fn2 = odd.n;
+    g_bytes_acc += 2 * (blas_bytes(S, P_F64, 1, false) + blas_bytes(S, even.prec, 1, false));
+    WL_HIP(launch_unpack_spinor(even.prec, a, kBlasBlock, s));
+    return WL_OK;
+}
+
+wl_status unpack_zero(ExecSet &S, double *const *canon, int parity, const Field &f, hipStream_t s)
+{
+    PackArgs a;
+    WL_TRY(pack_args(S, (const void *const *)canon, parity, f, s, &a));
+    g_bytes_acc += 2 * blas_bytes(S, P_F64, 1, false) + blas_bytes(S, f.prec, 1, false);
+    WL_HIP(launch_unpack_spinor(f.prec, a, kBlasBlock, s));
     return WL_OK;
 }
 
@@ -1182,17 +1196,16 @@ wl_status wilson_dslash(wl_gauge U, const double *in, double *out, int32_t nrhs,
         WL_TRY(coef_table(*S, {0, 0, 0, 0, 1.0}, &e.coef));
         WL_TRY(pack(*S, cin, 1 - parity, fi[1 - parity], s));
         WL_TRY(hop(*S, prec, recon, dagger, parity, fo[parity], fi[1 - parity], e, no_red(), s, false));
-        WL_TRY(unpack(*S, cout, parity, fo[parity], s));
-        WL_TRY(zero_canon(*S, cout, 1 - parity, s));
+        WL_TRY(unpack_zero(*S, cout, parity, fo[parity], s));
     } else {
         WL_TRY(coef_table(*S, {1.0, 0, 0, 0, -kappa}, &e.coef));
         e.nx = 1;
-        for (int p = 0; p < 2; ++p) WL_TRY(pack(*S, cin, p, fi[p], s));
+        WL_TRY(pack2(*S, cin, fi[0], fi[1], s));
         for (int p = 0; p < 2; ++p) {
             e.X[0] = fi[p];
             WL_TRY(hop(*S, prec, recon, dagger, p, fo[p], fi[1 - p], e, no_red(), s, false));
         }
-        for (int p = 0; p < 2; ++p) WL_TRY(unpack(*S, cout, p, fo[p], s));
+        WL_TRY(unpack2(*S, cout, fo[0], fo[1], s));
     }
     return WL_OK;
 }
@@ -1232,13 +1245,13 @@ wl_status wilson_clover_dslash(wl_gauge U, const double *in, double *out, int32_
     WL_TRY(coef_table(*S, {1.0, 0, 0, 0, -kappa}, &e.coef));
     e.nx = 1;
     e.clov = EPI_CLOV_X0;
-    for (int p = 0; p < 2; ++p) WL_TRY(pack(*S, cin, p, fi[p], s));
+    WL_TRY(pack2(*S, cin, fi[0], fi[1], s));
     for (int p = 0; p < 2; ++p) {
         e.X[0] = fi[p];
         // every vector, whatever mask an earlier solve on this set left behind
         WL_TRY(hop(*S, prec, recon, dagger, p, fo[p], fi[1 - p], e, no_red(), s, false));
     }
-    for (int p = 0; p < 2; ++p) WL_TRY(unpack(*S, cout, p, fo[p], s));
+    WL_TRY(unpack2(*S, cout, fo[0], fo[1], s));
     return WL_OK;
 }
 

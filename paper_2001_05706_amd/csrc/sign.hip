@@ -95,8 +95,7 @@ wl_status hw2_scale(wl_gauge U, double rho, const double *v0, hipStream_t s, dou
     WL_TRY(S1->field("pw_u0", P_F64, &u[0]));
     WL_TRY(S1->field("pw_u1", P_F64, &u[1]));
     const double *c[1] = {v0};
-    WL_TRY(pack(*S1, c, 0, u[0], s));
-    WL_TRY(pack(*S1, c, 1, u[1], s));
+    WL_TRY(pack2(*S1, c, u[0], u[1], s));
     double lm = 0;
     WL_TRY(power_lmax(*S1, rho, 18, 100, u, &lm, s));
     *scale = 1.02 * lm;
@@ -186,8 +185,7 @@ wl_status wl_hw2_lmax(wl_gauge U, double rho, const double *v0, int32_t iters, d
     WL_TRY(S->field("pw_u0", P_F64, &u[0]));
     WL_TRY(S->field("pw_u1", P_F64, &u[1]));
     const double *c[1] = {v0};
-    WL_TRY(pack(*S, c, 0, u[0], s));
-    WL_TRY(pack(*S, c, 1, u[1], s));
+    WL_TRY(pack2(*S, c, u[0], u[1], s));
     return power_lmax(*S, rho, 18, iters, u, lmax, s);
 }
 
@@ -229,8 +227,8 @@ wl_status overlap_sign_cheb(wl_gauge U, const double *in, double *out, int32_t n
     for (int p = 0; p < 2; ++p) {
         WL_TRY(S->field("sg_v" + std::to_string(p), prec, &v[p]));
         WL_TRY(S->field("sg_w" + std::to_string(p), prec, &w[p]));
-        WL_TRY(pack(*S, cin, p, v[p], s));
     }
+    WL_TRY(pack2(*S, cin, v[0], v[1], s));
     // deflation: the polynomial acts on v - sum_i xi_i <xi_i, v>
     std::vector<std::complex<double>> c, z;
     if (D.nev) {
@@ -250,7 +248,7 @@ wl_status overlap_sign_cheb(wl_gauge U, const double *in, double *out, int32_t n
         for (size_t k = 0; k < c.size(); ++k) z[k] = (D.lam[k / S->nvec] > 0 ? 1.0 : -1.0) * c[k];
         WL_TRY(defl_axpy(*S, D, prec, w, z, false, s));
     }
-    for (int p = 0; p < 2; ++p) WL_TRY(unpack(*S, cout, p, w[p], s));
+    WL_TRY(unpack2(*S, cout, w[0], w[1], s));
     WL_HIP(hipStreamSynchronize(s));
     return WL_OK;
 }

@@ -244,6 +244,16 @@ WL_HD uint4 ld_stream(const WL_G uint4 *p)
 }
 WL_HD float ld_stream(const WL_G float *p) { return WL_NT_LOAD(float, p); }
 
+// One complex number of a canonical FP64 field, streamed.  A caller's pointer is
+// only known to be aligned to a double, which a 16-byte global access allows.
+typedef double nt_d2u __attribute__((ext_vector_type(2), aligned(8)));
+WL_HD double2 ld_canon(const double *p)
+{
+    const nt_d2u v = WL_NT_LOAD(nt_d2u, p);
+    return double2{v.x, v.y};
+}
+WL_HD void st_canon(double *p, double re, double im) { WL_NT_STORE(nt_d2u, (nt_d2u{re, im}), p); }
+
 // load of a field element: plain, or with the non-temporal hint for fields
 // read once per launch
 template <bool NT, class CH> WL_HD CH ld_field(const WL_G CH *p)

@@ -223,10 +223,12 @@ wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], co
 wl_status blas(ExecSet &S, int op, int prec, const Field *f, int nf, const double *s0, const RedSpec &red,
                hipStream_t s, bool use_active = true, int parity = 0, int bcast = 0);
 wl_status convert(ExecSet &S, const Field &dst, const Field &src, hipStream_t s, bool use_active = true);
-// canonical <-> packed for one parity; canon[i] is the canonical field array of system i
+// canonical <-> packed; canon[i] is the canonical field array of system i: one
+// parity packed, both packed, both unpacked, one unpacked and the other zeroed
 wl_status pack(ExecSet &S, const double *const *canon, int parity, const Field &f, hipStream_t s);
-wl_status unpack(ExecSet &S, double *const *canon, int parity, const Field &f, hipStream_t s);
-wl_status zero_canon(ExecSet &S, double *const *canon, int parity, hipStream_t s);
+wl_status pack2(ExecSet &S, const double *const *canon, const Field &even, const Field &odd, hipStream_t s);
+wl_status unpack2(ExecSet &S, double *const *canon, const Field &even, const Field &odd, hipStream_t s);
+wl_status unpack_zero(ExecSet &S, double *const *canon, int parity, const Field &f, hipStream_t s);
 
 // sum the deferred |r|^2 partials of the last k iterations into hist rows 0..k-1
 wl_status hist_finalize(ExecSet &S, int k, hipStream_t s);

@@ -30,10 +30,14 @@ struct PackArgs {
     const VecDesc *vec;
     const BlkMap *map;
     int32_t nblocks;
-    int32_t parity;
+    int32_t parity;                // parity of f when one parity moves
     void *f;
     float *fn;
     const double *canon[kMaxSys];  // per system: canonical fields of all its rhs
+    int32_t both;                  // f is the even field and f2 the odd one
+    int32_t pad_;
+    void *f2;
+    float *fn2;
 };
 
 // hop.hip
@@ -78,10 +82,10 @@ hipError_t launch_hist_finalize(const double *partials, size_t row, const VecDes
 // y (prec_dst) = x (prec_src), f = {y, x}
 hipError_t launch_convert(int prec_dst, int prec_src, const BlasArgs &a, int block, hipStream_t s);
 
-// pack.hip
+// pack.hip -- the map's blocks hold `block` = 256 sites; unpacking one parity
+// (both == 0) writes zeros on the other
 hipError_t launch_pack_spinor(int prec, const PackArgs &a, int block, hipStream_t s);
 hipError_t launch_unpack_spinor(int prec, const PackArgs &a, int block, hipStream_t s);
-hipError_t launch_zero_canon(const PackArgs &a, int block, hipStream_t s);
 hipError_t launch_pack_gauge(int prec, int recon, const double *U_canon, void *out, const SysDesc &d,
                              hipStream_t s);
 

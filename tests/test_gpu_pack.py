@@ -1,0 +1,61 @@
+"""Canonical <-> packed conversion at the edges of its blocks (128 and 256
+checkerboard sites) and from pointers aligned to a double only.
+
+With parity -1 and kappa = 0 a D-slash call packs its input and unpacks the
+epilogue's 1 * x + 0, so the output is the storage rounding of the input, bit for
+bit (the host model of tests/gpu_util.py; exact in FP64).  A single-parity hop
+must equal the parity of the whole operator's hop and zeros elsewhere.
+"""
+import numpy as np
+import pytest
+
+import lattice_inputs as li
+import oracle
+from tests.gpu_util import need_gpu, quantize_spinor, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# sites per parity: 8 (less than a wave), 120, 128, 264, 256, 528, 840
+SHAPES = [(2, 2, 2, 2), (2, 6, 2, 10), (4, 4, 4, 4), (2, 2, 6, 22), (4, 4, 4, 8), (4, 2, 6, 22), (2, 10, 6, 14)]
+
+
+@pytest.mark.parametrize("L", SHAPES)
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16", "bf16"])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_round_trip(L, prec, offset):
+    w = need_gpu()
+    import torch
+
+    nrhs = 2
+    psi = li.gaussian_spinor(L, 11, nrhs=nrhs)
+    n = psi.size * 2
+    inp = torch.zeros(n + 1, dtype=torch.float64, device="cuda")[offset:offset + n]
+    out = torch.full((n + 3,), float("nan"), dtype=torch.float64, device="cuda")
+    inp.copy_(torch.from_numpy(psi.view(np.float64).reshape(-1)))
+    o = out[offset + 1:offset + 1 + n]
+    g = w.Gauge(L, to_dev(li.haar_links(L, 12)))
+    w.wilson_dslash(g, inp, o, nrhs, 0.0, -1, 0, prec, 12)
+    got = o.cpu().numpy()
+    want = psi.astype(np.complex64).astype(np.complex128) if prec == "f32" else psi
+    want = quantize_spinor(psi, prec) if prec in ("f16", "bf16") else want
+    assert np.array_equal(got, want.view(np.float64).reshape(-1))
+    whole = out.cpu().numpy()  # nothing written outside the field
+    assert np.isnan(np.delete(whole, np.s_[offset + 1:offset + 1 + n])).all()
+    g.close()
+
+
+@pytest.mark.parametrize("L", SHAPES)
+@pytest.mark.parametrize("parity", [0, 1])
+def test_other_parity_is_zero(L, parity):
+    w = need_gpu()
+    import torch
+
+    U, psi = li.haar_links(L, 13), li.gaussian_spinor(L, 14, nrhs=3)
+    g = w.Gauge(L, to_dev(U))
+    out = torch.full((psi.size * 2,), float("nan"), dtype=torch.float64, device="cuda")
+    w.wilson_dslash(g, to_dev(psi), out, 3, 0.0, parity, 0, "f64", 18)
+    got = out.cpu().numpy().view(np.complex128).reshape(psi.shape)
+    ref = oracle.hop(L, U, psi, out_parity=parity)
+    assert np.array_equal(got == 0, ref == 0)
+    assert np.abs(got - ref).max() <= 1e-13 * np.abs(ref).max() * 8  # 8 directions of FP64 products
+    g.close()
