@@ -8,6 +8,8 @@
 // site.  Each link is used once per hop and right-hand side; neighbour
 // spinors are shared by up to 8 output sites through L2, which the XCD-aware
 // block order keeps on one die.
+#include <algorithm>
+
 #include <hip/hip_ext.h>
 
 #include "wl_reduce.h"
@@ -65,6 +67,10 @@ template <int SP, int VAR> struct HopVar {
 };
 constexpr int kHopVariants = 11;
 
+// What a hop's epilogue ends in, one instantiation each: EP_CANON stores the
+// canonical FP64 field instead of the packed one.
+enum { EP_WILSON = 0, EP_CLOVER = 1, EP_CANON = 2, EP_CLOVER_CANON = 3 };
+
 // The fields of the output parity a block computes: the launch's first slot,
 // or for the second half of a twin launch the second one.  X and Xn point into
 // the kernel's argument block, so that an index that varies at run time still
@@ -99,8 +105,9 @@ __device__ __forceinline__ void load_x(const HopArgs &a, const HopIO &f, int j, 
 
 // Everything after the hopping sum at one output site of one vector: the
 // linear-combination epilogue, the store, and the site's reduction values.
-// acc holds H psi (FP16/BF16: already multiplied by the system's c).
-template <int SP, bool CLOV>
+// acc holds H psi (FP16/BF16: already multiplied by the system's c).  CANON:
+// the result stays in acc, rounded as the packed field would hold it.
+template <int SP, bool CLOV, bool CANON = false>
 __device__ __forceinline__ void hop_epilogue(const HopArgs &a, const HopIO &f, const VecDesc &vd, const SysDesc &sd,
                                              int cb, typename SpinorFmt<SP>::real acc[24], double rv[3])
 {
@@ -157,6 +164,12 @@ __device__ __forceinline__ void hop_epilogue(const HopArgs &a, const HopIO &f, c
 #pragma unroll
         for (int k = 0; k < 24; ++k) o[k] = fmadd(x[k], sj, o[k]);
     }
+    if constexpr (CANON) {
+        round_spinor<SP>(o);
+#pragma unroll
+        for (int k = 0; k < 24; ++k) acc[k] = o[k];
+        return;
+    }
     store_spinor<SP, true>((CH *)f.out + voff, f.out_norm ? f.out_norm + vd.site_off : nullptr, sd.stride, cb, o);
     if (a.red.kind != RED_NONE) {
         if (a.red.mode == RM_NORM) {
@@ -180,6 +193,54 @@ __device__ __forceinline__ void hop_epilogue(const HopArgs &a, const HopIO &f, c
     }
 }
 
+// EP_CANON: a wave stores the canonical sites of its 64 consecutive checkerboard
+// indices, through LDS private to the wave, consecutive lanes on consecutive 16
+// bytes.  A single-parity launch also zeroes the sites of the other parity, so
+// the wave writes one contiguous 24 KB; a launch that leaves them writes
+// 192-byte pieces.  Whole lines matter: with 64 bytes of a site per step
+// (a third of the LDS) the 32^3x64 FP16 hop with this epilogue took 190 us,
+// with whole lines 139, the packed hop and a separate unpack 158 (cold operands).
+// The row pitch puts the 16-byte accesses of neighbouring lanes on different banks.
+template <class T> constexpr int kStageRow = sizeof(T) == 4 ? 24 : 26;
+template <class T> constexpr int kStageBytes = 64 * kStageRow<T> * (int)sizeof(T);  // per wave
+
+template <class T>
+__device__ __forceinline__ void store_canon(const HopArgs &a, const HopIO &f, const VecDesc &vd, const SysDesc &sd,
+                                            int cb, bool live, const T o[24], void *stage)
+{
+    const int lane = (int)threadIdx.x & 63;
+    const int c0 = __builtin_amdgcn_readfirstlane(cb - lane);
+    const int n = live ? min(64, sd.Vh - c0) : 0;  // sites of the wave (uniform)
+    if (n <= 0) return;
+    // which site of each pair is the output's
+    const unsigned long long slots = __ballot(cb_coords(sd, min(cb, sd.Vh - 1), f.parity).x & 1);
+    double *base = a.canon + ((size_t)vd.rhs * (size_t)sd.Vh + (size_t)c0) * 48;
+    const T *st = (const T *)stage;
+    T *row = (T *)stage + lane * kStageRow<T>;
+    wave_lds_fence();  // an earlier vector's sites may still be read
+#pragma unroll
+    for (int k = 0; k < 24; ++k) row[k] = o[k];
+    wave_lds_fence();
+    if (a.canon_zero) {
+#pragma unroll
+        for (int i = 0; i < 24; ++i) {
+            const int e = i * 64 + lane, j = e / 24, r = e % 24;  // pair, 16-byte element of the pair
+            const int q = r < 12 ? r : r - 12;
+            const bool mine = (int)((slots >> (j & 63)) & 1) == (r >= 12);
+            const T *w = st + j * kStageRow<T> + 2 * q;
+            if (j < n) st_canon(base + 2 * e, mine ? (double)w[0] : 0.0, mine ? (double)w[1] : 0.0);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 12; ++i) {
+            const int e = i * 64 + lane, j = e / 12, q = e % 12;
+            const T *w = st + j * kStageRow<T> + 2 * q;
+            if (j < n)
+                st_canon(base + 48 * j + 24 * (int)((slots >> (j & 63)) & 1) + 2 * q, (double)w[0], (double)w[1]);
+        }
+    }
+}
+
 template <int SP>
 __device__ __forceinline__ HopSite hop_input(const HopArgs &a, const HopIO &f, const VecDesc &vd, const SysDesc &sd)
 {
@@ -195,11 +256,12 @@ __device__ __forceinline__ HopSite hop_input(const HopArgs &a, const HopIO &f, c
     return hs;
 }
 
-template <int SP, int GP, int R, bool DAG, int VAR, bool CLOV>
+template <int SP, int GP, int R, bool DAG, int VAR, int EP>
 __global__ __launch_bounds__((HopVar<SP, VAR>::max_block)) __attribute__((amdgpu_waves_per_eu(HopVar<SP, VAR>::waves)))
 void k_hop(HopArgs a)
 {
     using T = typename SpinorFmt<SP>::real;
+    constexpr bool CLOV = EP == EP_CLOVER || EP == EP_CLOVER_CANON, CANON = EP >= EP_CANON;
 
     constexpr bool RW = HopVar<SP, VAR>::rhs_waves;
     constexpr bool PAIR = HopVar<SP, VAR>::rhs_pairs;
@@ -245,23 +307,33 @@ void k_hop(HopArgs a)
         if (!live0 && !live1) return;
         const VecDesc vd1 = a.vec[has1 ? v1 : bm.v];
         double rv0[3] = {0.0, 0.0, 0.0}, rv1[3] = {0.0, 0.0, 0.0};
+        T acc0[24], acc1[24];
         if (cb < sd.Vh) {
             const HopSite hs0 = hop_input<SP>(a, f, vd, sd), hs1 = hop_input<SP>(a, f, vd1, sd);
-            T acc0[24], acc1[24];
             hop_site2<SP, GP, R, DAG, HopVar<SP, VAR>::nt>(sd, hs0, hs1, f.parity, cb, acc0, acc1);
-            if (live0) hop_epilogue<SP, CLOV>(a, f, vd, sd, cb, acc0, rv0);
-            if (live1) hop_epilogue<SP, CLOV>(a, f, vd1, sd, cb, acc1, rv1);
+            if (live0) hop_epilogue<SP, CLOV, CANON>(a, f, vd, sd, cb, acc0, rv0);
+            if (live1) hop_epilogue<SP, CLOV, CANON>(a, f, vd1, sd, cb, acc1, rv1);
+        }
+        if constexpr (CANON) {
+            extern __shared__ uint4 s_stage[];
+            void *stage = (char *)s_stage + (threadIdx.x >> 6) * kStageBytes<T>;
+            store_canon<T>(a, f, vd, sd, cb, live0, acc0, stage);
+            store_canon<T>(a, f, vd1, sd, cb, live1, acc1, stage);
         }
         // live0 and live1 are uniform over the block
         if (a.red.kind != RED_NONE && live0) block_reduce_store_n(a.red, vd.pslot0, bm.lblk, rv0);
         if (a.red.kind != RED_NONE && live1) block_reduce_store_n(a.red, vd1.pslot0, bm.lblk, rv1);
     } else {
         double rv[3] = {0.0, 0.0, 0.0};
+        T acc[24];
         if (valid && cb < sd.Vh) {
             const HopSite hs = hop_input<SP>(a, f, vd, sd);
-            T acc[24];
             hop_site<SP, GP, R, DAG, HopVar<SP, VAR>::fence, HopVar<SP, VAR>::nt>(sd, hs, f.parity, cb, acc);
-            hop_epilogue<SP, CLOV>(a, f, vd, sd, cb, acc, rv);
+            hop_epilogue<SP, CLOV, CANON>(a, f, vd, sd, cb, acc, rv);
+        }
+        if constexpr (CANON) {
+            extern __shared__ uint4 s_stage[];
+            store_canon<T>(a, f, vd, sd, cb, valid, acc, (char *)s_stage + (threadIdx.x >> 6) * kStageBytes<T>);
         }
         if constexpr (RW) {
             if (a.red.kind != RED_NONE && valid) wave_reduce_store_n(a.red, vd.pslot0, bm.lblk, rv);
@@ -315,13 +387,13 @@ __device__ __forceinline__ void lds_dir(const HopSite &hs, int lane, const float
     hop_accumulate<SP, MU, DIR, SG>(u, h0, h1, f, acc);
 }
 
-template <int SP, int GP, int R, bool DAG>
+template <int SP, int GP, int R, bool DAG, bool CANON>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void k_hop_lds(HopArgs a)
 {
     static_assert(SP != P_F64, "variant 8 stages FP32 links");
-    __shared__ float2 s_u[8][9][64];
-    __shared__ int s_n[8][64];
-    static_assert(sizeof(s_u) + sizeof(s_n) == kLdsLinkBytes, "LDS layout of variant 8");
+    extern __shared__ uint4 s_dyn[];
+    auto s_u = reinterpret_cast<float2(*)[9][64]>(s_dyn);
+    auto s_n = reinterpret_cast<int(*)[64]>(s_u + 8);
     const int lb = xcd_remap(blockIdx.x, a.nblocks);
     const int half = a.nblocks >> 1;
     const bool second = a.twin && lb >= half;
@@ -369,10 +441,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     const int v = bm.v + w;
     const bool valid = live(v);
     double rv[3] = {0.0, 0.0, 0.0};
+    float acc[24];
     if (valid && cb < sd.Vh) {
         const VecDesc vd = a.vec[v];
         const HopSite hs = hop_input<SP>(a, f, vd, sd);
-        float acc[24];
 #pragma unroll
         for (int k = 0; k < 24; ++k) acc[k] = 0.f;
         // two directions' operands in flight per wave, as variant 6
@@ -388,7 +460,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
         lds_dir<SP, 3, +1, DAG>(hs, lane, s_u[6], s_n[6], acc);
         lds_dir<SP, 3, -1, DAG>(hs, lane, s_u[7], s_n[7], acc);
         sched_fence(acc);
-        hop_epilogue<SP, false>(a, f, vd, sd, cb, acc, rv);
+        hop_epilogue<SP, false, CANON>(a, f, vd, sd, cb, acc, rv);
+    }
+    if constexpr (CANON) {
+        __syncthreads();  // the waves' stages take the place of the links
+        if (valid) store_canon<float>(a, f, a.vec[v], sd, cb, true, acc, (char *)s_dyn + w * kStageBytes<float>);
     }
     if (a.red.kind != RED_NONE && valid) wave_reduce_store_n(a.red, a.vec[v].pslot0, bm.lblk, rv);
     if (a.stamps) {
@@ -460,7 +536,7 @@ __device__ __forceinline__ void pencil_t(const HopSite &hs, int parity, int cb, 
     hop_accumulate<SP, 3, DIR, SG>(u, h0, h1, f, acc);
 }
 
-template <int SP, int GP, int R, bool DAG, int VAR>
+template <int SP, int GP, int R, bool DAG, int VAR, bool CANON>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(HopVar<SP, VAR>::waves)))
 void k_hop_pencil(HopArgs a)
 {
@@ -520,7 +596,11 @@ void k_hop_pencil(HopArgs a)
     sched_fence(acc);
 
     double rv[3] = {0.0, 0.0, 0.0};
-    hop_epilogue<SP, false>(a, f, vd, sd, cb, acc, rv);
+    hop_epilogue<SP, false, CANON>(a, f, vd, sd, cb, acc, rv);
+    if constexpr (CANON) {
+        // (behind the rows of the block's waves, which other waves may still read)
+        store_canon<float>(a, f, vd, sd, cb, true, acc, rows + nw * P::bytes + w * kStageBytes<float>);
+    }
     if (a.red.kind != RED_NONE) block_reduce_store_n(a.red, vd.pslot0, bm.lblk, rv);
     if (a.stamps) {
         __syncthreads();
@@ -541,19 +621,52 @@ static void dispatch(K kernel, const HopArgs &a, int block, hipStream_t s, hipEv
         hipLaunchKernelGGL(kernel, dim3(a.nblocks), dim3(block), lds, s, a);
 }
 
+template <int SP, int GP, int R, int VAR, int EP>
+static hipError_t launch_hop_ep(bool dag, const HopArgs &a, int block, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+{
+    const unsigned lds = EP >= EP_CANON ? (unsigned)(block / 64) * kStageBytes<typename SpinorFmt<SP>::real> : 0;
+    if (dag)
+        dispatch(k_hop<SP, GP, R, true, VAR, EP>, a, block, s, e0, e1, lds);
+    else
+        dispatch(k_hop<SP, GP, R, false, VAR, EP>, a, block, s, e0, e1, lds);
+    return hipGetLastError();
+}
+
 template <int SP, int GP, int R, int VAR>
 static hipError_t launch_hop_v(bool dag, bool clov, const HopArgs &a, int block, hipStream_t s, hipEvent_t e0,
                                hipEvent_t e1)
 {
-    // the clover epilogue is a separate instantiation: it needs registers the Wilson kernels do not
-    if (dag && clov)
-        dispatch(k_hop<SP, GP, R, true, VAR, true>, a, block, s, e0, e1);
-    else if (dag)
-        dispatch(k_hop<SP, GP, R, true, VAR, false>, a, block, s, e0, e1);
-    else if (clov)
-        dispatch(k_hop<SP, GP, R, false, VAR, true>, a, block, s, e0, e1);
+    // the clover epilogue is a separate instantiation: it needs registers the Wilson
+    // kernels do not, more than the one-direction variants 1 and 2 leave
+    if (clov) {
+        if constexpr (VAR == 1 || VAR == 2) return hipErrorInvalidValue;
+        else
+            return a.canon ? launch_hop_ep<SP, GP, R, VAR, EP_CLOVER_CANON>(dag, a, block, s, e0, e1)
+                           : launch_hop_ep<SP, GP, R, VAR, EP_CLOVER>(dag, a, block, s, e0, e1);
+    }
+    return a.canon ? launch_hop_ep<SP, GP, R, VAR, EP_CANON>(dag, a, block, s, e0, e1)
+                   : launch_hop_ep<SP, GP, R, VAR, EP_WILSON>(dag, a, block, s, e0, e1);
+}
+
+template <int SP, int GP, int R, bool CANON>
+static hipError_t launch_hop_lds(bool dag, const HopArgs &a, int block, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+{
+    const unsigned lds = std::max(kLdsLinkBytes, CANON ? block / 64 * kStageBytes<float> : 0);
+    if (dag)
+        dispatch(k_hop_lds<SP, GP, R, true, CANON>, a, block, s, e0, e1, lds);
     else
-        dispatch(k_hop<SP, GP, R, false, VAR, false>, a, block, s, e0, e1);
+        dispatch(k_hop_lds<SP, GP, R, false, CANON>, a, block, s, e0, e1, lds);
+    return hipGetLastError();
+}
+
+template <int SP, int GP, int R, int VAR, bool CANON>
+static hipError_t launch_hop_pencil(bool dag, const HopArgs &a, int block, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+{
+    const unsigned lds = (unsigned)(block / 64) * (PencilRow<SP>::bytes + (CANON ? kStageBytes<float> : 0));
+    if (dag)
+        dispatch(k_hop_pencil<SP, GP, R, true, VAR, CANON>, a, block, s, e0, e1, lds);
+    else
+        dispatch(k_hop_pencil<SP, GP, R, false, VAR, CANON>, a, block, s, e0, e1, lds);
     return hipGetLastError();
 }
 
@@ -573,11 +686,8 @@ static hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, i
     case 8:
         if constexpr (SP != P_F64) {
             if (clov || block % 64 != 0 || block > 1024) return hipErrorInvalidValue;
-            if (dag)
-                dispatch(k_hop_lds<SP, GP, R, true>, a, block, s, e0, e1);
-            else
-                dispatch(k_hop_lds<SP, GP, R, false>, a, block, s, e0, e1);
-            return hipGetLastError();
+            return a.canon ? launch_hop_lds<SP, GP, R, true>(dag, a, block, s, e0, e1)
+                           : launch_hop_lds<SP, GP, R, false>(dag, a, block, s, e0, e1);
         }
         return hipErrorInvalidValue;
     case 9:
@@ -585,14 +695,11 @@ static hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, i
         if constexpr (SP != P_F64) {
             // 2 to 8 slices per block, one vector per block, no twin launch
             if (clov || a.twin || block % 64 != 0 || block < 128 || block > 512) return hipErrorInvalidValue;
-            const unsigned lds = (unsigned)(block / 64 * PencilRow<SP>::bytes);
             if (var == 9)
-                dispatch(dag ? k_hop_pencil<SP, GP, R, true, 9> : k_hop_pencil<SP, GP, R, false, 9>, a, block, s, e0,
-                         e1, lds);
-            else
-                dispatch(dag ? k_hop_pencil<SP, GP, R, true, 10> : k_hop_pencil<SP, GP, R, false, 10>, a, block, s,
-                         e0, e1, lds);
-            return hipGetLastError();
+                return a.canon ? launch_hop_pencil<SP, GP, R, 9, true>(dag, a, block, s, e0, e1)
+                               : launch_hop_pencil<SP, GP, R, 9, false>(dag, a, block, s, e0, e1);
+            return a.canon ? launch_hop_pencil<SP, GP, R, 10, true>(dag, a, block, s, e0, e1)
+                           : launch_hop_pencil<SP, GP, R, 10, false>(dag, a, block, s, e0, e1);
         }
         return hipErrorInvalidValue;
     }

@@ -814,12 +814,14 @@ wl_status hop(ExecSet &S, int prec, int recon, bool dag, int par, const Field &o
         a.red = rs;
         a.one = S.nvec == 1;
         a.stream = S.stream_fields(prec);
+        a.canon = e.canon;
+        a.canon_zero = e.canon_zero;
         return a;
     };
     // tuned per epilogue shape: a hop that also reads X fields and reduces may
     // prefer another variant than a plain one
     const std::string key = hop_key(S, prec, recon, dag) + (clov ? "/clov" : "") + "/x" + std::to_string(e.nx) +
-                            (red.kind != RED_NONE ? "/r" : "");
+                            (red.kind != RED_NONE ? "/r" : "") + (e.canon ? "/canon" : "");
     const std::vector<int> cands = hop_cands(S, prec, clov);
     const int cfg = tuned_block(key, cands, s, [&](int c) -> hipError_t {
         const Layout *L = nullptr;
@@ -884,10 +886,11 @@ wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], co
 {
     // one launch for both output parities: a single-vector set has only one
     // wave per SIMD per parity on a small lattice, and the two halves of a
-    // whole-lattice operator are independent.  Otherwise (several vectors, a
-    // clover term, different epilogue shapes, kernel timing) two launches.
-    const bool clov = (e[0].clov != 0 || e[1].clov != 0) && S.has_clover;
-    if (S.nvec != 1 || clov || prof().on || e[0].nx != e[1].nx || e[0].g5 != e[1].g5 || e[0].coef != e[1].coef) {
+    // whole-lattice operator are independent.  Otherwise (several vectors,
+    // different epilogue shapes, kernel timing) two launches.
+    const bool clov = e[0].clov != 0 && S.has_clover;
+    if (S.nvec != 1 || prof().on || e[0].nx != e[1].nx || e[0].g5 != e[1].g5 || e[0].coef != e[1].coef ||
+        e[0].clov != e[1].clov || e[0].canon != e[1].canon) {
         for (int p = 0; p < 2; ++p) WL_TRY(hop(S, prec, recon, dag, p, out[p], in[1 - p], e[p], no_red(), s, use_active));
         return WL_OK;
     }
@@ -908,7 +911,9 @@ wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], co
         a.out_norm = out[0].n;
         a.epi.nx = e[0].nx;
         a.epi.g5 = e[0].g5;
+        a.epi.clov = clov ? e[0].clov : 0;
         a.epi.coef = e[0].coef;
+        a.canon = e[0].canon;
         for (int j = 0; j < 4; ++j) {
             a.epi.X[j] = e[0].X[j].p;
             a.epi.Xn[j] = e[0].X[j].n;
@@ -925,18 +930,20 @@ wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], co
         a.out_norm_b = out[1].n;
         return a;
     };
-    const std::string key = hop_key(S, prec, recon, dag) + "/twin/x" + std::to_string(e[0].nx);
-    std::vector<int> cands = hop_candidates(prec);
+    const std::string key = hop_key(S, prec, recon, dag) + (clov ? "/clov" : "") + "/twin/x" +
+                            std::to_string(e[0].nx) + (e[0].canon ? "/canon" : "");
+    std::vector<int> cands = hop_cands(S, prec, clov);
     cands.erase(std::remove_if(cands.begin(), cands.end(), [](int c) { return cfg_var(c) >= 6; }), cands.end());
     const int cfg = tuned_block(key, cands, s, [&](int c) -> hipError_t {
         const Layout *L = nullptr;
         if (hop_layout(S, c, &L) != WL_OK) return hipErrorOutOfMemory;
-        return launch_hop(prec, recon, dag, false, cfg_var(c), mk(L), cfg_block(c), s);
+        return launch_hop(prec, recon, dag, clov, cfg_var(c), mk(L), cfg_block(c), s);
     });
     const Layout *L = nullptr;
     WL_TRY(hop_layout(S, cfg, &L));
+    if (clov) g_bytes_acc += 2 * clover_bytes(S, prec, use_active);
     g_bytes_acc += 2 * (hop_bytes(S, prec, recon, use_active) + blas_bytes(S, prec, e[0].nx, use_active));
-    WL_HIP(launch_hop(prec, recon, dag, false, cfg_var(cfg), mk(L), cfg_block(cfg), s));
+    WL_HIP(launch_hop(prec, recon, dag, clov, cfg_var(cfg), mk(L), cfg_block(cfg), s));
     return WL_OK;
 }
 
@@ -1067,15 +1074,6 @@ wl_status unpack2(ExecSet &S, double *const *canon, const Field &even, const Fie
     return WL_OK;
 }
 
-wl_status unpack_zero(ExecSet &S, double *const *canon, int parity, const Field &f, hipStream_t s)
-{
-    PackArgs a;
-    WL_TRY(pack_args(S, (const void *const *)canon, parity, f, s, &a));
-    g_bytes_acc += 2 * blas_bytes(S, P_F64, 1, false) + blas_bytes(S, f.prec, 1, false);
-    WL_HIP(launch_unpack_spinor(f.prec, a, kBlasBlock, s));
-    return WL_OK;
-}
-
 // ------------------------------------------------------------------ validation helpers
 
 wl_status check_gauge(wl_gauge U)
@@ -1184,30 +1182,30 @@ wl_status wilson_dslash(wl_gauge U, const double *in, double *out, int32_t nrhs,
     hipStream_t s = (hipStream_t)stream;
     ExecSet *S = nullptr;
     WL_TRY(get_set({SysEntry{U, nrhs, kappa}}, &S));
-    Field fi[2], fo[2];
+    // the hop writes the canonical output itself: no packed result is stored and read back
+    Field fi[2];
+    const double *cin[1] = {in};
+    Epi e[2];
+    e[0].canon = e[1].canon = out;
+    if (parity >= 0) {
+        WL_TRY(S->field("dsl_in" + std::to_string(1 - parity), prec, &fi[1 - parity]));
+        WL_TRY(coef_table(*S, {0, 0, 0, 0, 1.0}, &e[0].coef));
+        e[0].canon_zero = 1;
+        WL_TRY(pack(*S, cin, 1 - parity, fi[1 - parity], s));
+        WL_TRY(hop(*S, prec, recon, dagger, parity, Field(), fi[1 - parity], e[0], no_red(), s, false));
+        return WL_OK;
+    }
+    const double *coef = nullptr;
+    WL_TRY(coef_table(*S, {1.0, 0, 0, 0, -kappa}, &coef));
     for (int p = 0; p < 2; ++p) {
         WL_TRY(S->field("dsl_in" + std::to_string(p), prec, &fi[p]));
-        WL_TRY(S->field("dsl_out" + std::to_string(p), prec, &fo[p]));
+        e[p].coef = coef;
+        e[p].nx = 1;
+        e[p].X[0] = fi[p];
     }
-    const double *cin[1] = {in};
-    double *cout[1] = {out};
-    Epi e;
-    if (parity >= 0) {
-        WL_TRY(coef_table(*S, {0, 0, 0, 0, 1.0}, &e.coef));
-        WL_TRY(pack(*S, cin, 1 - parity, fi[1 - parity], s));
-        WL_TRY(hop(*S, prec, recon, dagger, parity, fo[parity], fi[1 - parity], e, no_red(), s, false));
-        WL_TRY(unpack_zero(*S, cout, parity, fo[parity], s));
-    } else {
-        WL_TRY(coef_table(*S, {1.0, 0, 0, 0, -kappa}, &e.coef));
-        e.nx = 1;
-        WL_TRY(pack2(*S, cin, fi[0], fi[1], s));
-        for (int p = 0; p < 2; ++p) {
-            e.X[0] = fi[p];
-            WL_TRY(hop(*S, prec, recon, dagger, p, fo[p], fi[1 - p], e, no_red(), s, false));
-        }
-        WL_TRY(unpack2(*S, cout, fo[0], fo[1], s));
-    }
-    return WL_OK;
+    WL_TRY(pack2(*S, cin, fi[0], fi[1], s));
+    const Field fo[2];
+    return hop2(*S, prec, recon, dagger, fo, fi, e, s, false);
 }
 
 double wl_hop_bytes_per_site(wl_prec prec, int32_t recon, int32_t nrhs)
@@ -1233,26 +1231,24 @@ wl_status wilson_clover_dslash(wl_gauge U, const double *in, double *out, int32_
     hipStream_t s = (hipStream_t)stream;
     ExecSet *S = nullptr;
     WL_TRY(get_set({SysEntry{U, nrhs, kappa, csw}}, &S));
-    Field fi[2], fo[2];
+    // out_p = A in_p - kappa hop(in)_p, on every vector, whatever mask an earlier
+    // solve on this set left behind
+    Field fi[2];
+    const double *cin[1] = {in};
+    Epi e[2];
+    const double *coef = nullptr;
+    WL_TRY(coef_table(*S, {1.0, 0, 0, 0, -kappa}, &coef));
     for (int p = 0; p < 2; ++p) {
         WL_TRY(S->field("dsl_in" + std::to_string(p), prec, &fi[p]));
-        WL_TRY(S->field("dsl_out" + std::to_string(p), prec, &fo[p]));
+        e[p].coef = coef;
+        e[p].nx = 1;
+        e[p].clov = EPI_CLOV_X0;
+        e[p].X[0] = fi[p];
+        e[p].canon = out;
     }
-    const double *cin[1] = {in};
-    double *cout[1] = {out};
-    // out_p = A in_p - kappa hop(in)_p
-    Epi e;
-    WL_TRY(coef_table(*S, {1.0, 0, 0, 0, -kappa}, &e.coef));
-    e.nx = 1;
-    e.clov = EPI_CLOV_X0;
     WL_TRY(pack2(*S, cin, fi[0], fi[1], s));
-    for (int p = 0; p < 2; ++p) {
-        e.X[0] = fi[p];
-        // every vector, whatever mask an earlier solve on this set left behind
-        WL_TRY(hop(*S, prec, recon, dagger, p, fo[p], fi[1 - p], e, no_red(), s, false));
-    }
-    WL_TRY(unpack2(*S, cout, fo[0], fo[1], s));
-    return WL_OK;
+    const Field fo[2];
+    return hop2(*S, prec, recon, dagger, fo, fi, e, s, false);
 }
 
 wl_status wl_prof_enable(int32_t on)

@@ -374,6 +374,23 @@ WL_HD void load_spinor_raw(const void *base, const float *norm, int stride, int 
     }
 }
 
+// The 12 packed words and the norm of a half-precision site.  A zero site
+// stores zeros and a zero norm (point sources are zero almost everywhere).
+// Stored value: v * inv with inv = 1/m correctly rounded; for FP16 the multiply
+// and the conversion compile to one mixed-precision fma (v_fma_mixlo/hi_f16), so
+// the exact product is rounded once to nearest even; BF16 rounds the FP32
+// product to nearest even on its bits.
+template <int P> WL_HD void quantize_site(const float v[24], uint32_t q[12], float *norm)
+{
+    float m = 0.f;
+#pragma unroll
+    for (int k = 0; k < 24; ++k) m = fmaxf(m, fabsf(v[k]));
+    const float inv = m > 0.f ? 1.0f / m : 0.f;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) q[k] = pack2<P>(v[2 * k] * inv, v[2 * k + 1] * inv);
+    *norm = m;
+}
+
 template <int P, bool NT = false>
 WL_HD void store_spinor(void *base, float *norm, int stride, int cb, const typename SpinorFmt<P>::real v[24])
 {
@@ -387,22 +404,27 @@ WL_HD void store_spinor(void *base, float *norm, int stride, int cb, const typen
         for (int c = 0; c < 6; ++c)
             st_out<NT>(row_elem<float4>(b, c, stride, cb), float4{v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]});
     } else {
-        float m = 0.f;
-#pragma unroll
-        for (int k = 0; k < 24; ++k) m = fmaxf(m, fabsf(v[k]));
-        // a zero site stores zeros and a zero norm (point sources are zero almost everywhere).
-        // Stored value: v * inv with inv = 1/m correctly rounded; for FP16 the multiply
-        // and the conversion compile to one mixed-precision fma (v_fma_mixlo/hi_f16), so
-        // the exact product is rounded once to nearest even; BF16 rounds the FP32
-        // product to nearest even on its bits.
-        const float inv = m > 0.f ? 1.0f / m : 0.f;
+        float m;
+        uint32_t q[12];
+        quantize_site<P>(v, q, &m);
         st_out<NT>(row_elem<float>(norm, 0, 0, cb), m);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            uint32_t q[4];
+        for (int c = 0; c < 3; ++c)
+            st_out<NT>(row_elem<uint4>(b, c, stride, cb), uint4{q[4 * c], q[4 * c + 1], q[4 * c + 2], q[4 * c + 3]});
+    }
+}
+
+// v as a store to the packed field and a load from it would leave it
+template <int P> WL_HD void round_spinor(typename SpinorFmt<P>::real v[24])
+{
+    if constexpr (P == P_F16 || P == P_BF16) {
+        float m;
+        uint32_t q[12];
+        quantize_site<P>(v, q, &m);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) q[k] = pack2<P>(v[8 * c + 2 * k] * inv, v[8 * c + 2 * k + 1] * inv);
-            st_out<NT>(row_elem<uint4>(b, c, stride, cb), uint4{q[0], q[1], q[2], q[3]});
+        for (int k = 0; k < 12; ++k) {
+            v[2 * k] = lo16_to_float<P>(q[k]) * m;
+            v[2 * k + 1] = hi16_to_float<P>(q[k]) * m;
         }
     }
 }

@@ -207,6 +207,10 @@ struct Epi {
     int clov = 0;  // EPI_CLOV_* bits (act only on systems with a clover term)
     const double *coef = nullptr;  // device [nsys][5]
     Field X[4];
+    // the result goes to this canonical field instead of `out` (one system, no
+    // reduction); canon_zero: with zeros on the other parity
+    double *canon = nullptr;
+    int canon_zero = 0;
 };
 
 RedSpec no_red();
@@ -224,11 +228,10 @@ wl_status blas(ExecSet &S, int op, int prec, const Field *f, int nf, const doubl
                hipStream_t s, bool use_active = true, int parity = 0, int bcast = 0);
 wl_status convert(ExecSet &S, const Field &dst, const Field &src, hipStream_t s, bool use_active = true);
 // canonical <-> packed; canon[i] is the canonical field array of system i: one
-// parity packed, both packed, both unpacked, one unpacked and the other zeroed
+// parity packed, both packed, both unpacked
 wl_status pack(ExecSet &S, const double *const *canon, int parity, const Field &f, hipStream_t s);
 wl_status pack2(ExecSet &S, const double *const *canon, const Field &even, const Field &odd, hipStream_t s);
 wl_status unpack2(ExecSet &S, double *const *canon, const Field &even, const Field &odd, hipStream_t s);
-wl_status unpack_zero(ExecSet &S, double *const *canon, int parity, const Field &f, hipStream_t s);
 
 // sum the deferred |r|^2 partials of the last k iterations into hist rows 0..k-1
 wl_status hist_finalize(ExecSet &S, int k, hipStream_t s);

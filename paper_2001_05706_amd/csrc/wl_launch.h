@@ -136,6 +136,12 @@ struct HopArgs {
     float *out_norm_b;
     const void *X_b[4];
     const float *Xn_b[4];
+    // canon (single-system sets, no reduction; null: off): the result goes to
+    // this canonical FP64 field of all vectors instead of `out`; canon_zero:
+    // with zeros on the other parity
+    double *canon;
+    int32_t canon_zero;
+    int32_t pad_;
 };
 
 }  // namespace wl

@@ -10,6 +10,15 @@
 
 namespace wl {
 
+// Orders a wave's LDS writes before its later LDS reads by other lanes: the
+// hardware runs one wave's LDS accesses in order, so only the compiler is held.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ double wave_sum(double v)
 {
 #pragma unroll
