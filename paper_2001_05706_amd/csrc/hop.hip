@@ -72,7 +72,7 @@ constexpr int kHopVariants = 11;
 enum { EP_WILSON = 0, EP_CLOVER = 1, EP_CANON = 2, EP_CLOVER_CANON = 3 };
 
 // The fields of the output parity a block computes: the launch's first slot,
-// or for the second half of a twin launch the second one.  X and Xn point into
+// or for the odd blocks of a twin launch the second one.  X and Xn point into
 // the kernel's argument block, so that an index that varies at run time still
 // reads them with scalar loads.
 struct HopIO {
@@ -266,13 +266,12 @@ void k_hop(HopArgs a)
     constexpr bool RW = HopVar<SP, VAR>::rhs_waves;
     constexpr bool PAIR = HopVar<SP, VAR>::rhs_pairs;
     const int lb = xcd_remap(blockIdx.x, a.nblocks);
-    // a twin launch's second half computes the other output parity from the
-    // second field slot (the selection is uniform over the block)
-    const int half = a.nblocks >> 1;
-    const bool second = a.twin && lb >= half;
+    // a twin launch's odd blocks compute the other output parity from the second
+    // field slot (the selection is uniform over the block)
+    const bool second = a.twin && (lb & 1);
     const HopIO f = second ? HopIO{1 - a.parity, a.in_b, a.in_norm_b, a.out_b, a.out_norm_b, a.X_b, a.Xn_b}
                            : HopIO{a.parity, a.in, a.in_norm, a.out, a.out_norm, a.epi.X, a.epi.Xn};
-    const BlkMap bm = a.map[second ? lb - half : lb];
+    const BlkMap bm = a.map[a.twin ? lb >> 1 : lb];
     int v = bm.v, cb;
     bool valid = true;
     if constexpr (RW) {
@@ -395,11 +394,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     auto s_u = reinterpret_cast<float2(*)[9][64]>(s_dyn);
     auto s_n = reinterpret_cast<int(*)[64]>(s_u + 8);
     const int lb = xcd_remap(blockIdx.x, a.nblocks);
-    const int half = a.nblocks >> 1;
-    const bool second = a.twin && lb >= half;
+    const bool second = a.twin && (lb & 1);
     const HopIO f = second ? HopIO{1 - a.parity, a.in_b, a.in_norm_b, a.out_b, a.out_norm_b, a.X_b, a.Xn_b}
                            : HopIO{a.parity, a.in, a.in_norm, a.out, a.out_norm, a.epi.X, a.epi.Xn};
-    const BlkMap bm = a.map[second ? lb - half : lb];
+    const BlkMap bm = a.map[a.twin ? lb >> 1 : lb];
     const int lane = (int)threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int nw = (int)blockDim.x >> 6;
@@ -416,8 +414,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     // stage: wave w rebuilds the links of directions w, w + nw, ... (all waves
     // take part, also those whose right-hand side is idle).  When the block
     // holds every right-hand side of its system, no other block reads these
-    // links: they are loaded non-temporally.
-    const bool nt = a.vec[bm.v].rhs == 0 && (bm.v + nw >= a.nvec || a.vec[bm.v + nw].sys != sys);
+    // links (in a twin launch its twin does): they are loaded non-temporally.
+    const bool nt = !a.twin && a.vec[bm.v].rhs == 0 && (bm.v + nw >= a.nvec || a.vec[bm.v + nw].sys != sys);
     if (cb < sd.Vh) {
         const Site st = cb_coords(sd, cb, f.parity);
         HopSite hl;
@@ -549,12 +547,14 @@ void k_hop_pencil(HopArgs a)
     unsigned char *rows = reinterpret_cast<unsigned char *>(s_pencil);
 
     const int lb = xcd_remap(blockIdx.x, a.nblocks);
-    const BlkMap bm = a.map[lb];
+    const bool second = a.twin && (lb & 1);
+    const HopIO f = second ? HopIO{1 - a.parity, a.in_b, a.in_norm_b, a.out_b, a.out_norm_b, a.X_b, a.Xn_b}
+                           : HopIO{a.parity, a.in, a.in_norm, a.out, a.out_norm, a.epi.X, a.epi.Xn};
+    const BlkMap bm = a.map[a.twin ? lb >> 1 : lb];
     if (a.active && !a.active[a.one ? 0 : bm.v]) return;  // uniform over the block
     const VecDesc vd = a.vec[a.one ? 0 : bm.v];
     const SysDesc sd = a.sys[a.one ? 0 : vd.sys];
     if (a.stamps && threadIdx.x == 0) a.stamps[2 * lb] = (unsigned long long)wall_clock64();
-    const HopIO f{a.parity, a.in, a.in_norm, a.out, a.out_norm, a.epi.X, a.epi.Xn};
     const int lane = (int)threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int nw = (int)blockDim.x >> 6;
@@ -693,8 +693,8 @@ static hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, i
     case 9:
     case 10:
         if constexpr (SP != P_F64) {
-            // 2 to 8 slices per block, one vector per block, no twin launch
-            if (clov || a.twin || block % 64 != 0 || block < 128 || block > 512) return hipErrorInvalidValue;
+            // 2 to 8 slices per block, one vector per block
+            if (clov || block % 64 != 0 || block < 128 || block > 512) return hipErrorInvalidValue;
             if (var == 9)
                 return a.canon ? launch_hop_pencil<SP, GP, R, 9, true>(dag, a, block, s, e0, e1)
                                : launch_hop_pencil<SP, GP, R, 9, false>(dag, a, block, s, e0, e1);

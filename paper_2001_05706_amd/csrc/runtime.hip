@@ -706,7 +706,9 @@ std::string hop_key(const ExecSet &S, int prec, int recon, bool dag)
 int cfg_make(int var, int block, int col) { return var | (block << 4) | (col << 16); }
 int cfg_var(int c) { return c & 15; }
 int cfg_block(int c) { return (c >> 4) & 4095; }
-int cfg_col(int c) { return c >> 16; }
+int cfg_col(int c) { return (c >> 16) & 4095; }
+// whole-lattice operators (hop2): the parities in two launches instead of one
+constexpr int kCfgSplit = 1 << 29;
 
 // Candidate configurations: every variant x block size x column height of 4 or
 // 16 z-planes (taller columns sweep longer runs of consecutive sites: FP64
@@ -884,46 +886,50 @@ wl_status hop(ExecSet &S, int prec, int recon, bool dag, int par, const Field &o
 wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], const Field in[2], const Epi e[2],
                hipStream_t s, bool use_active)
 {
-    // one launch for both output parities: a single-vector set has only one
-    // wave per SIMD per parity on a small lattice, and the two halves of a
-    // whole-lattice operator are independent.  Otherwise (several vectors,
-    // different epilogue shapes, kernel timing) two launches.
+    // one launch for both output parities, which share their operands (see
+    // HopArgs::twin).  With several vectors the tuner decides between one launch
+    // and two: the parities' fields then compete for the XCD's L2 (FP32 recon-12,
+    // one launch against two: 4 RHS at 24^3x48 455 and 500 us a call, 12 RHS
+    // 1347 and 1319, the 12-RHS sign function at 16^3x32 60.7 and 64.0 ms).
+    // Different epilogue shapes and kernel timing take two.
     const bool clov = e[0].clov != 0 && S.has_clover;
-    if (S.nvec != 1 || prof().on || e[0].nx != e[1].nx || e[0].g5 != e[1].g5 || e[0].coef != e[1].coef ||
+    if (prof().on || e[0].nx != e[1].nx || e[0].g5 != e[1].g5 || e[0].coef != e[1].coef ||
         e[0].clov != e[1].clov || e[0].canon != e[1].canon) {
         for (int p = 0; p < 2; ++p) WL_TRY(hop(S, prec, recon, dag, p, out[p], in[1 - p], e[p], no_red(), s, use_active));
         return WL_OK;
     }
     const SysDesc *sysd = nullptr;
     WL_TRY(S.sys_table(prec, recon, s, &sysd));
-    auto mk = [&](const Layout *L) {
+    // slot 0 or 1: that output parity alone; 2: both
+    auto mk = [&](const Layout *L, int slot) {
         HopArgs a{};
+        const int p = slot & 1;
         a.sys = sysd;
         a.vec = L->d_vec;
         a.map = L->d_map;
         a.active = use_active ? S.d_active : nullptr;
-        a.nblocks = 2 * L->nblocks;
-        a.parity = 0;
+        a.nblocks = slot == 2 ? 2 * L->nblocks : L->nblocks;
+        a.parity = p;
         a.nvec = S.nvec;
-        a.in = in[1].p;
-        a.in_norm = in[1].n;
-        a.out = out[0].p;
-        a.out_norm = out[0].n;
+        a.in = in[1 - p].p;
+        a.in_norm = in[1 - p].n;
+        a.out = out[p].p;
+        a.out_norm = out[p].n;
         a.epi.nx = e[0].nx;
         a.epi.g5 = e[0].g5;
         a.epi.clov = clov ? e[0].clov : 0;
         a.epi.coef = e[0].coef;
         a.canon = e[0].canon;
         for (int j = 0; j < 4; ++j) {
-            a.epi.X[j] = e[0].X[j].p;
-            a.epi.Xn[j] = e[0].X[j].n;
+            a.epi.X[j] = e[p].X[j].p;
+            a.epi.Xn[j] = e[p].X[j].n;
             a.X_b[j] = e[1].X[j].p;
             a.Xn_b[j] = e[1].X[j].n;
         }
         a.red = no_red();
-        a.one = 1;
+        a.one = S.nvec == 1;
         a.stream = S.stream_fields(prec);
-        a.twin = 1;
+        a.twin = slot == 2;
         a.in_b = in[0].p;
         a.in_norm_b = in[0].n;
         a.out_b = out[1].p;
@@ -933,17 +939,26 @@ wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], co
     const std::string key = hop_key(S, prec, recon, dag) + (clov ? "/clov" : "") + "/twin/x" +
                             std::to_string(e[0].nx) + (e[0].canon ? "/canon" : "");
     std::vector<int> cands = hop_cands(S, prec, clov);
-    cands.erase(std::remove_if(cands.begin(), cands.end(), [](int c) { return cfg_var(c) >= 6; }), cands.end());
+    if (S.nvec > 1) {
+        const size_t n = cands.size();
+        for (size_t i = 0; i < n; ++i) cands.push_back(cands[i] | kCfgSplit);
+    }
+    auto run = [&](int c, const Layout *L) -> hipError_t {
+        const int var = cfg_var(c), B = cfg_block(c);
+        if (!(c & kCfgSplit)) return launch_hop(prec, recon, dag, clov, var, mk(L, 2), B, s);
+        const hipError_t r = launch_hop(prec, recon, dag, clov, var, mk(L, 0), B, s);
+        return r != hipSuccess ? r : launch_hop(prec, recon, dag, clov, var, mk(L, 1), B, s);
+    };
     const int cfg = tuned_block(key, cands, s, [&](int c) -> hipError_t {
         const Layout *L = nullptr;
         if (hop_layout(S, c, &L) != WL_OK) return hipErrorOutOfMemory;
-        return launch_hop(prec, recon, dag, clov, cfg_var(c), mk(L), cfg_block(c), s);
+        return run(c, L);
     });
     const Layout *L = nullptr;
     WL_TRY(hop_layout(S, cfg, &L));
     if (clov) g_bytes_acc += 2 * clover_bytes(S, prec, use_active);
     g_bytes_acc += 2 * (hop_bytes(S, prec, recon, use_active) + blas_bytes(S, prec, e[0].nx, use_active));
-    WL_HIP(launch_hop(prec, recon, dag, clov, cfg_var(cfg), mk(L), cfg_block(cfg), s));
+    WL_HIP(run(cfg, L));
     return WL_OK;
 }
 

@@ -220,7 +220,6 @@ RedSpec red_spec(ExecSet &S, int kind, double *dst, int nv = 1, int mode = RM_NO
 wl_status hop(ExecSet &S, int prec, int recon, bool dag, int out_parity, const Field &out, const Field &in,
               const Epi &e, const RedSpec &red, hipStream_t s, bool use_active = true);
 // out_p = epi_p(hop(in_{1-p})) for both parities p (no reduction), in one launch
-// when the set is a single vector
 wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], const Field in[2], const Epi e[2],
                hipStream_t s, bool use_active = true);
 // bcast: bit j marks field j as a single vector shared by every vector of the set

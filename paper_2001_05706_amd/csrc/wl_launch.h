@@ -126,9 +126,12 @@ struct HopArgs {
     // one == 1: the set is a single vector (vector 0 of system 0), so a block
     // loads its descriptors without waiting for the block map
     int32_t one;
-    // twin == 1: the launch covers both output parities: logical blocks
-    // [nblocks/2, nblocks) repeat the block map for output parity 1 - parity,
-    // reading the fields of the second slot below (no reduction)
+    // twin == 1: the launch covers both output parities: logical block 2k is
+    // entry k of the block map for output parity `parity`, 2k + 1 the same sites
+    // of the other parity, from the second slot below (no reduction).  The two
+    // read the same lines at the same time: each parity's epilogue field X0 is
+    // the other's neighbour input, and the backward links of one are the forward
+    // links of the other.
     int32_t twin;
     const void *in_b;
     const float *in_norm_b;
