@@ -671,7 +671,7 @@ static hipError_t launch_hop_pencil(bool dag, const HopArgs &a, int block, hipSt
 }
 
 template <int SP, int GP, int R>
-static hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, int block, hipStream_t s,
+hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, int block, hipStream_t s,
                                hipEvent_t e0, hipEvent_t e1)
 {
     switch (var) {
@@ -706,6 +706,24 @@ static hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, i
     return hipErrorInvalidValue;
 }
 
+// The kernels of one storage format are compiled in a source of their own (hop_*.hip,
+// which define WL_HOP_FORMAT and include this file), so that the formats build in
+// parallel; this file by itself compiles the dispatch over them.
+#ifdef WL_HOP_FORMAT
+template hipError_t launch_hop_t<WL_HOP_FORMAT>(int var, bool dag, bool clov, const HopArgs &a, int block,
+                                                hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+#else
+#define WL_HOP_EXTERN(...)                                                                                          \
+    extern template hipError_t launch_hop_t<__VA_ARGS__>(int var, bool dag, bool clov, const HopArgs &a, int block, \
+                                                         hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+WL_HOP_EXTERN(P_F64, P_F64, 18);
+WL_HOP_EXTERN(P_F64, P_F64, 12);
+WL_HOP_EXTERN(P_F32, P_F32, 18);
+WL_HOP_EXTERN(P_F32, P_F32, 12);
+WL_HOP_EXTERN(P_F16, P_F16, 12);
+WL_HOP_EXTERN(P_BF16, P_BF16, 12);
+#undef WL_HOP_EXTERN
+
 // FP64 runs variants 0-7 (variants 8-10 stage FP32 or half-precision data in LDS)
 int hop_variants(int prec) { return prec == P_F64 ? 8 : kHopVariants; }
 
@@ -720,5 +738,6 @@ hipError_t launch_hop(int prec, int recon, bool dag, bool clov, int var, const H
     if (prec == P_BF16 && recon == 12) return launch_hop_t<P_BF16, P_BF16, 12>(var, dag, clov, a, block, s, e0, e1);
     return hipErrorInvalidValue;
 }
+#endif
 
 }  // namespace wl
