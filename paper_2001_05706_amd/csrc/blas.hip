@@ -504,28 +504,60 @@ __global__ __launch_bounds__(1024) void k_red_finalize(RedSpec r, const VecDesc 
     if (threadIdx.x == 0) red_finalize(r, v, tot, in);
 }
 
-// Deferred |r|^2 of k iterations: block (v, j) sums row j of the per-iteration
-// partials of vector v in a fixed order into hist[j * nvec + v].
-__global__ __launch_bounds__(256) void k_hist_finalize(const double *partials, size_t row, const VecDesc *vec,
-                                                       const int32_t *active, int nvec, double *hist, int32_t *bad)
+// The report of a chunk of k iterations: one block per vector, one wave per
+// history row, which sums the row's partials of the vector in a fixed order (or
+// takes the finished value).  The rows and the vector's flag go straight to
+// pinned host memory: a copy queued behind the chunk cost the solver a further
+// launch and its gap before the host could decide.
+__global__ __launch_bounds__(1024) void k_hist_report(const double *partials, size_t row, const VecDesc *vec,
+                                                      const int32_t *active, int nvec, int k, const double *hist,
+                                                      int32_t *bad, double *host_hist, int32_t *host_bad)
 {
-    const int v = blockIdx.x, j = blockIdx.y;
+    const int v = blockIdx.x;
     if (active && !active[v]) return;
+    __shared__ int s_bad;
+    if (threadIdx.x == 0) s_bad = bad[v];
+    __syncthreads();
     const VecDesc vd = vec[v];
-    const double *p = partials + (size_t)j * row + vd.pslot0;
-    double s = 0.0;
-    for (int i = threadIdx.x; i < vd.nblk; i += blockDim.x) s += p[i];
-    s = block_sum(s);
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    for (int j = threadIdx.x >> 6; j < k; j += nw) {
+        double s;
+        if (partials) {
+            const double *p = partials + (size_t)j * row + vd.pslot0;
+            s = 0.0;
+            // eight partials per step, all loaded before any is added
+            int i = lane;
+            for (; i + 7 * 64 < vd.nblk; i += 8 * 64) {
+                double w[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) w[u] = p[i + u * 64];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s += w[u];
+            }
+            for (; i < vd.nblk; i += 64) s += p[i];
+            s = wave_sum(s);
+        } else {
+            s = hist[(size_t)j * nvec + v];
+        }
+        if (lane == 0) {
+            host_hist[(size_t)j * nvec + v] = s;
+            if (!isfinite(s)) atomicOr(&s_bad, 1);
+        }
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        hist[(size_t)j * nvec + v] = s;
-        if (!isfinite(s) && bad) bad[v] |= 1;
+        bad[v] = s_bad;
+        host_bad[v] = s_bad;
     }
 }
 
-hipError_t launch_hist_finalize(const double *partials, size_t row, const VecDesc *vec, const int32_t *active, int nvec,
-                                int k, double *hist, int32_t *bad, hipStream_t s)
+hipError_t launch_hist_report(const double *partials, size_t row, const VecDesc *vec, const int32_t *active, int nvec,
+                              int k, const double *hist, int32_t *bad, double *host_hist, int32_t *host_bad,
+                              hipStream_t s)
 {
-    hipLaunchKernelGGL(k_hist_finalize, dim3(nvec, k), dim3(256), 0, s, partials, row, vec, active, nvec, hist, bad);
+    const int waves = k < 16 ? k : 16;
+    hipLaunchKernelGGL(k_hist_report, dim3(nvec), dim3(64 * waves), 0, s, partials, row, vec, active, nvec, k, hist,
+                       bad, host_hist, host_bad);
     return hipGetLastError();
 }
 

@@ -140,14 +140,15 @@ struct Cg {
         return WL_OK;
     }
 
-    // rh = b' - M xh in FP64 with |rh|^2 into SC_RR.  Links are rebuilt from 12
+    // rh = b' - M xh in FP64 with |rh|^2 into SC_RR and the host's report.  Links are rebuilt from 12
     // reals when the caller chose recon-12 (exact to rounding for SU(3)); the
     // final true residual always uses all 18.
     wl_status residual64(bool use_active = true)
     {
         WL_TRY(hop(S, P_F64, recon, false, 1, t64, xh, first(c_plain), no_red(), s, use_active));
-        WL_TRY(hop(S, P_F64, recon, false, 0, rh, t64, second(c_res, 2, xh, bp),
-                   red_spec(S, RED_STORE, S.scal(SC_RR)), s, use_active));
+        RedSpec rr = red_spec(S, RED_STORE, S.scal(SC_RR));
+        rr.host = S.dev_report(ExecSet::kRepRR);
+        WL_TRY(hop(S, P_F64, recon, false, 0, rh, t64, second(c_res, 2, xh, bp), rr, s, use_active));
         return WL_OK;
     }
 
@@ -262,7 +263,7 @@ struct Cg {
     {
         if (!use_graphs || prof().on) {
             for (int j = 0; j < k; ++j) WL_TRY(iteration(j));
-            if (method == M_CGNR) WL_TRY(hist_finalize(S, k, s));
+            WL_TRY(hist_report(S, k, method == M_CGNR, s));
             return WL_OK;
         }
         // the coefficient tables are cached by content, so their addresses name
@@ -283,7 +284,7 @@ struct Cg {
             WL_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed));
             wl_status st = WL_OK;
             for (int j = 0; j < k && st == WL_OK; ++j) st = iteration(j);
-            if (st == WL_OK && method == M_CGNR) st = hist_finalize(S, k, s);
+            if (st == WL_OK) st = hist_report(S, k, method == M_CGNR, s);
             hipGraph_t g = nullptr;
             hipError_t ce = hipStreamEndCapture(cs, &g);
             s = user;
@@ -364,7 +365,10 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
     const bool trace = getenv("WL_DEBUG") != nullptr;  // per-chunk solver trace on stderr
     WL_TRY(cg.setup());
     const int nv = S.nvec;
-    double *hp = S.h_pinned;  // [kHist * nv] history, then scalars
+    const double *hp = S.report(0);                                       // |r|^2 history rows of the last chunk
+    const double *hrr = S.report(ExecSet::kRepRR);                        // the last FP64 |r|^2
+    double *hsc = S.report(ExecSet::kRepSc);                              // scalar slots, when copied
+    const int32_t *hbad = (const int32_t *)S.report(ExecSet::kRepBad);    // non-finite flags
 
     std::fill(S.h_active.begin(), S.h_active.end(), 1);
     WL_TRY(S.upload_active(s));
@@ -386,25 +390,27 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                red_spec(S, RED_STORE, S.scal(SC_RR)), s));
     WL_TRY(pack(S, (const double *const *)x, 0, cg.xh, s));
     // r = b' - M x.  When every initial guess is zero (the usual start) r = b'
-    // exactly and the residual's two FP64 hops are replaced by a copy: the
-    // guesses' |x_e|^2 are read back first to decide.
+    // exactly and the residual's two FP64 hops are replaced by a copy, queued
+    // while the host reads |x_e|^2 (and |eta|^2, |b'|^2) to decide.
     WL_TRY(blas(S, BL_NORM2, P_F64, &cg.xh, 1, nullptr, red_spec(S, RED_STORE, S.scal(SC_TMP)), s));
-    WL_HIP(hipMemcpyAsync(hp, S.scal(SC_TMP), sizeof(double) * nv, hipMemcpyDeviceToHost, s));
-    WL_HIP(hipStreamSynchronize(s));
+    WL_HIP(hipMemcpyAsync(hsc, S.sc, sizeof(double) * ExecSet::SC_N * nv, hipMemcpyDeviceToHost, s));
+    WL_HIP(hipEventRecord(S.rr_ev, s));
+    WL_TRY(convert(S, cg.rh, cg.bp, s));
+    WL_TRY(wait_spin(S.rr_ev));
     bool zero_guess = true;
-    for (int v = 0; v < nv; ++v) zero_guess = zero_guess && hp[v] == 0.0;
-    if (zero_guess)
-        WL_TRY(convert(S, cg.rh, cg.bp, s));
-    else
+    for (int v = 0; v < nv; ++v) zero_guess = zero_guess && hsc[SC_TMP * nv + v] == 0.0;
+    if (!zero_guess) {
         WL_TRY(cg.residual64());
-    WL_HIP(hipMemcpyAsync(hp, S.sc, sizeof(double) * ExecSet::SC_N * nv, hipMemcpyDeviceToHost, s));
-    WL_HIP(hipStreamSynchronize(s));
+        WL_HIP(hipMemcpyAsync(hsc, S.sc, sizeof(double) * ExecSet::SC_N * nv, hipMemcpyDeviceToHost, s));
+        WL_HIP(hipEventRecord(S.rr_ev, s));
+        WL_TRY(wait_spin(S.rr_ev));
+    }
     std::vector<double> eta_n(nv), rmax(nv), last_true(nv), target(nv);
     std::vector<int> iters(nv, 0), updates(nv, 0), conv(nv, 0), done(nv, 0), stall(nv, 0);
     std::vector<int> zero_src(nv, 0);
     for (int v = 0; v < nv; ++v) {
-        eta_n[v] = std::sqrt(hp[SC_ETA * nv + v]);
-        const double r = std::sqrt(hp[SC_RR * nv + v]);
+        eta_n[v] = std::sqrt(hsc[SC_ETA * nv + v]);
+        const double r = std::sqrt(hsc[SC_RR * nv + v]);
         target[v] = tol * eta_n[v];
         if (!std::isfinite(eta_n[v]) || !std::isfinite(r))
             return set_error(WL_ERR_NONFINITE, "non-finite source or initial guess (rhs %d)", v);
@@ -500,10 +506,7 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
             WL_TRY(cg.chunk(k));
             cg.use_graphs = graphs;
             first = false;
-            // the k history rows and the flags behind the whole history, in one copy
-            WL_HIP(hipMemcpyAsync(hp, S.hist, sizeof(double) * ExecSet::kHist * nv + sizeof(int32_t) * nv,
-                                  hipMemcpyDeviceToHost, s));
-            int32_t *hbad = (int32_t *)(hp + (size_t)ExecSet::kHist * nv);
+            // the chunk ended with the k history rows and the flags in the report
             WL_HIP(hipEventRecord(S.rr_ev, s));
             WL_TRY(wait_spin(S.rr_ev));
             if (trace) {
@@ -578,7 +581,6 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                 for (int v = 0; v < nv; ++v) S.h_active[v] = upd[v];
                 WL_TRY(S.upload_active(s));
                 WL_TRY(cg.residual64());
-                WL_HIP(hipMemcpyAsync(hp, S.scal(SC_RR), sizeof(double) * nv, hipMemcpyDeviceToHost, s));
                 WL_HIP(hipEventRecord(S.rr_ev, s));
                 // every updated vector that goes on (continued or restarted) needs
                 // r from the new residual, and for CGNR s = M^+ r: they are queued
@@ -592,7 +594,7 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                 bool stalled = false;
                 for (int v = 0; v < nv; ++v) {
                     if (!upd[v]) continue;
-                    const double r = std::sqrt(hp[v]);
+                    const double r = std::sqrt(hrr[v]);
                     if (trace)
                         fprintf(stderr, "[wl cg] update rhs %d after %d iters: FP64 |r|/|eta| = %.3e (prev %.3e)%s\n", v,
                                 iters[v], r / eta_n[v], last_true[v] / eta_n[v], restart[v] ? " restart" : "");
@@ -687,15 +689,16 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
     WL_TRY(hop(S, P_F64, 18, false, 1, cg.xo, cg.xh, cg.epi(cg.c_bp, 1, cg.eta_o, Field(), EPI_CLOV_INV), no_red(), s));
     WL_TRY(hop(S, P_F64, 18, false, 0, cg.rh, cg.xo, cg.epi(cg.c_tres, 2, cg.xh, cg.eta_e, EPI_CLOV_X0),
                red_spec(S, RED_STORE, S.scal(SC_RR)), s));
-    WL_TRY(hop(S, P_F64, 18, false, 1, cg.t64, cg.xh, cg.epi(cg.c_tres, 2, cg.xo, cg.eta_o, EPI_CLOV_X0),
-               red_spec(S, RED_ACCUM, S.scal(SC_RR)), s));
+    RedSpec tr = red_spec(S, RED_ACCUM, S.scal(SC_RR));
+    tr.host = S.dev_report(ExecSet::kRepRR);
+    WL_TRY(hop(S, P_F64, 18, false, 1, cg.t64, cg.xh, cg.epi(cg.c_tres, 2, cg.xo, cg.eta_o, EPI_CLOV_X0), tr, s));
     WL_TRY(unpack2(S, x, cg.xh, cg.xo, s));
-    WL_HIP(hipMemcpyAsync(hp, S.scal(SC_RR), sizeof(double) * nv, hipMemcpyDeviceToHost, s));
-    WL_HIP(hipStreamSynchronize(s));
+    WL_HIP(hipEventRecord(S.rr_ev, s));
+    WL_TRY(wait_spin(S.rr_ev));
     const double t1 = now_s();
     bool allconv = true;
     for (int v = 0; v < nv; ++v) {
-        const double tr = eta_n[v] > 0 ? std::sqrt(hp[v]) / eta_n[v] : 0.0;
+        const double tr = eta_n[v] > 0 ? std::sqrt(hrr[v]) / eta_n[v] : 0.0;
         if (info) {
             info[v].iters = iters[v];
             info[v].reliable_updates = updates[v];

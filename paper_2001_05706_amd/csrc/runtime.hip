@@ -132,8 +132,9 @@ static std::mutex g_tune_mu;
 static std::map<std::string, int> g_tuned;
 
 int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream_t s,
-                const std::function<hipError_t(int)> &run)
+                const std::function<hipError_t(int)> &run, bool *settled)
 {
+    if (settled) *settled = false;
     // WL_TUNE_FORCE=<variant>:<block>[:<column height>] pins every hop launch
     // whose candidates hold that variant and block size (tests of each
     // variant; column height 4 by default, any height >= 1 accepted)
@@ -147,7 +148,10 @@ int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(key);
-        if (it != g_tuned.end()) return it->second;
+        if (it != g_tuned.end()) {
+            if (settled) *settled = true;
+            return it->second;
+        }
     }
     // untuned (tuning switched off, or first met inside a graph capture, where
     // nothing may be timed): 256-thread blocks in columns of 4 z-planes
@@ -225,6 +229,7 @@ int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream
     if (getenv("WL_DEBUG")) fprintf(stderr, "[wl tune] %s -> %d (%.4f ms per launch)\n", key.c_str(), best, best_ms);
     std::lock_guard<std::mutex> lk(g_tune_mu);
     g_tuned[key] = best;
+    if (settled) *settled = true;
     return best;
 }
 
@@ -350,9 +355,10 @@ ExecSet::~ExecSet()
     (void)hipFree(d_active);
     (void)hipFree(partials);
     (void)hipFree(sc);
-    (void)hipFree(hist);  // bad lives at its end
+    (void)hipFree(hist);
+    (void)hipFree(bad);
     (void)hipFree(hist_partials);
-    (void)hipHostFree(h_pinned);
+    (void)hipHostFree(h_report);
     (void)hipHostFree(h_masks);
     for (auto &e : mask_ev)
         if (e) (void)hipEventDestroy(e);
@@ -392,16 +398,15 @@ wl_status ExecSet::init()
     WL_ALLOC(d_active, sizeof(int32_t) * nvec);
     WL_ALLOC(partials, sizeof(double) * 3 * max_pslots);
     WL_ALLOC(sc, sizeof(double) * SC_N * nvec);
-    // the flags follow the history in one allocation, so that the host reads
-    // both with one copy (the same layout as the pinned mirror)
-    WL_ALLOC(hist, sizeof(double) * kHist * nvec + sizeof(int32_t) * nvec);
-    bad = (int32_t *)(hist + (size_t)kHist * nvec);
+    WL_ALLOC(hist, sizeof(double) * kHist * nvec);
+    WL_ALLOC(bad, sizeof(int32_t) * nvec);
     WL_ALLOC(hist_partials, sizeof(double) * kHist * max_pslots);
-    if (hipHostMalloc((void **)&h_pinned, sizeof(double) * (kHist + SC_N + 1) * nvec + 64, 0) != hipSuccess) {
+    if (hipHostMalloc((void **)&h_report, sizeof(double) * (kRepBad + 1) * nvec, 0) != hipSuccess) {
         (void)hipGetLastError();
-        h_pinned = nullptr;
+        h_report = nullptr;
         return set_error(WL_ERR_NOMEM, "cannot allocate pinned host memory");
     }
+    WL_HIP(hipHostGetDevicePointer((void **)&d_report, h_report, 0));
     if (hipHostMalloc((void **)&h_masks, sizeof(int32_t) * kMaskRing * nvec, 0) != hipSuccess) {
         (void)hipGetLastError();
         h_masks = nullptr;
@@ -786,6 +791,42 @@ static std::vector<int> hop_cands(const ExecSet &S, int prec, bool clov)
     return cands;
 }
 
+// A kind of hop launch of a set, as an index into its plans
+static int plan_id(int prec, int recon, bool dag, bool clov, const Epi &e, bool red, bool twin)
+{
+    return prec | (recon == 12) << 2 | (int)dag << 3 | (int)clov << 4 | (int)red << 5 | (int)twin << 6 |
+           (e.canon != nullptr) << 7 | e.nx << 8;
+}
+
+// The launch configuration and block map of one kind of hop: from the set's plans
+// once the tuner has settled it (a D-slash call or a solver's eager launch spent
+// more host time on the tuner's key, the candidate list and the lookups than on
+// the launch), else from the tuner.  A pinned configuration is looked at anew
+// each time.
+template <class Key, class Cands, class Run>
+static wl_status hop_plan(ExecSet &S, int id, ExecSet::HopPlan *pl, hipStream_t s, Key key, Cands cands, Run run)
+{
+    const bool pinned = getenv("WL_TUNE_FORCE") != nullptr;
+    if (!pinned) {
+        auto it = S.plans.find(id);
+        if (it != S.plans.end()) {
+            *pl = it->second;
+            return WL_OK;
+        }
+    }
+    bool settled = false;
+    pl->cfg = tuned_block(key(), cands(), s,
+                          [&](int c) -> hipError_t {
+                              const Layout *L = nullptr;
+                              if (hop_layout(S, c, &L) != WL_OK) return hipErrorOutOfMemory;
+                              return run(c, L);
+                          },
+                          &settled);
+    WL_TRY(hop_layout(S, pl->cfg, &pl->L));
+    if (settled && !pinned) S.plans[id] = *pl;
+    return WL_OK;
+}
+
 wl_status hop(ExecSet &S, int prec, int recon, bool dag, int par, const Field &out, const Field &in, const Epi &e,
               const RedSpec &red, hipStream_t s, bool use_active)
 {
@@ -822,19 +863,20 @@ wl_status hop(ExecSet &S, int prec, int recon, bool dag, int par, const Field &o
     };
     // tuned per epilogue shape: a hop that also reads X fields and reduces may
     // prefer another variant than a plain one
-    const std::string key = hop_key(S, prec, recon, dag) + (clov ? "/clov" : "") + "/x" + std::to_string(e.nx) +
-                            (red.kind != RED_NONE ? "/r" : "") + (e.canon ? "/canon" : "");
-    const std::vector<int> cands = hop_cands(S, prec, clov);
-    const int cfg = tuned_block(key, cands, s, [&](int c) -> hipError_t {
-        const Layout *L = nullptr;
-        if (hop_layout(S, c, &L) != WL_OK) return hipErrorOutOfMemory;
-        // with the launch's own reduction: the partial slots it writes are
-        // rewritten by the launch that follows the tuning
-        return launch_hop(prec, recon, dag, clov, cfg_var(c), mk(L, red), cfg_block(c), s);
-    });
-    const int B = cfg_block(cfg), var = cfg_var(cfg);
-    const Layout *L = nullptr;
-    WL_TRY(hop_layout(S, cfg, &L));
+    ExecSet::HopPlan pl{};
+    WL_TRY(hop_plan(S, plan_id(prec, recon, dag, clov, e, red.kind != RED_NONE, false), &pl, s,
+                    [&]() {
+                        return hop_key(S, prec, recon, dag) + (clov ? "/clov" : "") + "/x" + std::to_string(e.nx) +
+                               (red.kind != RED_NONE ? "/r" : "") + (e.canon ? "/canon" : "");
+                    },
+                    [&]() { return hop_cands(S, prec, clov); },
+                    [&](int c, const Layout *Lc) -> hipError_t {
+                        // with the launch's own reduction: the partial slots it writes are
+                        // rewritten by the launch that follows the tuning
+                        return launch_hop(prec, recon, dag, clov, cfg_var(c), mk(Lc, red), cfg_block(c), s);
+                    }));
+    const int B = cfg_block(pl.cfg), var = cfg_var(pl.cfg);
+    const Layout *L = pl.L;
     const double bytes = hop_bytes(S, prec, recon, use_active) + blas_bytes(S, prec, e.nx, use_active) +
                          (clov ? ((e.clov & EPI_CLOV_X0) ? 1 : 0) + ((e.clov & EPI_CLOV_INV) ? 1 : 0) : 0) *
                              clover_bytes(S, prec, use_active);
@@ -936,29 +978,28 @@ wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], co
         a.out_norm_b = out[1].n;
         return a;
     };
-    const std::string key = hop_key(S, prec, recon, dag) + (clov ? "/clov" : "") + "/twin/x" +
-                            std::to_string(e[0].nx) + (e[0].canon ? "/canon" : "");
-    std::vector<int> cands = hop_cands(S, prec, clov);
-    if (S.nvec > 1) {
-        const size_t n = cands.size();
-        for (size_t i = 0; i < n; ++i) cands.push_back(cands[i] | kCfgSplit);
-    }
     auto run = [&](int c, const Layout *L) -> hipError_t {
         const int var = cfg_var(c), B = cfg_block(c);
         if (!(c & kCfgSplit)) return launch_hop(prec, recon, dag, clov, var, mk(L, 2), B, s);
         const hipError_t r = launch_hop(prec, recon, dag, clov, var, mk(L, 0), B, s);
         return r != hipSuccess ? r : launch_hop(prec, recon, dag, clov, var, mk(L, 1), B, s);
     };
-    const int cfg = tuned_block(key, cands, s, [&](int c) -> hipError_t {
-        const Layout *L = nullptr;
-        if (hop_layout(S, c, &L) != WL_OK) return hipErrorOutOfMemory;
-        return run(c, L);
-    });
-    const Layout *L = nullptr;
-    WL_TRY(hop_layout(S, cfg, &L));
+    ExecSet::HopPlan pl{};
+    WL_TRY(hop_plan(S, plan_id(prec, recon, dag, clov, e[0], false, true), &pl, s,
+                    [&]() {
+                        return hop_key(S, prec, recon, dag) + (clov ? "/clov" : "") + "/twin/x" +
+                               std::to_string(e[0].nx) + (e[0].canon ? "/canon" : "");
+                    },
+                    [&]() {
+                        std::vector<int> c = hop_cands(S, prec, clov);
+                        const size_t n = c.size();
+                        for (size_t i = 0; i < n && S.nvec > 1; ++i) c.push_back(c[i] | kCfgSplit);
+                        return c;
+                    },
+                    run));
     if (clov) g_bytes_acc += 2 * clover_bytes(S, prec, use_active);
     g_bytes_acc += 2 * (hop_bytes(S, prec, recon, use_active) + blas_bytes(S, prec, e[0].nx, use_active));
-    WL_HIP(run(cfg, L));
+    WL_HIP(run(pl.cfg, pl.L));
     return WL_OK;
 }
 
@@ -1004,12 +1045,12 @@ wl_status blas(ExecSet &S, int op, int prec, const Field *f, int nf, const doubl
     return WL_OK;
 }
 
-wl_status hist_finalize(ExecSet &S, int k, hipStream_t s)
+wl_status hist_report(ExecSet &S, int k, bool deferred, hipStream_t s)
 {
     const Layout *L = nullptr;
     WL_TRY(S.layout(kBlasBlock, &L));
-    WL_HIP(launch_hist_finalize(S.hist_partials, (size_t)S.max_pslots, L->d_vec, S.d_active, S.nvec, k, S.hist, S.bad,
-                                s));
+    WL_HIP(launch_hist_report(deferred ? S.hist_partials : nullptr, (size_t)S.max_pslots, L->d_vec, S.d_active, S.nvec,
+                              k, S.hist, S.bad, S.dev_report(0), (int32_t *)S.dev_report(ExecSet::kRepBad), s));
     return WL_OK;
 }
 

@@ -172,11 +172,16 @@ public:
     // reduction state (per vector unless noted)
     double *partials = nullptr;  // max slots over layouts (B = 64), 3 values each
     double *sc = nullptr;        // scalar arena, see SC_* below
-    int32_t *bad = nullptr;      // at the end of the hist allocation
-    double *hist = nullptr;      // residual history: [kHist][nvec], then bad
+    int32_t *bad = nullptr;
+    double *hist = nullptr;      // residual history: [kHist][nvec]
     double *hist_partials = nullptr;  // deferred block partials of the history: [kHist][max_pslots]
-    double *h_pinned = nullptr;  // pinned host mirror of hist, scalars and flags
+    // pinned host memory that kernels write (d_report: its device address):
+    // kHist history rows, one row of |r|^2, the scalar slots, then the flags
+    double *h_report = nullptr, *d_report = nullptr;
     static constexpr int kHist = 64;
+    static constexpr int kRepRR = kHist, kRepSc = kHist + 1, kRepBad = kHist + 1 + SC_COUNT;  // rows of nvec doubles
+    double *report(int row) { return h_report + (size_t)row * nvec; }
+    double *dev_report(int row) { return d_report + (size_t)row * nvec; }
 
     static constexpr int SC_N = SC_COUNT;  // scalar slots per vector (ScSlot)
     double *scal(int which) { return sc + (size_t)which * nvec; }
@@ -192,6 +197,12 @@ public:
     std::map<std::string, Field> fields;
     std::map<std::vector<double>, double *> coefs;
     std::map<std::string, hipGraphExec_t> graphs;  // captured iteration chunks
+    // launch configuration and block map of each kind of hop once it is tuned
+    struct HopPlan {
+        int cfg;
+        const Layout *L;
+    };
+    std::map<int, HopPlan> plans;
     int max_pslots = 0;
 };
 
@@ -232,8 +243,9 @@ wl_status pack(ExecSet &S, const double *const *canon, int parity, const Field &
 wl_status pack2(ExecSet &S, const double *const *canon, const Field &even, const Field &odd, hipStream_t s);
 wl_status unpack2(ExecSet &S, double *const *canon, const Field &even, const Field &odd, hipStream_t s);
 
-// sum the deferred |r|^2 partials of the last k iterations into hist rows 0..k-1
-wl_status hist_finalize(ExecSet &S, int k, hipStream_t s);
+// the last k iterations' |r|^2 (deferred: from their block partials; otherwise
+// from the hist rows) and the flags into the pinned report
+wl_status hist_report(ExecSet &S, int k, bool deferred, hipStream_t s);
 
 // device coefficient tables [nsys][5], cached by content
 wl_status coef_table(ExecSet &S, const std::vector<double> &c, const double **out);
@@ -279,8 +291,9 @@ wl_status defl_axpy(ExecSet &S, const Deflation &D, int prec, const Field y[2], 
 
 // ------------------------------------------------------------------ tuning and timing
 
+// settled (optional): the choice is the tuner's and holds for later calls
 int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream_t s,
-                const std::function<hipError_t(int)> &run);
+                const std::function<hipError_t(int)> &run, bool *settled = nullptr);
 bool capturing(hipStream_t s);
 std::string hop_key(const ExecSet &S, int prec, int recon, bool dag);
 std::vector<int> hop_candidates(int prec);

@@ -85,6 +85,7 @@ struct RedSpec {
     int32_t *bad;        // per-vector non-finite flag (bit 0)
     int32_t defer;       // 1: leave the partials for a later finishing pass (no finishing launch)
     int32_t pad_;
+    double *host;        // RED_STORE / RED_ACCUM: dst[v] also goes here (pinned host memory; null: off)
 };
 
 // Linear combination applied to the hopping term at the output site:

@@ -150,6 +150,7 @@ __device__ __forceinline__ void red_finalize(const RedSpec &r, int v, const doub
     }
 #undef WL_SC
     if (!finite && r.bad) r.bad[v] |= 1;
+    if (r.host) r.host[v] = r.dst[v];
 }
 
 // Called by every thread of the block (uniform control flow) with its own
