@@ -47,6 +47,8 @@ namespace wl {
 //  10: pencil blocks with cached links; fence 4 for FP16/BF16, 2 for FP32
 //      (FP32 and half-precision storage, Wilson epilogue; lattices whose time
 //      slices hold a multiple of 64 sites)
+//  11: the eight directions of 64 sites on the eight waves of a block (k_hop_split;
+//      Wilson epilogue)
 // Variants 4 and 5 exist for FP16/BF16 storage only (FP32 and FP64 operands of
 // four directions do not fit the registers); for those they repeat variant 3.
 template <int SP, int VAR> struct HopVar {
@@ -65,7 +67,7 @@ template <int SP, int VAR> struct HopVar {
     // occupancy target already allows 4 waves per SIMD; 512 otherwise
     static constexpr int max_block = waves >= 4 && VAR < 6 ? 1024 : 512;
 };
-constexpr int kHopVariants = 11;
+constexpr int kHopVariants = 12;
 
 // What a hop's epilogue ends in, one instantiation each: EP_CANON stores the
 // canonical FP64 field instead of the packed one.
@@ -608,6 +610,339 @@ void k_hop_pencil(HopArgs a)
     }
 }
 
+// Variant 11: the eight directions of 64 sites of one vector on the eight waves
+// of a block.  Wave d loads its direction's link and neighbour spinor, projects
+// and multiplies; the products meet in LDS, where each of the first waves adds a
+// few reals of every site over the directions in the order of hop_site (so the
+// result equals the other variants' bit for bit) and applies the epilogue to them.
+// For small and ordinary lattices, where the hop is one round of latencies after
+// another: a wave waits for one round of loads instead of four, eight times as
+// many waves are under way, and the eight readers of a spinor ask for it at the
+// same time.  Warm D-slash against the best per-site variant: 8^3x16 FP32 3.5 us
+// instead of 6.6, 12x14x10x18 FP64 4.9 instead of 10.5, 16^3x32 FP32 6.7 instead
+// of 8.8, 24^3x48 FP32 30.5 instead of 37; at 32^3x64 the products' way through
+// LDS costs more than the loads it hides (FP16 64 us against 52).
+template <int SP> struct SplitHop {
+    using T = typename SpinorFmt<SP>::real;
+    static constexpr bool half = SP == P_F16 || SP == P_BF16;
+    static constexpr int rows = half ? 13 : 12;     // reals per direction and site in LDS (half precision: and its factor)
+    static constexpr int per_wave = half ? 8 : 4;   // reals of a site that one wave finishes: whole chunk rows
+    static constexpr int finishers = 24 / per_wave;
+    static constexpr int buf = 8 * rows * 64;       // T's of the products
+    static constexpr int canon_row = sizeof(T) == 4 ? 24 : 26;
+    static constexpr int waves = SP == P_F64 ? 4 : 8;  // per SIMD
+};
+
+// Output real k of direction mu with projector sign sg: the product real it comes
+// from (0-5: U h0, 6-11: U h1) and whether it is subtracted; see reconstruct_add.
+struct SplitSrc {
+    int idx;
+    bool neg;
+};
+constexpr SplitSrc split_src(int mu, int sg, int k)
+{
+    if (k < 12) return {k, false};
+    const bool lower = k >= 18;  // spin 3
+    const int q = (k - 12) % 6, c = 2 * (q / 2), ri = q & 1;
+    switch (mu) {
+    case 0: return {(lower ? 0 : 6) + c + 1 - ri, (sg > 0) == (ri == 1)};
+    case 1: return {(lower ? 0 : 6) + c + ri, (sg > 0) == lower};
+    case 2: return {(lower ? 6 : 0) + c + 1 - ri, ((sg > 0) == (ri == 1)) != lower};
+    default: return {(lower ? 6 : 0) + c + ri, sg < 0};
+    }
+}
+
+// U P psi of direction MU, DIR at the lane's site into its column of `out`
+template <int SP, int GP, int R, int MU, int DIR, bool DAG, class T>
+__device__ __forceinline__ void split_product(const SysDesc &sd, const HopSite &hs, int parity, const Site &st, int cb,
+                                              T *out)
+{
+    constexpr int SG = (DIR > 0) == DAG ? +1 : -1;
+    bool flip;
+    const int ncb = neighbour<MU, DIR>(sd, st, cb, flip);
+    cpx<T> h0[3], h1[3], g[3], u[3][3];
+    const T f = project_neighbour<SP, MU, SG>(hs, ncb, flip, h0, h1);
+    hop_link<GP, R, MU, DIR, false>(hs, parity, cb, ncb, u);
+    su3_mul<(DIR < 0), T>(u, h0, g);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        out[(2 * c) * 64] = g[c].re;
+        out[(2 * c + 1) * 64] = g[c].im;
+    }
+    su3_mul<(DIR < 0), T>(u, h1, g);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        out[(6 + 2 * c) * 64] = g[c].re;
+        out[(7 + 2 * c) * 64] = g[c].im;
+    }
+    if constexpr (SplitHop<SP>::half) out[12 * 64] = f;
+}
+
+// reals W * per_wave ... of the hopping sum of the lane's site
+template <int SP, bool DAG, int W, int D>
+__device__ __forceinline__ void split_add(const typename SplitHop<SP>::T *b, typename SplitHop<SP>::T *acc)
+{
+    using S = SplitHop<SP>;
+    using T = typename S::T;
+    constexpr int mu = D >> 1, SG = ((D & 1) == 0) == DAG ? +1 : -1;
+    const T *g = b + D * S::rows * 64;
+    T f = 0;
+    if constexpr (S::half) f = g[12 * 64];
+#pragma unroll
+    for (int i = 0; i < S::per_wave; ++i) {
+        const SplitSrc e = split_src(mu, SG, W * S::per_wave + i);
+        const T x = g[e.idx * 64];
+        if constexpr (S::half)
+            acc[i] = fmadd(x, e.neg ? -f : f, acc[i]);
+        else
+            acc[i] = e.neg ? acc[i] - x : acc[i] + x;
+    }
+}
+
+template <int SP, bool DAG, int W>
+__device__ __forceinline__ void split_sum(const typename SplitHop<SP>::T *b, typename SplitHop<SP>::T *acc)
+{
+#pragma unroll
+    for (int i = 0; i < SplitHop<SP>::per_wave; ++i) acc[i] = 0;
+    split_add<SP, DAG, W, 0>(b, acc);
+    split_add<SP, DAG, W, 1>(b, acc);
+    split_add<SP, DAG, W, 2>(b, acc);
+    split_add<SP, DAG, W, 3>(b, acc);
+    split_add<SP, DAG, W, 4>(b, acc);
+    split_add<SP, DAG, W, 5>(b, acc);
+    split_add<SP, DAG, W, 6>(b, acc);
+    split_add<SP, DAG, W, 7>(b, acc);
+}
+
+// reals w * per_wave ... of a packed site before its norm is applied
+template <int SP, bool NT>
+__device__ __forceinline__ void split_load(const void *base, int stride, int cb, int w, typename SplitHop<SP>::T *x)
+{
+    if constexpr (SP == P_F64) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const double2 v = ld_field<NT>(row_elem<double2>(base, 2 * w + c, stride, cb));
+            x[2 * c] = v.x;
+            x[2 * c + 1] = v.y;
+        }
+    } else if constexpr (SP == P_F32) {
+        const float4 v = ld_field<NT>(row_elem<float4>(base, w, stride, cb));
+        x[0] = v.x;
+        x[1] = v.y;
+        x[2] = v.z;
+        x[3] = v.w;
+    } else {
+        const uint4 v = ld_field<NT>(row_elem<uint4>(base, w, stride, cb));
+        const uint32_t q[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            x[2 * k] = half_part<SP, 0>(q[k]);
+            x[2 * k + 1] = half_part<SP, 1>(q[k]);
+        }
+    }
+}
+
+template <int SP, int GP, int R, bool DAG, bool CANON>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SplitHop<SP>::waves)))
+void k_hop_split(HopArgs a)
+{
+    using S = SplitHop<SP>;
+    using T = typename S::T;
+    using CH = typename SpinorFmt<SP>::chunk;
+    constexpr int PW = S::per_wave;
+    extern __shared__ uint4 s_split[];
+    __shared__ float s_max[S::half ? S::finishers : 1][64];
+    T *prod = reinterpret_cast<T *>(s_split);
+
+    const int lb = xcd_remap(blockIdx.x, a.nblocks);
+    const bool second = a.twin && (lb & 1);
+    const HopIO f = second ? HopIO{1 - a.parity, a.in_b, a.in_norm_b, a.out_b, a.out_norm_b, a.X_b, a.Xn_b}
+                           : HopIO{a.parity, a.in, a.in_norm, a.out, a.out_norm, a.epi.X, a.epi.Xn};
+    const BlkMap bm = a.map[a.twin ? lb >> 1 : lb];
+    if (a.active && !a.active[a.one ? 0 : bm.v]) return;
+    const VecDesc vd = a.vec[a.one ? 0 : bm.v];
+    const SysDesc sd = a.sys[a.one ? 0 : vd.sys];
+    if (a.stamps && threadIdx.x == 0) a.stamps[2 * lb] = (unsigned long long)wall_clock64();
+    const int lane = (int)threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int cb = bm.lblk * 64 + lane;
+    const bool live = cb < sd.Vh;
+    const int ccb = live ? cb : sd.Vh - 1;  // lanes past the end repeat the last site and store nothing
+    const Site st = cb_coords(sd, ccb, f.parity);
+    const HopSite hs = hop_input<SP>(a, f, vd, sd);
+    {
+        T *out = prod + w * S::rows * 64 + lane;
+        switch (w) {
+        case 0: split_product<SP, GP, R, 0, +1, DAG>(sd, hs, f.parity, st, ccb, out); break;
+        case 1: split_product<SP, GP, R, 0, -1, DAG>(sd, hs, f.parity, st, ccb, out); break;
+        case 2: split_product<SP, GP, R, 1, +1, DAG>(sd, hs, f.parity, st, ccb, out); break;
+        case 3: split_product<SP, GP, R, 1, -1, DAG>(sd, hs, f.parity, st, ccb, out); break;
+        case 4: split_product<SP, GP, R, 2, +1, DAG>(sd, hs, f.parity, st, ccb, out); break;
+        case 5: split_product<SP, GP, R, 2, -1, DAG>(sd, hs, f.parity, st, ccb, out); break;
+        case 6: split_product<SP, GP, R, 3, +1, DAG>(sd, hs, f.parity, st, ccb, out); break;
+        default: split_product<SP, GP, R, 3, -1, DAG>(sd, hs, f.parity, st, ccb, out); break;
+        }
+    }
+    const double *cf = a.epi.coef + vd.sys * 5;
+    const int nx = a.epi.nx;
+    const size_t voff = (size_t)vd.site_off * SpinorFmt<SP>::nchunk;
+    auto load = [&](int j, T *x, T &n) {
+        const CH *xb = (const CH *)f.X[j] + voff;
+        n = 1;
+        if (a.stream) {
+            split_load<SP, true>(xb, sd.stride, ccb, w, x);
+            if constexpr (S::half) n = ld_field<true>(row_elem<float>(f.Xn[j] + vd.site_off, 0, 0, ccb));
+        } else {
+            split_load<SP, false>(xb, sd.stride, ccb, w, x);
+            if constexpr (S::half) n = ld_field<false>(row_elem<float>(f.Xn[j] + vd.site_off, 0, 0, ccb));
+        }
+    };
+    // the first two epilogue operands are on their way while the products meet
+    T x0[PW], x1[PW], n0 = 1, n1 = 1;
+    if (w < S::finishers) {
+        if (nx >= 1) load(0, x0, n0);
+        if (nx >= 2) load(1, x1, n1);
+    }
+    __syncthreads();
+    double rv[3] = {0.0, 0.0, 0.0};
+    T o[PW];
+    if (w < S::finishers) {
+        const T *q = prod + lane;
+        switch (w) {
+        case 0: split_sum<SP, DAG, 0>(q, o); break;
+        case 1: split_sum<SP, DAG, 1>(q, o); break;
+        case 2: split_sum<SP, DAG, 2>(q, o); break;
+        case 3: if constexpr (!S::half) split_sum<SP, DAG, 3 % S::finishers>(q, o); break;
+        case 4: if constexpr (!S::half) split_sum<SP, DAG, 4 % S::finishers>(q, o); break;
+        default: if constexpr (!S::half) split_sum<SP, DAG, 5 % S::finishers>(q, o); break;
+        }
+        if constexpr (!S::half) {
+            const T c = (T)cf[4];
+#pragma unroll
+            for (int i = 0; i < PW; ++i) o[i] *= c;
+        }
+        if (nx >= 1) {
+            const T s0 = (T)cf[0] * n0;
+#pragma unroll
+            for (int i = 0; i < PW; ++i) o[i] = fmadd(x0[i], s0, o[i]);
+        }
+        if (a.epi.g5) {
+#pragma unroll
+            for (int i = 0; i < PW; ++i)
+                if (w * PW + i >= 12) o[i] = -o[i];
+        }
+        if (nx >= 2) {
+            const T s1 = (T)cf[1] * n1;
+#pragma unroll
+            for (int i = 0; i < PW; ++i) o[i] = fmadd(x1[i], s1, o[i]);
+        }
+        for (int j = 2; j < nx; ++j) {
+            T x[PW], n;
+            load(j, x, n);
+            const T sj = (T)cf[j] * n;
+#pragma unroll
+            for (int i = 0; i < PW; ++i) o[i] = fmadd(x[i], sj, o[i]);
+        }
+        if (a.red.kind != RED_NONE && live) {
+            T s = 0;
+#pragma unroll
+            for (int i = 0; i < PW; ++i) s = fmadd(o[i], o[i], s);
+            if (a.red.mode == RM_NORM) {
+                rv[0] = (double)s;
+            } else {
+                // <X1, o> or <o, X0>; linear in x: its site norm scales the sums
+                const bool dot1 = a.red.mode == RM_DOT_X1;
+                T cr = 0, ci = 0;
+#pragma unroll
+                for (int i = 0; i < PW; i += 2) {
+                    const T xr = dot1 ? x1[i] : x0[i], xi = dot1 ? x1[i + 1] : x0[i + 1];
+                    cr = fmadd(xr, o[i], cr);
+                    cr = fmadd(xi, o[i + 1], cr);
+                    ci = fmadd(xr, o[i + 1], ci);
+                    ci = fmadd(-xi, o[i], ci);
+                }
+                const double nx1 = (double)(dot1 ? n1 : n0);
+                rv[0] = (double)cr * nx1;
+                rv[1] = (dot1 ? (double)ci : -(double)ci) * nx1;
+                rv[2] = (double)s;
+            }
+        }
+    }
+    if constexpr (S::half) {
+        // the site's norm is the largest of its 24 reals
+        float m = 0.f;
+        if (w < S::finishers) {
+#pragma unroll
+            for (int i = 0; i < PW; ++i) m = fmaxf(m, fabsf(o[i]));
+            s_max[w][lane] = m;
+        }
+        __syncthreads();
+        if (w < S::finishers) {
+            m = fmaxf(fmaxf(s_max[0][lane], s_max[1][lane]), s_max[2][lane]);
+            const float inv = m > 0.f ? 1.0f / m : 0.f;
+            uint32_t qw[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) qw[k] = pack2<SP>(o[2 * k] * inv, o[2 * k + 1] * inv);
+            if constexpr (CANON) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    o[2 * k] = lo16_to_float<SP>(qw[k]) * m;
+                    o[2 * k + 1] = hi16_to_float<SP>(qw[k]) * m;
+                }
+            } else if (live) {
+                st_out<true>(row_elem<uint4>((CH *)f.out + voff, w, sd.stride, cb), uint4{qw[0], qw[1], qw[2], qw[3]});
+                if (w == 0) st_out<true>(row_elem<float>(f.out_norm + vd.site_off, 0, 0, cb), m);
+            }
+        }
+    } else if constexpr (!CANON) {
+        if (w < S::finishers && live) {
+            void *out = (CH *)f.out + voff;
+            if constexpr (SP == P_F64) {
+                st_out<true>(row_elem<double2>(out, 2 * w, sd.stride, cb), double2{o[0], o[1]});
+                st_out<true>(row_elem<double2>(out, 2 * w + 1, sd.stride, cb), double2{o[2], o[3]});
+            } else {
+                st_out<true>(row_elem<float4>(out, w, sd.stride, cb), float4{o[0], o[1], o[2], o[3]});
+            }
+        }
+    }
+    if constexpr (CANON) {
+        // the block's 64 pairs in whole lines (see store_canon), staged behind the products
+        T *site = prod + S::buf;
+        const unsigned long long slots = __ballot(st.x & 1);  // the same in every wave
+        if (w < S::finishers) {
+#pragma unroll
+            for (int i = 0; i < PW; ++i) site[lane * S::canon_row + w * PW + i] = o[i];
+        }
+        __syncthreads();
+        const int ns = min(64, sd.Vh - bm.lblk * 64);
+        double *base = a.canon + ((size_t)vd.rhs * (size_t)sd.Vh + (size_t)bm.lblk * 64) * 48;
+        if (a.canon_zero) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const int e = i * 512 + (int)threadIdx.x, j = e / 24, r = e % 24;
+                const int k = r < 12 ? r : r - 12;
+                const bool mine = (int)((slots >> j) & 1) == (r >= 12);
+                const T *p = site + j * S::canon_row + 2 * k;
+                if (j < ns) st_canon(base + 2 * e, mine ? (double)p[0] : 0.0, mine ? (double)p[1] : 0.0);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int e = i * 512 + (int)threadIdx.x, j = e / 12, k = e % 12;
+                if (j < ns) {
+                    const T *p = site + j * S::canon_row + 2 * k;
+                    st_canon(base + 48 * j + 24 * (int)((slots >> j) & 1) + 2 * k, (double)p[0], (double)p[1]);
+                }
+            }
+        }
+    }
+    if (a.red.kind != RED_NONE) block_reduce_store_n(a.red, vd.pslot0, bm.lblk, rv);
+    if (a.stamps) {
+        __syncthreads();
+        if (threadIdx.x == 0) a.stamps[2 * lb + 1] = (unsigned long long)wall_clock64();
+    }
+}
+
 // With events, the dispatch itself records them at the kernel's start and end
 // (the kernel-timing form of the launch), so the measured interval is the
 // kernel alone.
@@ -670,6 +1005,18 @@ static hipError_t launch_hop_pencil(bool dag, const HopArgs &a, int block, hipSt
     return hipGetLastError();
 }
 
+template <int SP, int GP, int R, bool CANON>
+static hipError_t launch_hop_split(bool dag, const HopArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+{
+    using S = SplitHop<SP>;
+    const unsigned lds = (unsigned)(S::buf + (CANON ? 64 * S::canon_row : 0)) * (unsigned)sizeof(typename S::T);
+    if (dag)
+        dispatch(k_hop_split<SP, GP, R, true, CANON>, a, 512, s, e0, e1, lds);
+    else
+        dispatch(k_hop_split<SP, GP, R, false, CANON>, a, 512, s, e0, e1, lds);
+    return hipGetLastError();
+}
+
 template <int SP, int GP, int R>
 hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, int block, hipStream_t s,
                                hipEvent_t e0, hipEvent_t e1)
@@ -690,6 +1037,10 @@ hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, int bloc
                            : launch_hop_lds<SP, GP, R, false>(dag, a, block, s, e0, e1);
         }
         return hipErrorInvalidValue;
+    case 11:
+        if (clov || block != 64) return hipErrorInvalidValue;  // 64 sites on 512 threads
+        return a.canon ? launch_hop_split<SP, GP, R, true>(dag, a, s, e0, e1)
+                       : launch_hop_split<SP, GP, R, false>(dag, a, s, e0, e1);
     case 9:
     case 10:
         if constexpr (SP != P_F64) {
@@ -724,8 +1075,9 @@ WL_HOP_EXTERN(P_F16, P_F16, 12);
 WL_HOP_EXTERN(P_BF16, P_BF16, 12);
 #undef WL_HOP_EXTERN
 
-// FP64 runs variants 0-7 (variants 8-10 stage FP32 or half-precision data in LDS)
-int hop_variants(int prec) { return prec == P_F64 ? 8 : kHopVariants; }
+// (FP64 has no variants 8-10, which stage FP32 or half-precision data in LDS)
+bool hop_has_variant(int prec, int var) { return var >= 0 && var < kHopVariants && !(prec == P_F64 && var >= 8 && var <= 10); }
+int hop_variants() { return kHopVariants; }
 
 hipError_t launch_hop(int prec, int recon, bool dag, bool clov, int var, const HopArgs &a, int block, hipStream_t s,
                       hipEvent_t e0, hipEvent_t e1)

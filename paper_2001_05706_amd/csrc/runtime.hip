@@ -724,7 +724,8 @@ std::vector<int> hop_candidates(int prec)
     const bool half = prec == P_F16 || prec == P_BF16;
     std::vector<int> c;
     for (int col : {4, 16})
-        for (int v = 0; v < hop_variants(prec); ++v) {
+        for (int v = 0; v < hop_variants(); ++v) {
+            if (!hop_has_variant(prec, v)) continue;
             if ((v == 4 || v == 5) && !half) continue;  // four directions in flight: half precision only
             // variants 6 and 8: 4 or 8 (8: also 12 or 16) right-hand sides per block
             if (v == 6 || v == 8) {
@@ -738,6 +739,11 @@ std::vector<int> hop_candidates(int prec)
             // pencil blocks of 2, 4 or 8 time slices
             if (v == 9 || v == 10) {
                 for (int b : {128, 256, 512}) c.push_back(cfg_make(v, b, col));
+                continue;
+            }
+            // variant 11: 64 sites of one vector per block
+            if (v == 11) {
+                c.push_back(cfg_make(v, 64, col));
                 continue;
             }
             for (int b : {64, 128, 256, 512}) c.push_back(cfg_make(v, b, col));
@@ -756,7 +762,7 @@ static wl_status hop_layout(ExecSet &S, int cfg, const Layout **L)
     const int var = cfg_var(cfg), B = cfg_block(cfg);
     const int key = var == 6 || var == 8 ? -(B / 64)
                     : var == 7           ? kPairLayout + B
-                    : var >= 9           ? kPencilLayout + B / 64
+                    : var == 9 || var == 10 ? kPencilLayout + B / 64
                                          : B;
     return S.layout(key, L, cfg_col(cfg));
 }
@@ -780,7 +786,7 @@ static std::vector<int> hop_cands(const ExecSet &S, int prec, bool clov)
         const int v = cfg_var(c);
         if (clov && (v == 1 || v == 2 || v >= 8)) continue;
         if (max_nrhs < 2 && v >= 6 && v <= 8) continue;
-        if (v >= 9) {
+        if (v == 9 || v == 10) {
             bool ok = slices64;
             for (auto &e : S.systems) ok = ok && e.g->geom.L[3] % (cfg_block(c) / 64) == 0;
             if (!ok) continue;

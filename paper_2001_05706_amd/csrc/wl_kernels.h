@@ -41,12 +41,13 @@ struct PackArgs {
 };
 
 // hop.hip
-// var selects a launch variant (0 .. hop_variants(prec)-1, see hop.hip); clov
+// var selects a launch variant (0 .. hop_variants()-1, see hop.hip); clov
 // selects the instantiation with the clover epilogue; with events e0/e1 the
 // dispatch records them at the kernel's start and end
 hipError_t launch_hop(int prec, int recon, bool dag, bool clov, int var, const HopArgs &a, int block, hipStream_t s,
                       hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
-int hop_variants(int prec);  // launch variants available for a storage precision
+int hop_variants();
+bool hop_has_variant(int prec, int var);  // the variant exists for a storage precision
 
 // blas.hip -- all operate on the vectors of one set through its block map
 enum BlasOp {
