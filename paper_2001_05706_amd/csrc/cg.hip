@@ -163,28 +163,39 @@ struct Cg {
             Field fp[3] = {p, rl, q};
             WL_TRY(blas(S, BL_BICG_P, sloppy, fp, 3, nullptr, no_red(), s));
             WL_TRY(hop(S, sloppy, recon, false, 1, tl, p, first(c_plain), no_red(), s));
-            WL_TRY(hop(S, sloppy, recon, false, 0, q, tl, second(c_M, 2, p, rhat),
-                       red_spec(S, RED_BICG_ALPHA, nullptr, 2, RM_DOT_X1), s));
+            // (few partials of alpha and omega are left to the updates that use them)
+            RedSpec ra = red_spec(S, RED_BICG_ALPHA, nullptr, 2, RM_DOT_X1);
+            RedSpec ro = red_spec(S, RED_BICG_OMEGA, nullptr, 3, RM_OUT_X0);
+            ra.defer = ro.defer = 2;
+            WL_TRY(hop(S, sloppy, recon, false, 0, q, tl, second(c_M, 2, p, rhat), ra, s));
             Field fs[3] = {sv, rl, q};
-            WL_TRY(blas(S, BL_BICG_S, sloppy, fs, 3, nullptr, no_red(), s));
+            WL_TRY(blas(S, BL_BICG_S, sloppy, fs, 3, nullptr, no_red(), s, true, 0, 0, S.fold));
             WL_TRY(hop(S, sloppy, recon, false, 1, tl, sv, first(c_plain), no_red(), s));
-            WL_TRY(hop(S, sloppy, recon, false, 0, tb, tl, second(c_M, 1, sv),
-                       red_spec(S, RED_BICG_OMEGA, nullptr, 3, RM_OUT_X0), s));
+            WL_TRY(hop(S, sloppy, recon, false, 0, tb, tl, second(c_M, 1, sv), ro, s));
             Field fx[6] = {xl, p, sv, rl, tb, rhat};
-            WL_TRY(blas(S, BL_BICG_XR, sloppy, fx, 6, nullptr, red_spec(S, RED_BICG_RHO, hist_row, 3), s));
+            // (its own partials go behind the hop's, which other blocks may still be reading)
+            RedSpec rr = red_spec(S, RED_BICG_RHO, hist_row, 3);
+            rr.partials += (size_t)3 * S.max_pslots;
+            const Layout *fold = S.fold;
+            WL_TRY(blas(S, BL_BICG_XR, sloppy, fx, 6, nullptr, rr, s, true, 0, 0, fold));
             return WL_OK;
         }
         // q = M p, alpha = gamma / |q|^2;  r -= alpha q;  s = M^dagger r, beta;
         // then x += alpha p and p = s + beta p in one pass over p
-        WL_TRY(apply_M(sloppy, recon, false, q, p, tl, red_spec(S, RED_ALPHA, nullptr)));
+        // (few partials of alpha and beta are left to the updates that use them)
+        RedSpec ra = red_spec(S, RED_ALPHA, nullptr), rb = red_spec(S, RED_BETA, nullptr);
+        ra.defer = 2;
+        WL_TRY(apply_M(sloppy, recon, false, q, p, tl, ra));
+        const Layout *fold = S.fold;
+        rb.defer = fold ? 2 : 0;
         Field f[2] = {rl, q};
         RedSpec rr = red_spec(S, RED_STORE, hist_row);
         rr.partials = S.hist_partials + (size_t)j * S.max_pslots;
         rr.defer = 1;
-        WL_TRY(blas(S, BL_R_UPDATE, sloppy, f, 2, S.scal(SC_ALPHA), rr, s));
-        WL_TRY(apply_M(sloppy, recon, true, sv, rl, tl, red_spec(S, RED_BETA, nullptr)));
+        WL_TRY(blas(S, BL_R_UPDATE, sloppy, f, 2, S.scal(SC_ALPHA), rr, s, true, 0, 0, fold));
+        WL_TRY(apply_M(sloppy, recon, true, sv, rl, tl, rb));
         Field g[3] = {p, sv, xl};
-        WL_TRY(blas(S, BL_XPAY_X, sloppy, g, 3, S.scal(SC_BETA), no_red(), s));
+        WL_TRY(blas(S, BL_XPAY_X, sloppy, g, 3, S.scal(SC_BETA), no_red(), s, true, 0, 0, S.fold));
         return WL_OK;
     }
 

@@ -47,8 +47,7 @@ namespace wl {
 //  10: pencil blocks with cached links; fence 4 for FP16/BF16, 2 for FP32
 //      (FP32 and half-precision storage, Wilson epilogue; lattices whose time
 //      slices hold a multiple of 64 sites)
-//  11: the eight directions of 64 sites on the eight waves of a block (k_hop_split;
-//      Wilson epilogue)
+//  11: the eight directions of 64 sites on the eight waves of a block (k_hop_split)
 // Variants 4 and 5 exist for FP16/BF16 storage only (FP32 and FP64 operands of
 // four directions do not fit the registers); for those they repeat variant 3.
 template <int SP, int VAR> struct HopVar {
@@ -742,14 +741,65 @@ __device__ __forceinline__ void split_load(const void *base, int stride, int cb,
     }
 }
 
-template <int SP, int GP, int R, bool DAG, bool CANON>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SplitHop<SP>::waves)))
+// The 24 reals of a site as far as finishing wave W needs them for its rows of the
+// clover term: the six complex numbers of the block (or, half precision, blocks)
+// that its reals belong to, norm applied.
+template <int SP, int W, class T>
+__device__ __forceinline__ void split_load_blocks(const void *base, const float *norm, int stride, int cb, T x[24])
+{
+    constexpr int PW = SplitHop<SP>::per_wave;
+    if constexpr (SP == P_F64 || SP == P_F32) {
+        constexpr int b = W * PW / 12, per = 12 / PW;
+#pragma unroll
+        for (int c = 0; c < per; ++c) split_load<SP, false>(base, stride, cb, b * per + c, x + (b * per + c) * PW);
+    } else {
+        load_spinor<SP>(base, norm, stride, cb, x);
+    }
+}
+
+// y = the rows W * per_wave ... of the packed clover term applied to x, in the
+// order of clover_apply
+template <int SP, int W, class T>
+__device__ __forceinline__ void split_clover(const void *base, int stride, int cb, const T x[24], T *y)
+{
+    constexpr int PW = SplitHop<SP>::per_wave, CP = clover_prec<SP>();
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int lo = W * PW > 12 * b ? W * PW : 12 * b, hi = W * PW + PW < 12 * b + 12 ? W * PW + PW : 12 * b + 12;
+        if (lo >= hi) continue;
+        T m[36];
+        clover_block<CP>(base, stride, cb, b, m);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            const int k = 12 * b + 2 * i;
+            if (k < lo || k >= hi) continue;
+            T yr, yi;
+            clover_row(m, x + 12 * b, i, yr, yi);
+            y[k - W * PW] = yr;
+            y[k - W * PW + 1] = yi;
+        }
+    }
+}
+
+#define WL_EACH_FINISHER(w, CALL)                                          \
+    switch (w) {                                                           \
+    case 0: CALL(0); break;                                                \
+    case 1: CALL(1); break;                                                \
+    case 2: CALL(2); break;                                                \
+    case 3: if constexpr (!S::half) CALL(3 % S::finishers); break;         \
+    case 4: if constexpr (!S::half) CALL(4 % S::finishers); break;         \
+    default: if constexpr (!S::half) CALL(5 % S::finishers); break;        \
+    }
+
+template <int SP, int GP, int R, bool DAG, int EP>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(EP & EP_CLOVER ? 4 : SplitHop<SP>::waves)))
 void k_hop_split(HopArgs a)
 {
+    constexpr bool CLOV = EP == EP_CLOVER || EP == EP_CLOVER_CANON, CANON = EP >= EP_CANON;
     using S = SplitHop<SP>;
     using T = typename S::T;
     using CH = typename SpinorFmt<SP>::chunk;
-    constexpr int PW = S::per_wave;
+    constexpr int PW = S::per_wave, CP = clover_prec<SP>();
     extern __shared__ uint4 s_split[];
     __shared__ float s_max[S::half ? S::finishers : 1][64];
     T *prod = reinterpret_cast<T *>(s_split);
@@ -808,20 +858,34 @@ void k_hop_split(HopArgs a)
     T o[PW];
     if (w < S::finishers) {
         const T *q = prod + lane;
-        switch (w) {
-        case 0: split_sum<SP, DAG, 0>(q, o); break;
-        case 1: split_sum<SP, DAG, 1>(q, o); break;
-        case 2: split_sum<SP, DAG, 2>(q, o); break;
-        case 3: if constexpr (!S::half) split_sum<SP, DAG, 3 % S::finishers>(q, o); break;
-        case 4: if constexpr (!S::half) split_sum<SP, DAG, 4 % S::finishers>(q, o); break;
-        default: if constexpr (!S::half) split_sum<SP, DAG, 5 % S::finishers>(q, o); break;
-        }
+#define WL_SUM(W) split_sum<SP, DAG, W>(q, o)
+        WL_EACH_FINISHER(w, WL_SUM)
+#undef WL_SUM
         if constexpr (!S::half) {
             const T c = (T)cf[4];
 #pragma unroll
             for (int i = 0; i < PW; ++i) o[i] *= c;
         }
-        if (nx >= 1) {
+        bool plain = nx >= 1;
+        if constexpr (CLOV) {
+            if (nx >= 1 && (a.epi.clov & EPI_CLOV_X0) && sd.clov) {
+                plain = false;
+                const void *cl = clover_parity<CP>(sd.clov, f.parity, sd.stride);
+                const float *xn = f.Xn[0] ? f.Xn[0] + vd.site_off : nullptr;
+                T xs[24], y[PW];
+#define WL_CLOV(W)                                                                       \
+    {                                                                                    \
+        split_load_blocks<SP, W>((const CH *)f.X[0] + voff, xn, sd.stride, ccb, xs);     \
+        split_clover<SP, W>(cl, sd.stride, ccb, xs, y);                                  \
+    }
+                WL_EACH_FINISHER(w, WL_CLOV)
+#undef WL_CLOV
+                const T s0 = (T)cf[0];
+#pragma unroll
+                for (int i = 0; i < PW; ++i) o[i] = fmadd(y[i], s0, o[i]);
+            }
+        }
+        if (plain) {
             const T s0 = (T)cf[0] * n0;
 #pragma unroll
             for (int i = 0; i < PW; ++i) o[i] = fmadd(x0[i], s0, o[i]);
@@ -831,6 +895,29 @@ void k_hop_split(HopArgs a)
             for (int i = 0; i < PW; ++i)
                 if (w * PW + i >= 12) o[i] = -o[i];
         }
+    }
+    if constexpr (CLOV) {
+        if ((a.epi.clov & EPI_CLOV_INV) && sd.clovinv) {  // uniform over the block
+            // the rows of A^-1 need the whole block of the site: exchanged through LDS
+            T *site = prod + S::buf;
+            if (w < S::finishers) {
+#pragma unroll
+                for (int i = 0; i < PW; ++i) site[(w * PW + i) * 64 + lane] = o[i];
+            }
+            __syncthreads();
+            if (w < S::finishers) {
+                T xs[24];
+#pragma unroll
+                for (int k = 0; k < 24; ++k) xs[k] = site[k * 64 + lane];
+                const void *cl = clover_parity<CP>(sd.clovinv, f.parity, sd.stride);
+#define WL_CLOV_INV(W) split_clover<SP, W>(cl, sd.stride, ccb, xs, o)
+                WL_EACH_FINISHER(w, WL_CLOV_INV)
+#undef WL_CLOV_INV
+            }
+            if constexpr (CANON) __syncthreads();  // the stage of the canonical store lies there too
+        }
+    }
+    if (w < S::finishers) {
         if (nx >= 2) {
             const T s1 = (T)cf[1] * n1;
 #pragma unroll
@@ -1005,15 +1092,15 @@ static hipError_t launch_hop_pencil(bool dag, const HopArgs &a, int block, hipSt
     return hipGetLastError();
 }
 
-template <int SP, int GP, int R, bool CANON>
+template <int SP, int GP, int R, int EP>
 static hipError_t launch_hop_split(bool dag, const HopArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
     using S = SplitHop<SP>;
-    const unsigned lds = (unsigned)(S::buf + (CANON ? 64 * S::canon_row : 0)) * (unsigned)sizeof(typename S::T);
+    const unsigned lds = (unsigned)(S::buf + (EP != EP_WILSON ? 64 * S::canon_row : 0)) * (unsigned)sizeof(typename S::T);
     if (dag)
-        dispatch(k_hop_split<SP, GP, R, true, CANON>, a, 512, s, e0, e1, lds);
+        dispatch(k_hop_split<SP, GP, R, true, EP>, a, 512, s, e0, e1, lds);
     else
-        dispatch(k_hop_split<SP, GP, R, false, CANON>, a, 512, s, e0, e1, lds);
+        dispatch(k_hop_split<SP, GP, R, false, EP>, a, 512, s, e0, e1, lds);
     return hipGetLastError();
 }
 
@@ -1038,9 +1125,12 @@ hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, int bloc
         }
         return hipErrorInvalidValue;
     case 11:
-        if (clov || block != 64) return hipErrorInvalidValue;  // 64 sites on 512 threads
-        return a.canon ? launch_hop_split<SP, GP, R, true>(dag, a, s, e0, e1)
-                       : launch_hop_split<SP, GP, R, false>(dag, a, s, e0, e1);
+        if (block != 64) return hipErrorInvalidValue;  // 64 sites on 512 threads
+        if (clov)
+            return a.canon ? launch_hop_split<SP, GP, R, EP_CLOVER_CANON>(dag, a, s, e0, e1)
+                           : launch_hop_split<SP, GP, R, EP_CLOVER>(dag, a, s, e0, e1);
+        return a.canon ? launch_hop_split<SP, GP, R, EP_CANON>(dag, a, s, e0, e1)
+                       : launch_hop_split<SP, GP, R, EP_WILSON>(dag, a, s, e0, e1);
     case 9:
     case 10:
         if constexpr (SP != P_F64) {

@@ -396,7 +396,7 @@ wl_status ExecSet::init()
     if (total_sites > (size_t)INT32_MAX / 16) return set_error(WL_ERR_GEOM, "set too large");
     h_active.assign(nvec, 1);
     WL_ALLOC(d_active, sizeof(int32_t) * nvec);
-    WL_ALLOC(partials, sizeof(double) * 3 * max_pslots);
+    WL_ALLOC(partials, sizeof(double) * 2 * 3 * max_pslots);
     WL_ALLOC(sc, sizeof(double) * SC_N * nvec);
     WL_ALLOC(hist, sizeof(double) * kHist * nvec);
     WL_ALLOC(bad, sizeof(int32_t) * nvec);
@@ -499,6 +499,7 @@ wl_status ExecSet::layout(int B, const Layout **out, int col)
         const int nb = (systems[i].g->geom.Vh + sites - 1) / sites;
         for (int r = 0; r < nrhs; ++r) {
             hv[vbase + r].nblk = nb;
+            L.max_nblk = std::max(L.max_nblk, nb);
             hv[vbase + r].pslot0 = ps;
             ps += nb;
         }
@@ -784,7 +785,7 @@ static std::vector<int> hop_cands(const ExecSet &S, int prec, bool clov)
     std::vector<int> cands;
     for (int c : hop_candidates(prec)) {
         const int v = cfg_var(c);
-        if (clov && (v == 1 || v == 2 || v >= 8)) continue;
+        if (clov && (v == 1 || v == 2 || (v >= 8 && v <= 10))) continue;
         if (max_nrhs < 2 && v >= 6 && v <= 8) continue;
         if (v == 9 || v == 10) {
             bool ok = slices64;
@@ -797,11 +798,34 @@ static std::vector<int> hop_cands(const ExecSet &S, int prec, bool clov)
     return cands;
 }
 
+static const int kBlasBlock = 256;
+
+// The most block partials of a vector that a consuming update sums itself
+// instead of waiting for a finishing launch (4.5 us and its gap).  Every block of
+// the update reads all of them: with up to 2048 that hides behind its field loads
+// (CGNR: 4^4 FP64 1485 -> 1350 us, 16^3x32 FP32 4440 -> 4230, 32^3x64 FP16 33.0 ->
+// 32.8 ms); with 16384 (64-site blocks at 32^3x64) the FP16 solve took 36.8 ms.
+constexpr int kFoldPartials = 2048;
+
 // A kind of hop launch of a set, as an index into its plans
 static int plan_id(int prec, int recon, bool dag, bool clov, const Epi &e, bool red, bool twin)
 {
     return prec | (recon == 12) << 2 | (int)dag << 3 | (int)clov << 4 | (int)red << 5 | (int)twin << 6 |
            (e.canon != nullptr) << 7 | e.nx << 8;
+}
+
+// Up to this many blocks of 64 sites a set's hop is variant 11 without timing it:
+// all its blocks are resident at once, and the hop lasts as long as its chain of
+// latencies (512 blocks, FP32 16^4: 4.5 us against 7.1 for the best per-site
+// variant; 32 blocks: 3.5 against 6.6; 12 RHS of 8^4, 384 blocks: 4.4 against 10.6;
+// at 1024 blocks FP64 already loses, 14.9 against 13.7).  Timed from the host,
+// launches this short cannot be told apart.
+constexpr int kSplitBlocks = 512;
+static int blocks64(const ExecSet &S)
+{
+    int n = 0;
+    for (auto &e : S.systems) n += e.nrhs * ((e.g->geom.Vh + 63) / 64);
+    return n;
 }
 
 // The launch configuration and block map of one kind of hop: from the set's plans
@@ -821,6 +845,13 @@ static wl_status hop_plan(ExecSet &S, int id, ExecSet::HopPlan *pl, hipStream_t 
         }
     }
     bool settled = false;
+    const char *tune = getenv("WL_TUNE");
+    if (!pinned && !(tune && tune[0] == '0') && blocks64(S) <= kSplitBlocks) {
+        pl->cfg = cfg_make(11, 64, 4);
+        WL_TRY(hop_layout(S, pl->cfg, &pl->L));
+        S.plans[id] = *pl;
+        return WL_OK;
+    }
     pl->cfg = tuned_block(key(), cands(), s,
                           [&](int c) -> hipError_t {
                               const Layout *L = nullptr;
@@ -927,7 +958,11 @@ wl_status hop(ExecSet &S, int prec, int recon, bool dag, int par, const Field &o
     } else {
         WL_HIP(launch_hop(prec, recon, dag, clov, var, mk(L, red), B, s));
     }
-    if (red.kind != RED_NONE) WL_HIP(launch_red_finalize(red, L->d_vec, use_active ? S.d_active : nullptr, S.nvec, s));
+    // few partials are summed by the kernel that needs the scalar, in each of its
+    // blocks while its field loads are under way
+    S.fold = red.kind != RED_NONE && red.defer == 2 && L->max_nblk <= kFoldPartials ? L : nullptr;
+    if (red.kind != RED_NONE && !S.fold)
+        WL_HIP(launch_red_finalize(red, L->d_vec, use_active ? S.d_active : nullptr, S.nvec, s));
     return WL_OK;
 }
 
@@ -1009,10 +1044,9 @@ wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], co
     return WL_OK;
 }
 
-static const int kBlasBlock = 256;
 
 wl_status blas(ExecSet &S, int op, int prec, const Field *f, int nf, const double *s0, const RedSpec &red,
-               hipStream_t s, bool use_active, int parity, int bcast)
+               hipStream_t s, bool use_active, int parity, int bcast, const Layout *fold)
 {
     const SysDesc *sysd = nullptr;
     if (op == BL_CLOV_INV)
@@ -1039,6 +1073,12 @@ wl_status blas(ExecSet &S, int op, int prec, const Field *f, int nf, const doubl
     a.red = red;
     a.parity = parity;
     a.bcast = bcast;
+    if (fold) {
+        a.fold_vec = fold->d_vec;
+        a.fold_partials = S.partials;
+        a.fold_sc = S.sc;
+        a.fold_bad = S.bad;
+    }
     static const int passes[] = {6, 3, 0, 1, 1, 2, 1, 2, 4, 3, 7, 2, 2, 2, 3, 3, 0, 3, 5};
     if (op == BL_CLOV_INV) g_bytes_acc += clover_bytes(S, prec, use_active);
     if (op == BL_ROT) g_bytes_acc += blas_bytes(S, prec, S.nvec + 1, use_active);

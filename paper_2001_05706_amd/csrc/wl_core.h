@@ -583,72 +583,79 @@ template <int P> constexpr int clover_prec() { return P == P_F64 ? P_F64 : P == 
 // packed index of entry (i, j), i < j, of a 6x6 block
 WL_HD int clov_upper(int i, int j) { return 6 + 2 * (i * 6 - i * (i + 1) / 2 + (j - i - 1)); }
 
-// o <- A o (or A^{-1} o for the inverse field) at site cb; base is the parity's chunk 0
+// block b (36 reals) of the packed clover term at site cb; base is the parity's chunk 0
 template <int P, class T>
-WL_HD void clover_apply(const void *base, int stride, int cb, T o[24])
+WL_HD void clover_block(const void *base, int stride, int cb, int b, T m[36])
 {
     using CF = CloverFmt<P>;
-    uint32_t h[36];  // FP16: the site's 72 halves, two per word
     if constexpr (P == P_F16) {
+        // 18 words: rows of four, the second block from the middle of row 4 on
+        uint32_t h[20];
+        const int r0 = b ? 4 : 0;
 #pragma unroll
-        for (int c = 0; c < 9; ++c) {
-            const uint4 w = *row_elem<uint4>(base, c, stride, cb);
+        for (int c = 0; c < 5; ++c) {
+            const uint4 w = *row_elem<uint4>(base, r0 + c, stride, cb);
             h[4 * c] = w.x;
             h[4 * c + 1] = w.y;
             h[4 * c + 2] = w.z;
             h[4 * c + 3] = w.w;
         }
+#pragma unroll
+        for (int k = 0; k < 18; ++k) {
+            const uint32_t w = b ? h[2 + k] : h[k];
+            m[2 * k] = (T)lo16_to_float<P_F16>(w);
+            m[2 * k + 1] = (T)hi16_to_float<P_F16>(w);
+        }
+    } else if constexpr (P == P_F64) {
+#pragma unroll
+        for (int c = 0; c < 18; ++c) {
+            const double2 w = *row_elem<double2>(base, 18 * b + c, stride, cb);
+            m[2 * c] = (T)w.x;
+            m[2 * c + 1] = (T)w.y;
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < 9; ++c) {
+            const float4 w = *row_elem<typename CF::chunk>(base, 9 * b + c, stride, cb);
+            m[4 * c] = (T)w.x;
+            m[4 * c + 1] = (T)w.y;
+            m[4 * c + 2] = (T)w.z;
+            m[4 * c + 3] = (T)w.w;
+        }
     }
+}
+
+// row i of a packed block applied to the block's 12 reals x
+template <class T> WL_HD void clover_row(const T m[36], const T *x, int i, T &yr, T &yi)
+{
+    yr = m[i] * x[2 * i];
+    yi = m[i] * x[2 * i + 1];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        if (j == i) continue;
+        // M_ij = (re, im) for i < j; M_ij = conj(M_ji) for i > j
+        const int u = i < j ? clov_upper(i, j) : clov_upper(j, i);
+        const T mr = m[u], mi = i < j ? m[u + 1] : -m[u + 1];
+        // fused multiply-adds written out (every launch variant rounds alike)
+        yr = fmadd(mr, x[2 * j], yr);
+        yr = fmadd(-mi, x[2 * j + 1], yr);
+        yi = fmadd(mr, x[2 * j + 1], yi);
+        yi = fmadd(mi, x[2 * j], yi);
+    }
+}
+
+// o <- A o (or A^{-1} o for the inverse field) at site cb; base is the parity's chunk 0
+template <int P, class T>
+WL_HD void clover_apply(const void *base, int stride, int cb, T o[24])
+{
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-        T m[36];
-        if constexpr (P == P_F16) {
+        T m[36], y[12];
+        clover_block<P>(base, stride, cb, b, m);
 #pragma unroll
-            for (int k = 0; k < 36; ++k) {
-                const int e = 36 * b + k;
-                m[k] = (T)(e & 1 ? hi16_to_float<P_F16>(h[e >> 1]) : lo16_to_float<P_F16>(h[e >> 1]));
-            }
-        } else if constexpr (P == P_F64) {
+        for (int i = 0; i < 6; ++i) clover_row(m, o + 12 * b, i, y[2 * i], y[2 * i + 1]);
 #pragma unroll
-            for (int c = 0; c < 18; ++c) {
-                const double2 w = *row_elem<double2>(base, 18 * b + c, stride, cb);
-                m[2 * c] = (T)w.x;
-                m[2 * c + 1] = (T)w.y;
-            }
-        } else {
-#pragma unroll
-            for (int c = 0; c < 9; ++c) {
-                const float4 w = *row_elem<typename CF::chunk>(base, 9 * b + c, stride, cb);
-                m[4 * c] = (T)w.x;
-                m[4 * c + 1] = (T)w.y;
-                m[4 * c + 2] = (T)w.z;
-                m[4 * c + 3] = (T)w.w;
-            }
-        }
-        T xr[6], xi[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            xr[k] = o[12 * b + 2 * k];
-            xi[k] = o[12 * b + 2 * k + 1];
-        }
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            T yr = m[i] * xr[i], yi = m[i] * xi[i];
-#pragma unroll
-            for (int j = 0; j < 6; ++j) {
-                if (j == i) continue;
-                // M_ij = (re, im) for i < j; M_ij = conj(M_ji) for i > j
-                const int u = i < j ? clov_upper(i, j) : clov_upper(j, i);
-                const T mr = m[u], mi = i < j ? m[u + 1] : -m[u + 1];
-                // fused multiply-adds written out (every launch variant rounds alike)
-                yr = fmadd(mr, xr[j], yr);
-                yr = fmadd(-mi, xi[j], yr);
-                yi = fmadd(mr, xi[j], yi);
-                yi = fmadd(mi, xr[j], yi);
-            }
-            o[12 * b + 2 * i] = yr;
-            o[12 * b + 2 * i + 1] = yi;
-        }
+        for (int k = 0; k < 12; ++k) o[12 * b + k] = y[k];
     }
 }
 

@@ -100,6 +100,7 @@ struct Layout {
     int B = 0;
     int nblocks = 0;
     int npslots = 0;
+    int max_nblk = 0;  // blocks of the largest vector
     VecDesc *d_vec = nullptr;
     BlkMap *d_map = nullptr;
 };
@@ -170,7 +171,8 @@ public:
     hipEvent_t rr_ev = nullptr;      // marks a readback the host waits for while later work runs
 
     // reduction state (per vector unless noted)
-    double *partials = nullptr;  // max slots over layouts (B = 64), 3 values each
+    double *partials = nullptr;  // max slots over layouts (B = 64), 3 values each, twice: the hops' and
+                                 // behind them those of an update that reads the hops' (see fold)
     double *sc = nullptr;        // scalar arena, see SC_* below
     int32_t *bad = nullptr;
     double *hist = nullptr;      // residual history: [kHist][nvec]
@@ -203,6 +205,7 @@ public:
         const Layout *L;
     };
     std::map<int, HopPlan> plans;
+    const Layout *fold = nullptr;  // set by hop: the layout of partials left for the consumer
     int max_pslots = 0;
 };
 
@@ -228,14 +231,16 @@ RedSpec no_red();
 RedSpec red_spec(ExecSet &S, int kind, double *dst, int nv = 1, int mode = RM_NORM);
 
 // out_p = epilogue(hop(in_{1-p})) on every active vector of the set
+// (red.defer == 2: S.fold tells afterwards whether the partials were left)
 wl_status hop(ExecSet &S, int prec, int recon, bool dag, int out_parity, const Field &out, const Field &in,
               const Epi &e, const RedSpec &red, hipStream_t s, bool use_active = true);
 // out_p = epi_p(hop(in_{1-p})) for both parities p (no reduction), in one launch
 wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], const Field in[2], const Epi e[2],
                hipStream_t s, bool use_active = true);
-// bcast: bit j marks field j as a single vector shared by every vector of the set
+// bcast: bit j marks field j as a single vector shared by every vector of the set;
+// fold: the layout whose partials the kernel finishes itself (BL_R_UPDATE, BL_XPAY_X)
 wl_status blas(ExecSet &S, int op, int prec, const Field *f, int nf, const double *s0, const RedSpec &red,
-               hipStream_t s, bool use_active = true, int parity = 0, int bcast = 0);
+               hipStream_t s, bool use_active = true, int parity = 0, int bcast = 0, const Layout *fold = nullptr);
 wl_status convert(ExecSet &S, const Field &dst, const Field &src, hipStream_t s, bool use_active = true);
 // canonical <-> packed; canon[i] is the canonical field array of system i: one
 // parity packed, both packed, both unpacked

@@ -21,6 +21,12 @@ struct BlasArgs {
     int32_t one;       // the set holds one vector (its descriptors are at index 0)
     int32_t stream;    // solver-iteration kernels: fields read and written non-temporally
     RedSpec red;
+    // not null (BL_R_UPDATE, BL_XPAY_X, BL_BICG_S, BL_BICG_XR): alpha, beta or omega
+    // is still the producing hop's block partials, laid out by these vector descriptors
+    const VecDesc *fold_vec;
+    const double *fold_partials;
+    double *fold_sc;     // scalar slots, written by each vector's first block
+    int32_t *fold_bad;
 };
 
 constexpr int kMaxSys = 64;  // systems per set (canonical pointers travel by value)

@@ -41,7 +41,7 @@ WL_HD int xcd_remap(int h, int nb)
 // Per-vector scalar slots of a set: scalar `slot` of vector v lives at
 // sc[slot * nvec + v].  Complex scalars use two slots (re, im).
 enum ScSlot {
-    SC_ALPHA = 0, SC_BETA, SC_GAM, SC_QQ, SC_RR, SC_ETA, SC_TMP,
+    SC_ALPHA = 0, SC_BETA, SC_GAM, SC_GAMP /* gamma of the previous step */, SC_QQ, SC_RR, SC_ETA, SC_TMP,
     SC_RHO_RE, SC_RHO_IM,      // BiCGStab rho = <rhat, r>
     SC_RHOP_RE, SC_RHOP_IM,    // rho of the previous iteration
     SC_AL_RE, SC_AL_IM,        // complex alpha
@@ -83,7 +83,8 @@ struct RedSpec {
     double *sc;          // scalar slots (ScSlot)
     double *dst;         // RED_STORE / RED_ACCUM / RED_BICG_RHO target, indexed by vector
     int32_t *bad;        // per-vector non-finite flag (bit 0)
-    int32_t defer;       // 1: leave the partials for a later finishing pass (no finishing launch)
+    int32_t defer;       // 1: leave the partials for a later finishing pass (no finishing launch);
+                         // 2 (a hop's alpha or beta): leave them for the consuming update if they are few
     int32_t pad_;
     double *host;        // RED_STORE / RED_ACCUM: dst[v] also goes here (pinned host memory; null: off)
 };
