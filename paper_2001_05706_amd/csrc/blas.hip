@@ -59,28 +59,6 @@ template <int P> __device__ __forceinline__ const void *fbase(const BlasArgs &a,
     return (a.bcast >> j) & 1 ? a.f[j] : vbase<P>(a.f[j], vd);
 }
 
-// The sums of the NV values of the producing hop's block partials of vector vi, the
-// same in every thread: each block adds them in the same fixed order.
-template <int NV> __device__ __forceinline__ void fold_sum(const BlasArgs &a, int vi, double *sum)
-{
-    __shared__ double s_sum[NV];
-    const VecDesc pd = a.fold_vec[vi];
-    const double *p = a.fold_partials + (size_t)pd.pslot0 * NV;
-    double s[NV];
-#pragma unroll
-    for (int k = 0; k < NV; ++k) s[k] = 0.0;
-    for (int i = threadIdx.x; i < pd.nblk; i += blockDim.x)
-#pragma unroll
-        for (int k = 0; k < NV; ++k) s[k] += p[(size_t)i * NV + k];
-    block_sum_n(s, NV);
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int k = 0; k < NV; ++k) s_sum[k] = s[k];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NV; ++k) sum[k] = s_sum[k];
-}
-
 template <int P, bool ONE = false, bool NT = false>
 __global__ __launch_bounds__(256) void k_cg_update(BlasArgs a)
 {
@@ -122,38 +100,6 @@ __global__ __launch_bounds__(256) void k_xpay(BlasArgs a)
 }
 
 
-// alpha = gamma / |q|^2 from the partials of |q|^2; the vector's first block
-// stores it, and gamma aside for the step that replaces it
-__device__ __forceinline__ double fold_alpha(const BlasArgs &a, int vi, int lblk)
-{
-    const double g = a.sc[SC_GAM * a.nvec + vi];
-    double qq;
-    fold_sum<1>(a, vi, &qq);
-    const double al = qq > 0.0 ? g / qq : 0.0;
-    if (lblk == 0 && threadIdx.x == 0) {
-        a.fold_sc[SC_ALPHA * a.nvec + vi] = al;
-        a.fold_sc[SC_GAMP * a.nvec + vi] = g;
-        if (!isfinite(qq)) a.fold_bad[vi] |= 1;
-    }
-    return al;
-}
-
-// beta = |s|^2 / gamma from the partials of |s|^2, and gamma = |s|^2 (the old gamma
-// is read from where fold_alpha put it: this launch overwrites its slot)
-__device__ __forceinline__ double fold_beta(const BlasArgs &a, int vi, int lblk)
-{
-    const double g = a.sc[SC_GAMP * a.nvec + vi];
-    double ss;
-    fold_sum<1>(a, vi, &ss);
-    const double be = g > 0.0 ? ss / g : 0.0;
-    if (lblk == 0 && threadIdx.x == 0) {
-        a.fold_sc[SC_BETA * a.nvec + vi] = be;
-        a.fold_sc[SC_GAM * a.nvec + vi] = ss;
-        if (!isfinite(ss)) a.fold_bad[vi] |= 1;
-    }
-    return be;
-}
-
 // CGNR with the solution update folded into the direction update: the
 // residual step alone here, x += alpha p with p = s + beta p below.  Their
 // coefficients come from the finishing launch of the hop's reduction, or from
@@ -169,7 +115,7 @@ __global__ __launch_bounds__(256) void k_r_update(BlasArgs a)
         load_spinor<P, NT>(vbase<P>(a.f[0], vd), nbase(a.fn[0], vd), sd.stride, cb, r);
         load_spinor<P, NT>(vbase<P>(a.f[1], vd), nbase(a.fn[1], vd), sd.stride, cb, q);
     }
-    const T al = (T)(a.fold_vec ? fold_alpha(a, vi, bm.lblk) : a.s0[vi]);
+    const T al = (T)(a.fold.vec ? fold_alpha(a.fold, vi, bm.lblk) : a.s0[vi]);
     if (live) {
 #pragma unroll
         for (int k = 0; k < 24; ++k) r[k] -= al * q[k];
@@ -192,7 +138,7 @@ __global__ __launch_bounds__(256) void k_xpay_x(BlasArgs a)
         load_spinor<P, NT>(vbase<P>(a.f[2], vd), nbase(a.fn[2], vd), sd.stride, cb, x);
     }
     const T al = (T)a.sc[SC_ALPHA * a.nvec + vi];
-    const T be = (T)(a.fold_vec ? fold_beta(a, vi, bm.lblk) : a.s0[vi]);
+    const T be = (T)(a.fold.vec ? fold_beta(a.fold, vi, bm.lblk) : a.s0[vi]);
     if (!live) return;
 #pragma unroll
     for (int k = 0; k < 24; ++k) {
@@ -342,20 +288,20 @@ __global__ __launch_bounds__(256) void k_bicg_s(BlasArgs a)
         load_spinor<P, NT>(vbase<P>(a.f[2], vd), nbase(a.fn[2], vd), sd.stride, cb, v);
     }
     double ar, ai;
-    if (a.fold_vec) {
+    if (a.fold.vec) {
         // alpha = rho / <rhat, v> from its partials; rho_prev = rho (as k_red_finalize)
         double rr, ri, d[2];
         cscal(a, SC_RHO_RE, vi, rr, ri);
-        fold_sum<2>(a, vi, d);
+        fold_sum<2>(a.fold, vi, d);
         const double d2 = d[0] * d[0] + d[1] * d[1];
         ar = d2 > 0.0 ? (rr * d[0] + ri * d[1]) / d2 : 0.0;
         ai = d2 > 0.0 ? (ri * d[0] - rr * d[1]) / d2 : 0.0;
         if (bm.lblk == 0 && threadIdx.x == 0) {
-            a.fold_sc[(size_t)SC_AL_RE * a.nvec + vi] = ar;
-            a.fold_sc[(size_t)SC_AL_IM * a.nvec + vi] = ai;
-            a.fold_sc[(size_t)SC_RHOP_RE * a.nvec + vi] = rr;
-            a.fold_sc[(size_t)SC_RHOP_IM * a.nvec + vi] = ri;
-            if (!(d2 > 0.0) || !isfinite(d[0]) || !isfinite(d[1])) a.fold_bad[vi] |= 1;
+            a.fold.sc[(size_t)SC_AL_RE * a.nvec + vi] = ar;
+            a.fold.sc[(size_t)SC_AL_IM * a.nvec + vi] = ai;
+            a.fold.sc[(size_t)SC_RHOP_RE * a.nvec + vi] = rr;
+            a.fold.sc[(size_t)SC_RHOP_IM * a.nvec + vi] = ri;
+            if (!(d2 > 0.0) || !isfinite(d[0]) || !isfinite(d[1])) a.fold.bad[vi] |= 1;
         }
     } else {
         cscal(a, SC_AL_RE, vi, ar, ai);
@@ -381,16 +327,16 @@ __global__ __launch_bounds__(256) void k_bicg_xr(BlasArgs a)
     }
     double ar, ai, orr, oi;
     cscal(a, SC_AL_RE, vi, ar, ai);
-    if (a.fold_vec) {
+    if (a.fold.vec) {
         // omega = <t, s> / |t|^2 from its partials (as k_red_finalize)
         double d[3];
-        fold_sum<3>(a, vi, d);
+        fold_sum<3>(a.fold, vi, d);
         orr = d[2] > 0.0 ? d[0] / d[2] : 0.0;
         oi = d[2] > 0.0 ? d[1] / d[2] : 0.0;
         if (bm.lblk == 0 && threadIdx.x == 0) {
-            a.fold_sc[(size_t)SC_OM_RE * a.nvec + vi] = orr;
-            a.fold_sc[(size_t)SC_OM_IM * a.nvec + vi] = oi;
-            if (!(d[2] > 0.0) || !isfinite(d[0]) || !isfinite(d[1]) || !isfinite(d[2])) a.fold_bad[vi] |= 1;
+            a.fold.sc[(size_t)SC_OM_RE * a.nvec + vi] = orr;
+            a.fold.sc[(size_t)SC_OM_IM * a.nvec + vi] = oi;
+            if (!(d[2] > 0.0) || !isfinite(d[0]) || !isfinite(d[1]) || !isfinite(d[2])) a.fold.bad[vi] |= 1;
         }
     } else {
         cscal(a, SC_OM_RE, vi, orr, oi);

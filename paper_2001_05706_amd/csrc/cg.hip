@@ -152,6 +152,43 @@ struct Cg {
         return WL_OK;
     }
 
+    // The k iterations of a chunk.  Small FP32 and FP64 sets run CGNR in four
+    // launches an iteration instead of six: the updates ride on the hops.  The
+    // launch after an update forms the updated field at its neighbours from the two
+    // fields it comes from (with the scalar from the block partials), and the one
+    // after that stores it at its own sites:
+    //   HI_P: t = D (s + beta p);             HI_Q: x += alpha p, p = s + beta p, q = p - k^2 D t
+    //   HI_R: t = D^+ (r - alpha q);          HI_S: r -= alpha q, s = r - k^2 D^+ t
+    // The first iteration starts from the p that the chunk found, and the last
+    // one's x and p are updated by themselves behind it.
+    wl_status iterations(int k)
+    {
+        if (method != M_CGNR || !iter_fused(S, sloppy)) {
+            for (int j = 0; j < k; ++j) WL_TRY(iteration(j));
+            return hist_report(S, k, method == M_CGNR, s);
+        }
+        const Layout *lq = nullptr, *ls = nullptr;
+        const Field own_q[3] = {sv, p, xl}, own_s[3] = {rl, q, Field()};
+        for (int j = 0; j < k; ++j) {
+            if (j == 0) {
+                RedSpec ra = red_spec(S, RED_ALPHA, nullptr);
+                ra.defer = 2;
+                WL_TRY(apply_M(sloppy, recon, false, q, p, tl, ra));
+                lq = S.fold;
+                if (!lq) return set_error(WL_ERR_ARG, "partials of a small set were not left to its update");
+            } else {
+                WL_TRY(hop_iter(S, sloppy, recon, HI_P, tl, sv, &p, nullptr, c_plain, ls, nullptr, s, nullptr));
+                WL_TRY(hop_iter(S, sloppy, recon, HI_Q, q, tl, nullptr, own_q, c_M, nullptr, nullptr, s, &lq));
+            }
+            WL_TRY(hop_iter(S, sloppy, recon, HI_R, tl, rl, &q, nullptr, c_plain, lq, nullptr, s, nullptr));
+            WL_TRY(hop_iter(S, sloppy, recon, HI_S, sv, tl, nullptr, own_s, c_M, nullptr,
+                            S.hist_partials + (size_t)j * S.max_pslots, s, &ls));
+        }
+        Field g[3] = {p, sv, xl};
+        WL_TRY(blas(S, BL_XPAY_X, sloppy, g, 3, nullptr, no_red(), s, true, 0, 0, ls));
+        return hist_report(S, k, true, s, 64);
+    }
+
     // iteration j of a chunk in the sloppy precision; history row j receives |r|^2
     // (CGNR: its block partials are summed for the whole chunk by hist_finalize)
     wl_status iteration(int j)
@@ -273,9 +310,7 @@ struct Cg {
     wl_status chunk(int k)
     {
         if (!use_graphs || prof().on) {
-            for (int j = 0; j < k; ++j) WL_TRY(iteration(j));
-            WL_TRY(hist_report(S, k, method == M_CGNR, s));
-            return WL_OK;
+            return iterations(k);
         }
         // the coefficient tables are cached by content, so their addresses name
         // the systems' kappas: a chunk captured for other kappas is not reused
@@ -293,9 +328,7 @@ struct Cg {
             hipStream_t user = s;
             s = cs;
             WL_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed));
-            wl_status st = WL_OK;
-            for (int j = 0; j < k && st == WL_OK; ++j) st = iteration(j);
-            if (st == WL_OK) st = hist_report(S, k, method == M_CGNR, s);
+            const wl_status st = iterations(k);
             hipGraph_t g = nullptr;
             hipError_t ce = hipStreamEndCapture(cs, &g);
             s = user;

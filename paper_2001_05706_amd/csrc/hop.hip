@@ -651,6 +651,47 @@ constexpr SplitSrc split_src(int mu, int sg, int k)
     }
 }
 
+// reals w * per_wave ... of a packed FP32 or FP64 site, plain stores (the next
+// launch reads them)
+template <int SP>
+__device__ __forceinline__ void split_store(void *base, int stride, int cb, int w, const typename SplitHop<SP>::T *o)
+{
+    if constexpr (SP == P_F64) {
+        st_out<false>(row_elem<double2>(base, 2 * w, stride, cb), double2{o[0], o[1]});
+        st_out<false>(row_elem<double2>(base, 2 * w + 1, stride, cb), double2{o[2], o[3]});
+    } else {
+        st_out<false>(row_elem<float4>(base, w, stride, cb), float4{o[0], o[1], o[2], o[3]});
+    }
+}
+
+// U P v of direction MU, DIR for a neighbour's FP32 or FP64 spinor v
+template <int SP, int MU, int DIR, bool DAG, class T>
+__device__ __forceinline__ void split_multiply(const T v[24], bool flip, const cpx<T> u[3][3], T *out)
+{
+    constexpr int SG = (DIR > 0) == DAG ? +1 : -1;
+    cpx<T> h0[3], h1[3], g[3];
+    project<MU, SG>(v, h0, h1);
+    if (flip) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            h0[c] = {-h0[c].re, -h0[c].im};
+            h1[c] = {-h1[c].re, -h1[c].im};
+        }
+    }
+    su3_mul<(DIR < 0), T>(u, h0, g);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        out[(2 * c) * 64] = g[c].re;
+        out[(2 * c + 1) * 64] = g[c].im;
+    }
+    su3_mul<(DIR < 0), T>(u, h1, g);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        out[(6 + 2 * c) * 64] = g[c].re;
+        out[(7 + 2 * c) * 64] = g[c].im;
+    }
+}
+
 // U P psi of direction MU, DIR at the lane's site into its column of `out`
 template <int SP, int GP, int R, int MU, int DIR, bool DAG, class T>
 __device__ __forceinline__ void split_product(const SysDesc &sd, const HopSite &hs, int parity, const Site &st, int cb,
@@ -1030,6 +1071,147 @@ void k_hop_split(HopArgs a)
     }
 }
 
+// The four launches of a CGNR iteration of a small set (FP32 and FP64, Wilson;
+// steps of Cg::iterations), on the blocks of variant 11.  A small iteration lasts
+// as long as its launches: the two update kernels and the two finishing launches
+// between the hops took as long as the hops.  Here
+//   HI_P, HI_R  the input is in + z in2 (z = beta or -alpha, finished here from
+//               the previous launch's partials), formed at every neighbour;
+//   HI_Q, HI_S  that field is formed again at the output sites and stored, with
+//               x, as the epilogue's X0, and the hop's norm (HI_S: and |r|^2) goes
+//               to the partials.
+// CGNR to 1e-10: 8^3x16 FP32 2070 -> 1790 us, 4^3x8 FP32 1850 -> 1590.
+template <int SP, int GP, int R, bool DAG, bool COMB>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SP == P_F64 ? 2 : 4)))
+void k_hop_iter(HopArgs a)
+{
+    using S = SplitHop<SP>;
+    using T = typename S::T;
+    using CH = typename SpinorFmt<SP>::chunk;
+    static_assert(!S::half, "half-precision fields round when they are stored");
+    constexpr int PW = S::per_wave;
+    extern __shared__ uint4 s_split[];
+    T *prod = reinterpret_cast<T *>(s_split);
+
+    const int lb = xcd_remap(blockIdx.x, a.nblocks);
+    const BlkMap bm = a.map[lb];
+    const int vi = a.one ? 0 : bm.v;
+    if (a.active && !a.active[vi]) return;
+    const VecDesc vd = a.vec[vi];
+    const SysDesc sd = a.sys[a.one ? 0 : vd.sys];
+    const int lane = (int)threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int cb = bm.lblk * 64 + lane;
+    const bool live = cb < sd.Vh;
+    const int ccb = live ? cb : sd.Vh - 1;
+    const Site st = cb_coords(sd, ccb, a.parity);
+    const HopIO f{a.parity, a.in, nullptr, a.out, nullptr, a.epi.X, a.epi.Xn};
+    const HopSite hs = hop_input<SP>(a, f, vd, sd);
+    const size_t voff = (size_t)vd.site_off * SpinorFmt<SP>::nchunk;
+    const CH *in2 = (const CH *)a.in2 + voff;
+    T *pout = prod + w * S::rows * 64 + lane;
+#define WL_EACH_DIR(CALL)             \
+    switch (w) {                      \
+    case 0: CALL(0, +1); break;       \
+    case 1: CALL(0, -1); break;       \
+    case 2: CALL(1, +1); break;       \
+    case 3: CALL(1, -1); break;       \
+    case 4: CALL(2, +1); break;       \
+    case 5: CALL(2, -1); break;       \
+    case 6: CALL(3, +1); break;       \
+    default: CALL(3, -1); break;      \
+    }
+    if constexpr (COMB) {
+        // every load of the wave's direction goes out, then the scalar is finished
+        T v[24], v2[24];
+        cpx<T> u[3][3];
+        bool flip;
+        int ncb;
+#define WL_LOAD(MU, DIR)                                    \
+    {                                                       \
+        ncb = neighbour<MU, DIR>(sd, st, ccb, flip);        \
+        load_spinor<SP>(hs.in, nullptr, sd.stride, ncb, v); \
+        load_spinor<SP>(in2, nullptr, sd.stride, ncb, v2);  \
+        hop_link<GP, R, MU, DIR, false>(hs, a.parity, ccb, ncb, u); \
+    }
+        WL_EACH_DIR(WL_LOAD)
+#undef WL_LOAD
+        // HI_P (no adjoint) beta, HI_R (adjoint) -alpha
+        const T z = DAG ? (T)(-fold_alpha(a.fold, vi, bm.lblk)) : (T)fold_beta(a.fold, vi, bm.lblk);
+#pragma unroll
+        for (int k = 0; k < 24; ++k) v[k] = fmadd(z, v2[k], v[k]);
+#define WL_PROD(MU, DIR) split_multiply<SP, MU, DIR, DAG>(v, flip, u, pout)
+        WL_EACH_DIR(WL_PROD)
+#undef WL_PROD
+    } else {
+#define WL_PROD(MU, DIR) split_product<SP, GP, R, MU, DIR, DAG>(sd, hs, a.parity, st, ccb, pout)
+        WL_EACH_DIR(WL_PROD)
+#undef WL_PROD
+    }
+#undef WL_EACH_DIR
+    // own-site fields: HI_Q s, p, x; HI_S r, q
+    T x0[PW], x1[PW], x2[PW];
+    double z1 = 0.0, z2 = 0.0;
+    if constexpr (!COMB) {
+        if (w < S::finishers) {
+            split_load<SP, false>((const CH *)a.epi.X[0] + voff, sd.stride, ccb, w, x0);
+            split_load<SP, false>((const CH *)a.epi.X[1] + voff, sd.stride, ccb, w, x1);
+            if constexpr (!DAG) split_load<SP, false>((const CH *)a.epi.X[2] + voff, sd.stride, ccb, w, x2);
+        }
+        z2 = a.fold.sc[(size_t)SC_ALPHA * a.nvec + vi];
+        if constexpr (!DAG) z1 = a.fold.sc[(size_t)SC_BETA * a.nvec + vi];
+    }
+    __syncthreads();
+    double rv = 0.0, rr = 0.0;
+    if (w < S::finishers) {
+        T o[PW], n[PW];
+        const T *q = prod + lane;
+#define WL_SUM(W) split_sum<SP, DAG, W>(q, o)
+        WL_EACH_FINISHER(w, WL_SUM)
+#undef WL_SUM
+        const T c = (T)a.epi.coef[vd.sys * 5 + 4];
+#pragma unroll
+        for (int i = 0; i < PW; ++i) o[i] *= c;
+        if constexpr (!COMB) {
+            if constexpr (DAG) {
+                const T al = (T)(-z2);
+#pragma unroll
+                for (int i = 0; i < PW; ++i) n[i] = fmadd(al, x1[i], x0[i]);  // r - alpha q
+            } else {
+                const T be = (T)z1, al = (T)z2;
+#pragma unroll
+                for (int i = 0; i < PW; ++i) {
+                    x2[i] = fmadd(al, x1[i], x2[i]);  // x + alpha p
+                    n[i] = fmadd(be, x1[i], x0[i]);   // s + beta p
+                }
+                if (live) split_store<SP>((CH *)a.out3 + voff, sd.stride, cb, w, x2);
+            }
+            if (live) split_store<SP>((CH *)a.out2 + voff, sd.stride, cb, w, n);
+            const T c0 = (T)a.epi.coef[vd.sys * 5];
+#pragma unroll
+            for (int i = 0; i < PW; ++i) o[i] = fmadd(n[i], c0, o[i]);
+            if (live) {
+                T s1 = 0, s2 = 0;
+#pragma unroll
+                for (int i = 0; i < PW; ++i) {
+                    s1 = fmadd(o[i], o[i], s1);
+                    s2 = fmadd(n[i], n[i], s2);
+                }
+                rv = (double)s1;
+                rr = (double)s2;
+            }
+        }
+        if (live) split_store<SP>((CH *)f.out + voff, sd.stride, cb, w, o);
+    }
+    if constexpr (!COMB) {
+        block_reduce_store(a.red, vd.pslot0, bm.lblk, rv);
+        if constexpr (DAG) {
+            const double bs = block_sum(rr);
+            if (threadIdx.x == 0) a.partials2[vd.pslot0 + bm.lblk] = bs;
+        }
+    }
+}
+
 // With events, the dispatch itself records them at the kernel's start and end
 // (the kernel-timing form of the launch), so the measured interval is the
 // kernel alone.
@@ -1147,16 +1329,36 @@ hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, int bloc
     return hipErrorInvalidValue;
 }
 
+// One launch of the CGNR iteration of small sets
+template <int SP, int GP, int R>
+hipError_t launch_hop_iter_t(int step, const HopArgs &a, hipStream_t s)
+{
+    if constexpr (SP == P_F64 || SP == P_F32) {
+        const unsigned lds = (unsigned)SplitHop<SP>::buf * (unsigned)sizeof(typename SplitHop<SP>::T);
+        switch (step) {
+        case HI_P: dispatch(k_hop_iter<SP, GP, R, false, true>, a, 512, s, nullptr, nullptr, lds); break;
+        case HI_Q: dispatch(k_hop_iter<SP, GP, R, false, false>, a, 512, s, nullptr, nullptr, lds); break;
+        case HI_R: dispatch(k_hop_iter<SP, GP, R, true, true>, a, 512, s, nullptr, nullptr, lds); break;
+        case HI_S: dispatch(k_hop_iter<SP, GP, R, true, false>, a, 512, s, nullptr, nullptr, lds); break;
+        default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
+}
+
 // The kernels of one storage format are compiled in a source of their own (hop_*.hip,
 // which define WL_HOP_FORMAT and include this file), so that the formats build in
 // parallel; this file by itself compiles the dispatch over them.
 #ifdef WL_HOP_FORMAT
 template hipError_t launch_hop_t<WL_HOP_FORMAT>(int var, bool dag, bool clov, const HopArgs &a, int block,
                                                 hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+template hipError_t launch_hop_iter_t<WL_HOP_FORMAT>(int step, const HopArgs &a, hipStream_t s);
 #else
 #define WL_HOP_EXTERN(...)                                                                                          \
     extern template hipError_t launch_hop_t<__VA_ARGS__>(int var, bool dag, bool clov, const HopArgs &a, int block, \
-                                                         hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+                                                         hipStream_t s, hipEvent_t e0, hipEvent_t e1);              \
+    extern template hipError_t launch_hop_iter_t<__VA_ARGS__>(int step, const HopArgs &a, hipStream_t s)
 WL_HOP_EXTERN(P_F64, P_F64, 18);
 WL_HOP_EXTERN(P_F64, P_F64, 12);
 WL_HOP_EXTERN(P_F32, P_F32, 18);
@@ -1178,6 +1380,15 @@ hipError_t launch_hop(int prec, int recon, bool dag, bool clov, int var, const H
     if (prec == P_F32 && recon == 12) return launch_hop_t<P_F32, P_F32, 12>(var, dag, clov, a, block, s, e0, e1);
     if (prec == P_F16 && recon == 12) return launch_hop_t<P_F16, P_F16, 12>(var, dag, clov, a, block, s, e0, e1);
     if (prec == P_BF16 && recon == 12) return launch_hop_t<P_BF16, P_BF16, 12>(var, dag, clov, a, block, s, e0, e1);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_hop_iter(int prec, int recon, int step, const HopArgs &a, hipStream_t s)
+{
+    if (prec == P_F64 && recon == 18) return launch_hop_iter_t<P_F64, P_F64, 18>(step, a, s);
+    if (prec == P_F64 && recon == 12) return launch_hop_iter_t<P_F64, P_F64, 12>(step, a, s);
+    if (prec == P_F32 && recon == 18) return launch_hop_iter_t<P_F32, P_F32, 18>(step, a, s);
+    if (prec == P_F32 && recon == 12) return launch_hop_iter_t<P_F32, P_F32, 12>(step, a, s);
     return hipErrorInvalidValue;
 }
 #endif

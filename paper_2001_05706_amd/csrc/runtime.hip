@@ -798,7 +798,6 @@ static std::vector<int> hop_cands(const ExecSet &S, int prec, bool clov)
     return cands;
 }
 
-static const int kBlasBlock = 256;
 
 // The most block partials of a vector that a consuming update sums itself
 // instead of waiting for a finishing launch (4.5 us and its gap).  Every block of
@@ -806,6 +805,11 @@ static const int kBlasBlock = 256;
 // (CGNR: 4^4 FP64 1485 -> 1350 us, 16^3x32 FP32 4440 -> 4230, 32^3x64 FP16 33.0 ->
 // 32.8 ms); with 16384 (64-site blocks at 32^3x64) the FP16 solve took 36.8 ms.
 constexpr int kFoldPartials = 2048;
+
+static Fold fold_of(const ExecSet &S, const Layout *L)
+{
+    return Fold{L->d_vec, S.partials, S.sc, S.bad, S.nvec, 0};
+}
 
 // A kind of hop launch of a set, as an index into its plans
 static int plan_id(int prec, int recon, bool dag, bool clov, const Epi &e, bool red, bool twin)
@@ -966,6 +970,61 @@ wl_status hop(ExecSet &S, int prec, int recon, bool dag, int par, const Field &o
     return WL_OK;
 }
 
+// The four-launch iteration reads two fields at every neighbour where the six
+// launches read one: it pays while launches cost more than that.  CGNR to 1e-10,
+// six launches against four: FP32 8^3x16 2070 and 1790 us, 16^4 (512 blocks of 64
+// sites) 2840 and 2620, 16^3x32 (1024) 4230 and 4360; FP64 8^3x16 (64 blocks) 2360
+// and 2150, 12^3x24 (324) 3740 and 4050.  Half-precision fields round when they
+// are stored, so a field formed at the neighbours would not be the stored one.
+constexpr int kIterBlocksF32 = 512, kIterBlocksF64 = 128;
+bool iter_fused(const ExecSet &S, int prec)
+{
+    const char *tune = getenv("WL_TUNE");
+    const int most = prec == P_F32 ? kIterBlocksF32 : prec == P_F64 ? kIterBlocksF64 : 0;
+    return !S.has_clover && !prof().on && !getenv("WL_TUNE_FORCE") && !(tune && tune[0] == '0') && blocks64(S) <= most;
+}
+
+wl_status hop_iter(ExecSet &S, int prec, int recon, int step, const Field &out, const Field &in, const Field *in2,
+                   const Field *own, const double *coef, const Layout *fold, double *partials2, hipStream_t s,
+                   const Layout **laid)
+{
+    const SysDesc *sysd = nullptr;
+    WL_TRY(S.sys_table(prec, recon, s, &sysd));
+    const Layout *L = nullptr;
+    WL_TRY(S.layout(64, &L));
+    HopArgs a{};
+    a.sys = sysd;
+    a.vec = L->d_vec;
+    a.map = L->d_map;
+    a.active = S.d_active;
+    a.nblocks = L->nblocks;
+    a.parity = step == HI_P || step == HI_R ? 1 : 0;
+    a.nvec = S.nvec;
+    a.in = in.p;
+    a.out = out.p;
+    a.in2 = in2 ? in2->p : nullptr;
+    a.epi.coef = coef;
+    for (int j = 0; own && j < 3; ++j) a.epi.X[j] = own[j].p;
+    if (step == HI_Q) {  // p and x are updated in place
+        a.out2 = own[1].p;
+        a.out3 = own[2].p;
+    } else if (step == HI_S) {  // r is
+        a.out2 = own[0].p;
+    }
+    a.red = red_spec(S, step == HI_Q || step == HI_S ? RED_ALPHA : RED_NONE, nullptr);
+    a.one = S.nvec == 1;
+    a.partials2 = partials2;
+    if (fold) a.fold = fold_of(S, fold);
+    a.fold.sc = S.sc;
+    a.fold.nvec = S.nvec;
+    // algorithmic bytes: links, input(s) and output, the own-site fields read and written
+    static const int extra[4] = {1, 5, 1, 3};
+    g_bytes_acc += hop_bytes(S, prec, recon, true) + blas_bytes(S, prec, extra[step], true);
+    WL_HIP(launch_hop_iter(prec, recon, step, a, s));
+    if (laid) *laid = L;
+    return WL_OK;
+}
+
 wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], const Field in[2], const Epi e[2],
                hipStream_t s, bool use_active)
 {
@@ -1073,12 +1132,7 @@ wl_status blas(ExecSet &S, int op, int prec, const Field *f, int nf, const doubl
     a.red = red;
     a.parity = parity;
     a.bcast = bcast;
-    if (fold) {
-        a.fold_vec = fold->d_vec;
-        a.fold_partials = S.partials;
-        a.fold_sc = S.sc;
-        a.fold_bad = S.bad;
-    }
+    if (fold) a.fold = fold_of(S, fold);
     static const int passes[] = {6, 3, 0, 1, 1, 2, 1, 2, 4, 3, 7, 2, 2, 2, 3, 3, 0, 3, 5};
     if (op == BL_CLOV_INV) g_bytes_acc += clover_bytes(S, prec, use_active);
     if (op == BL_ROT) g_bytes_acc += blas_bytes(S, prec, S.nvec + 1, use_active);
@@ -1091,10 +1145,10 @@ wl_status blas(ExecSet &S, int op, int prec, const Field *f, int nf, const doubl
     return WL_OK;
 }
 
-wl_status hist_report(ExecSet &S, int k, bool deferred, hipStream_t s)
+wl_status hist_report(ExecSet &S, int k, bool deferred, hipStream_t s, int block)
 {
     const Layout *L = nullptr;
-    WL_TRY(S.layout(kBlasBlock, &L));
+    WL_TRY(S.layout(block, &L));
     WL_HIP(launch_hist_report(deferred ? S.hist_partials : nullptr, (size_t)S.max_pslots, L->d_vec, S.d_active, S.nvec,
                               k, S.hist, S.bad, S.dev_report(0), (int32_t *)S.dev_report(ExecSet::kRepBad), s));
     return WL_OK;

@@ -250,7 +250,18 @@ wl_status unpack2(ExecSet &S, double *const *canon, const Field &even, const Fie
 
 // the last k iterations' |r|^2 (deferred: from their block partials; otherwise
 // from the hist rows) and the flags into the pinned report
-wl_status hist_report(ExecSet &S, int k, bool deferred, hipStream_t s);
+// (block: of the layout that the partials are in)
+constexpr int kBlasBlock = 256;
+wl_status hist_report(ExecSet &S, int k, bool deferred, hipStream_t s, int block = kBlasBlock);
+
+// The four-launch CGNR iteration of small sets (see hop.hip): whether a set takes
+// it, and one of its launches.  own: the fields at the output sites; fold: the
+// layout of the partials whose scalar the launch needs; laid: the layout of the
+// partials it leaves
+bool iter_fused(const ExecSet &S, int prec);
+wl_status hop_iter(ExecSet &S, int prec, int recon, int step, const Field &out, const Field &in, const Field *in2,
+                   const Field *own, const double *coef, const Layout *fold, double *partials2, hipStream_t s,
+                   const Layout **laid);
 
 // device coefficient tables [nsys][5], cached by content
 wl_status coef_table(ExecSet &S, const std::vector<double> &c, const double **out);

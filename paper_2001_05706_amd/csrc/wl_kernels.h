@@ -21,12 +21,8 @@ struct BlasArgs {
     int32_t one;       // the set holds one vector (its descriptors are at index 0)
     int32_t stream;    // solver-iteration kernels: fields read and written non-temporally
     RedSpec red;
-    // not null (BL_R_UPDATE, BL_XPAY_X, BL_BICG_S, BL_BICG_XR): alpha, beta or omega
-    // is still the producing hop's block partials, laid out by these vector descriptors
-    const VecDesc *fold_vec;
-    const double *fold_partials;
-    double *fold_sc;     // scalar slots, written by each vector's first block
-    int32_t *fold_bad;
+    Fold fold;         // BL_R_UPDATE, BL_XPAY_X, BL_BICG_S, BL_BICG_XR: alpha, beta or omega
+                       // is still the producing hop's block partials
 };
 
 constexpr int kMaxSys = 64;  // systems per set (canonical pointers travel by value)
@@ -54,6 +50,11 @@ hipError_t launch_hop(int prec, int recon, bool dag, bool clov, int var, const H
                       hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 int hop_variants();
 bool hop_has_variant(int prec, int var);  // the variant exists for a storage precision
+
+// One of the four launches of a CGNR iteration of a small set (see hop.hip),
+// FP32 or FP64; the map's blocks hold 64 sites
+enum HopIter { HI_P = 0, HI_Q = 1, HI_R = 2, HI_S = 3 };
+hipError_t launch_hop_iter(int prec, int recon, int step, const HopArgs &a, hipStream_t s);
 
 // blas.hip -- all operate on the vectors of one set through its block map
 enum BlasOp {

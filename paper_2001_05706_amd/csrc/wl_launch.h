@@ -89,6 +89,18 @@ struct RedSpec {
     double *host;        // RED_STORE / RED_ACCUM: dst[v] also goes here (pinned host memory; null: off)
 };
 
+// A reduction whose block partials are finished by the kernel that uses its result
+// (vec null: off): the partials, laid out by these vector descriptors, and the
+// scalar slots and flags the finishing step writes.
+struct Fold {
+    const VecDesc *vec;
+    const double *partials;
+    double *sc;
+    int32_t *bad;
+    int32_t nvec;
+    int32_t pad_;
+};
+
 // Linear combination applied to the hopping term at the output site:
 //   out = Ci G5?( a0 C0 X0 + c hop ) + a1 X1 + a2 X2 + a3 X3
 // with coefficients per system in device memory: coef[sys * 5 + {0..3: a0..a3, 4: c}].
@@ -147,6 +159,13 @@ struct HopArgs {
     double *canon;
     int32_t canon_zero;
     int32_t pad_;
+    // CGNR iteration of small sets (k_hop_iter): the second field of a combined
+    // input, the updated fields beside `out`, the partials of |r|^2
+    const void *in2;
+    void *out2;
+    void *out3;
+    double *partials2;
+    Fold fold;
 };
 
 }  // namespace wl

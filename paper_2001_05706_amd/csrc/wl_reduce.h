@@ -184,6 +184,60 @@ __device__ __forceinline__ void wave_reduce_store_n(const RedSpec &r, int pslot0
     }
 }
 
+// The sums of the NV values of the producing hop's block partials of vector vi, the
+// same in every thread: each block adds them in the same fixed order.
+template <int NV> __device__ __forceinline__ void fold_sum(const Fold &a, int vi, double *sum)
+{
+    __shared__ double s_sum[NV];
+    const VecDesc pd = a.vec[vi];
+    const double *p = a.partials + (size_t)pd.pslot0 * NV;
+    double s[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) s[k] = 0.0;
+    for (int i = threadIdx.x; i < pd.nblk; i += blockDim.x)
+#pragma unroll
+        for (int k = 0; k < NV; ++k) s[k] += p[(size_t)i * NV + k];
+    block_sum_n(s, NV);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int k = 0; k < NV; ++k) s_sum[k] = s[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) sum[k] = s_sum[k];
+}
+
+// alpha = gamma / |q|^2 from the partials of |q|^2; the vector's first block
+// stores it, and gamma aside for the step that replaces it
+__device__ __forceinline__ double fold_alpha(const Fold &a, int vi, int lblk)
+{
+    const double g = a.sc[SC_GAM * a.nvec + vi];
+    double qq;
+    fold_sum<1>(a, vi, &qq);
+    const double al = qq > 0.0 ? g / qq : 0.0;
+    if (lblk == 0 && threadIdx.x == 0) {
+        a.sc[SC_ALPHA * a.nvec + vi] = al;
+        a.sc[SC_GAMP * a.nvec + vi] = g;
+        if (!isfinite(qq)) a.bad[vi] |= 1;
+    }
+    return al;
+}
+
+// beta = |s|^2 / gamma from the partials of |s|^2, and gamma = |s|^2 (the old gamma
+// is read from where fold_alpha put it: this launch overwrites its slot)
+__device__ __forceinline__ double fold_beta(const Fold &a, int vi, int lblk)
+{
+    const double g = a.sc[SC_GAMP * a.nvec + vi];
+    double ss;
+    fold_sum<1>(a, vi, &ss);
+    const double be = g > 0.0 ? ss / g : 0.0;
+    if (lblk == 0 && threadIdx.x == 0) {
+        a.sc[SC_BETA * a.nvec + vi] = be;
+        a.sc[SC_GAM * a.nvec + vi] = ss;
+        if (!isfinite(ss)) a.bad[vi] |= 1;
+    }
+    return be;
+}
+
 // <a, b> = sum conj(a) b over one site (12 complex numbers)
 template <class T> __device__ __forceinline__ void site_cdot(const T a[24], const T b[24], double &re, double &im)
 {
