@@ -69,8 +69,9 @@ template <int SP, int VAR> struct HopVar {
 constexpr int kHopVariants = 12;
 
 // What a hop's epilogue ends in, one instantiation each: EP_CANON stores the
-// canonical FP64 field instead of the packed one.
-enum { EP_WILSON = 0, EP_CLOVER = 1, EP_CANON = 2, EP_CLOVER_CANON = 3 };
+// canonical FP64 field instead of the packed one.  (Bit 2, variant 11 only: the
+// input and X0 are read from the canonical field too.)
+enum { EP_WILSON = 0, EP_CLOVER = 1, EP_CANON = 2, EP_CLOVER_CANON = 3, EP_DIRECT = 4 };
 
 // The fields of the output parity a block computes: the launch's first slot,
 // or for the odd blocks of a twin launch the second one.  X and Xn point into
@@ -599,8 +600,8 @@ void k_hop_pencil(HopArgs a)
     double rv[3] = {0.0, 0.0, 0.0};
     hop_epilogue<SP, false, CANON>(a, f, vd, sd, cb, acc, rv);
     if constexpr (CANON) {
-        // (behind the rows of the block's waves, which other waves may still read)
-        store_canon<float>(a, f, vd, sd, cb, true, acc, rows + nw * P::bytes + w * kStageBytes<float>);
+        __syncthreads();  // the waves' stages take the place of the rows
+        store_canon<float>(a, f, vd, sd, cb, true, acc, rows + w * kStageBytes<float>);
     }
     if (a.red.kind != RED_NONE) block_reduce_store_n(a.red, vd.pslot0, bm.lblk, rv);
     if (a.stamps) {
@@ -692,17 +693,58 @@ __device__ __forceinline__ void split_multiply(const T v[24], bool flip, const c
     }
 }
 
-// U P psi of direction MU, DIR at the lane's site into its column of `out`
-template <int SP, int GP, int R, int MU, int DIR, bool DAG, class T>
+// Site `lex` of the canonical field `base`, rounded as packing it rounds: FP64 and
+// FP32 the 24 reals; FP16/BF16 the packed words and the norm
+template <int SP>
+__device__ __forceinline__ void canon_site(const double *base, int lex, typename SplitHop<SP>::T v[24], uint32_t q[12],
+                                           float *norm)
+{
+    const WL_G double *p = (const WL_G double *)base + (size_t)lex * 24;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        const nt_d2u w = *(const WL_G nt_d2u *)(p + 2 * k);
+        v[2 * k] = (typename SplitHop<SP>::T)w.x;
+        v[2 * k + 1] = (typename SplitHop<SP>::T)w.y;
+    }
+    if constexpr (SplitHop<SP>::half) quantize_site<SP>(v, q, norm);
+}
+
+// U P psi of direction MU, DIR at the lane's site into its column of `out`; DIRECT:
+// psi is the vector of the canonical field that starts at `canon`
+template <int SP, int GP, int R, int MU, int DIR, bool DAG, bool DIRECT = false, class T>
 __device__ __forceinline__ void split_product(const SysDesc &sd, const HopSite &hs, int parity, const Site &st, int cb,
-                                              T *out)
+                                              T *out, const double *canon = nullptr)
 {
     constexpr int SG = (DIR > 0) == DAG ? +1 : -1;
     bool flip;
     const int ncb = neighbour<MU, DIR>(sd, st, cb, flip);
     cpx<T> h0[3], h1[3], g[3], u[3][3];
-    const T f = project_neighbour<SP, MU, SG>(hs, ncb, flip, h0, h1);
-    hop_link<GP, R, MU, DIR, false>(hs, parity, cb, ncb, u);
+    T f;
+    if constexpr (DIRECT) {
+        // the neighbour is the site of its pair with the x of its own parity
+        T v[24];
+        uint32_t q[12];
+        float m;
+        canon_site<SP>(canon, 2 * ncb + ((MU == 0 ? st.x + 1 : st.x) & 1), v, q, &m);
+        hop_link<GP, R, MU, DIR, false>(hs, parity, cb, ncb, u);
+        if constexpr (SplitHop<SP>::half) {
+            project_half<SP, MU, SG>(q, h0, h1);
+            f = (flip ? -m : m) * (T)hs.scale;
+        } else {
+            project<MU, SG>(v, h0, h1);
+            if (flip) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    h0[c] = {-h0[c].re, -h0[c].im};
+                    h1[c] = {-h1[c].re, -h1[c].im};
+                }
+            }
+            f = 1;
+        }
+    } else {
+        f = project_neighbour<SP, MU, SG>(hs, ncb, flip, h0, h1);
+        hop_link<GP, R, MU, DIR, false>(hs, parity, cb, ncb, u);
+    }
     su3_mul<(DIR < 0), T>(u, h0, g);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -822,6 +864,18 @@ __device__ __forceinline__ void split_clover(const void *base, int stride, int c
     }
 }
 
+#define WL_EACH_DIR(w, CALL)          \
+    switch (w) {                      \
+    case 0: CALL(0, +1); break;       \
+    case 1: CALL(0, -1); break;       \
+    case 2: CALL(1, +1); break;       \
+    case 3: CALL(1, -1); break;       \
+    case 4: CALL(2, +1); break;       \
+    case 5: CALL(2, -1); break;       \
+    case 6: CALL(3, +1); break;       \
+    default: CALL(3, -1); break;      \
+    }
+
 #define WL_EACH_FINISHER(w, CALL)                                          \
     switch (w) {                                                           \
     case 0: CALL(0); break;                                                \
@@ -833,10 +887,10 @@ __device__ __forceinline__ void split_clover(const void *base, int stride, int c
     }
 
 template <int SP, int GP, int R, bool DAG, int EP>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(EP & EP_CLOVER ? 4 : SplitHop<SP>::waves)))
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(EP & EP_DIRECT ? 2 : EP & EP_CLOVER ? 4 : SplitHop<SP>::waves)))
 void k_hop_split(HopArgs a)
 {
-    constexpr bool CLOV = EP == EP_CLOVER || EP == EP_CLOVER_CANON, CANON = EP >= EP_CANON;
+    constexpr bool CLOV = (EP & 1) != 0, CANON = (EP & 2) != 0, DIRECT = (EP & EP_DIRECT) != 0;
     using S = SplitHop<SP>;
     using T = typename S::T;
     using CH = typename SpinorFmt<SP>::chunk;
@@ -861,18 +915,12 @@ void k_hop_split(HopArgs a)
     const int ccb = live ? cb : sd.Vh - 1;  // lanes past the end repeat the last site and store nothing
     const Site st = cb_coords(sd, ccb, f.parity);
     const HopSite hs = hop_input<SP>(a, f, vd, sd);
+    const double *canon = DIRECT ? a.canon_in + (size_t)vd.rhs * (size_t)sd.Vh * 48 : nullptr;
     {
         T *out = prod + w * S::rows * 64 + lane;
-        switch (w) {
-        case 0: split_product<SP, GP, R, 0, +1, DAG>(sd, hs, f.parity, st, ccb, out); break;
-        case 1: split_product<SP, GP, R, 0, -1, DAG>(sd, hs, f.parity, st, ccb, out); break;
-        case 2: split_product<SP, GP, R, 1, +1, DAG>(sd, hs, f.parity, st, ccb, out); break;
-        case 3: split_product<SP, GP, R, 1, -1, DAG>(sd, hs, f.parity, st, ccb, out); break;
-        case 4: split_product<SP, GP, R, 2, +1, DAG>(sd, hs, f.parity, st, ccb, out); break;
-        case 5: split_product<SP, GP, R, 2, -1, DAG>(sd, hs, f.parity, st, ccb, out); break;
-        case 6: split_product<SP, GP, R, 3, +1, DAG>(sd, hs, f.parity, st, ccb, out); break;
-        default: split_product<SP, GP, R, 3, -1, DAG>(sd, hs, f.parity, st, ccb, out); break;
-        }
+#define WL_PROD(MU, DIR) split_product<SP, GP, R, MU, DIR, DAG, DIRECT>(sd, hs, f.parity, st, ccb, out, canon)
+        WL_EACH_DIR(w, WL_PROD)
+#undef WL_PROD
     }
     const double *cf = a.epi.coef + vd.sys * 5;
     const int nx = a.epi.nx;
@@ -890,9 +938,31 @@ void k_hop_split(HopArgs a)
     };
     // the first two epilogue operands are on their way while the products meet
     T x0[PW], x1[PW], n0 = 1, n1 = 1;
+    // (DIRECT: X0 is the input at the output site, and there is no other)
+    T xc[24];
     if (w < S::finishers) {
-        if (nx >= 1) load(0, x0, n0);
-        if (nx >= 2) load(1, x1, n1);
+        if constexpr (DIRECT) {
+            if (nx >= 1) {
+                uint32_t q[12];
+                float m = 1.f;
+                canon_site<SP>(canon, 2 * ccb + (st.x & 1), xc, q, &m);
+                n0 = (T)m;
+                if constexpr (S::half) {
+#pragma unroll
+                    for (int k = 0; k < 12; ++k) {
+                        xc[2 * k] = half_part<SP, 0>(q[k]);
+                        xc[2 * k + 1] = half_part<SP, 1>(q[k]);
+                    }
+                }
+#define WL_OWN(W)                                     \
+    _Pragma("unroll") for (int i = 0; i < PW; ++i) x0[i] = xc[W * PW + i]
+                WL_EACH_FINISHER(w, WL_OWN)
+#undef WL_OWN
+            }
+        } else {
+            if (nx >= 1) load(0, x0, n0);
+            if (nx >= 2) load(1, x1, n1);
+        }
     }
     __syncthreads();
     double rv[3] = {0.0, 0.0, 0.0};
@@ -914,10 +984,15 @@ void k_hop_split(HopArgs a)
                 const void *cl = clover_parity<CP>(sd.clov, f.parity, sd.stride);
                 const float *xn = f.Xn[0] ? f.Xn[0] + vd.site_off : nullptr;
                 T xs[24], y[PW];
-#define WL_CLOV(W)                                                                       \
-    {                                                                                    \
-        split_load_blocks<SP, W>((const CH *)f.X[0] + voff, xn, sd.stride, ccb, xs);     \
-        split_clover<SP, W>(cl, sd.stride, ccb, xs, y);                                  \
+                if constexpr (DIRECT) {
+#pragma unroll
+                    for (int k = 0; k < 24; ++k) xs[k] = S::half ? xc[k] * n0 : xc[k];
+                }
+#define WL_CLOV(W)                                                                           \
+    {                                                                                        \
+        if constexpr (!DIRECT)                                                               \
+            split_load_blocks<SP, W>((const CH *)f.X[0] + voff, xn, sd.stride, ccb, xs);     \
+        split_clover<SP, W>(cl, sd.stride, ccb, xs, y);                                      \
     }
                 WL_EACH_FINISHER(w, WL_CLOV)
 #undef WL_CLOV
@@ -1110,17 +1185,6 @@ void k_hop_iter(HopArgs a)
     const size_t voff = (size_t)vd.site_off * SpinorFmt<SP>::nchunk;
     const CH *in2 = (const CH *)a.in2 + voff;
     T *pout = prod + w * S::rows * 64 + lane;
-#define WL_EACH_DIR(CALL)             \
-    switch (w) {                      \
-    case 0: CALL(0, +1); break;       \
-    case 1: CALL(0, -1); break;       \
-    case 2: CALL(1, +1); break;       \
-    case 3: CALL(1, -1); break;       \
-    case 4: CALL(2, +1); break;       \
-    case 5: CALL(2, -1); break;       \
-    case 6: CALL(3, +1); break;       \
-    default: CALL(3, -1); break;      \
-    }
     if constexpr (COMB) {
         // every load of the wave's direction goes out, then the scalar is finished
         T v[24], v2[24];
@@ -1134,21 +1198,20 @@ void k_hop_iter(HopArgs a)
         load_spinor<SP>(in2, nullptr, sd.stride, ncb, v2);  \
         hop_link<GP, R, MU, DIR, false>(hs, a.parity, ccb, ncb, u); \
     }
-        WL_EACH_DIR(WL_LOAD)
+        WL_EACH_DIR(w, WL_LOAD)
 #undef WL_LOAD
         // HI_P (no adjoint) beta, HI_R (adjoint) -alpha
         const T z = DAG ? (T)(-fold_alpha(a.fold, vi, bm.lblk)) : (T)fold_beta(a.fold, vi, bm.lblk);
 #pragma unroll
         for (int k = 0; k < 24; ++k) v[k] = fmadd(z, v2[k], v[k]);
 #define WL_PROD(MU, DIR) split_multiply<SP, MU, DIR, DAG>(v, flip, u, pout)
-        WL_EACH_DIR(WL_PROD)
+        WL_EACH_DIR(w, WL_PROD)
 #undef WL_PROD
     } else {
 #define WL_PROD(MU, DIR) split_product<SP, GP, R, MU, DIR, DAG>(sd, hs, a.parity, st, ccb, pout)
-        WL_EACH_DIR(WL_PROD)
+        WL_EACH_DIR(w, WL_PROD)
 #undef WL_PROD
     }
-#undef WL_EACH_DIR
     // own-site fields: HI_Q s, p, x; HI_S r, q
     T x0[PW], x1[PW], x2[PW];
     double z1 = 0.0, z2 = 0.0;
@@ -1266,7 +1329,7 @@ static hipError_t launch_hop_lds(bool dag, const HopArgs &a, int block, hipStrea
 template <int SP, int GP, int R, int VAR, bool CANON>
 static hipError_t launch_hop_pencil(bool dag, const HopArgs &a, int block, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
-    const unsigned lds = (unsigned)(block / 64) * (PencilRow<SP>::bytes + (CANON ? kStageBytes<float> : 0));
+    const unsigned lds = (unsigned)(block / 64) * std::max(PencilRow<SP>::bytes, CANON ? kStageBytes<float> : 0);
     if (dag)
         dispatch(k_hop_pencil<SP, GP, R, true, VAR, CANON>, a, block, s, e0, e1, lds);
     else
@@ -1290,6 +1353,7 @@ template <int SP, int GP, int R>
 hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, int block, hipStream_t s,
                                hipEvent_t e0, hipEvent_t e1)
 {
+    if (a.canon_in && var != 11) return hipErrorInvalidValue;
     switch (var) {
     case 0: return launch_hop_v<SP, GP, R, 0>(dag, clov, a, block, s, e0, e1);
     case 1: return launch_hop_v<SP, GP, R, 1>(dag, clov, a, block, s, e0, e1);
@@ -1308,6 +1372,10 @@ hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, int bloc
         return hipErrorInvalidValue;
     case 11:
         if (block != 64) return hipErrorInvalidValue;  // 64 sites on 512 threads
+        if (a.canon_in && (!a.canon || a.epi.nx > 1)) return hipErrorInvalidValue;
+        if (a.canon_in)
+            return clov ? launch_hop_split<SP, GP, R, EP_CLOVER_CANON | EP_DIRECT>(dag, a, s, e0, e1)
+                        : launch_hop_split<SP, GP, R, EP_CANON | EP_DIRECT>(dag, a, s, e0, e1);
         if (clov)
             return a.canon ? launch_hop_split<SP, GP, R, EP_CLOVER_CANON>(dag, a, s, e0, e1)
                            : launch_hop_split<SP, GP, R, EP_CLOVER>(dag, a, s, e0, e1);

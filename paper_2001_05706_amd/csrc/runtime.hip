@@ -832,6 +832,24 @@ static int blocks64(const ExecSet &S)
     return n;
 }
 
+static bool split_untimed(const ExecSet &S)
+{
+    const char *tune = getenv("WL_TUNE");
+    return !getenv("WL_TUNE_FORCE") && !(tune && tune[0] == '0') && blocks64(S) <= kSplitBlocks;
+}
+
+// A D-slash call on up to this many blocks (of both parities when both are
+// computed) reads its canonical input in the hop, one launch instead of two.  The
+// neighbours' 192-byte sites are read 16 bytes a lane, which costs more than the
+// pack launch once the blocks no longer run side by side: FP32 8^3x16 hop 7.5 us
+// against 12.5, 12x14x10x18 operator (474 blocks) 10.7 against 15.3, FP64 12.5
+// against 14.8, clover 14.1 against 16.5; 16^4 operator (1024) 18.6 against 18.4.
+constexpr int kDirectBlocks = 512;
+static bool dslash_direct(const ExecSet &S, int parities)
+{
+    return split_untimed(S) && parities * blocks64(S) <= kDirectBlocks;
+}
+
 // The launch configuration and block map of one kind of hop: from the set's plans
 // once the tuner has settled it (a D-slash call or a solver's eager launch spent
 // more host time on the tuner's key, the candidate list and the lookups than on
@@ -849,8 +867,7 @@ static wl_status hop_plan(ExecSet &S, int id, ExecSet::HopPlan *pl, hipStream_t 
         }
     }
     bool settled = false;
-    const char *tune = getenv("WL_TUNE");
-    if (!pinned && !(tune && tune[0] == '0') && blocks64(S) <= kSplitBlocks) {
+    if (split_untimed(S)) {
         pl->cfg = cfg_make(11, 64, 4);
         WL_TRY(hop_layout(S, pl->cfg, &pl->L));
         S.plans[id] = *pl;
@@ -899,6 +916,7 @@ wl_status hop(ExecSet &S, int prec, int recon, bool dag, int par, const Field &o
         a.one = S.nvec == 1;
         a.stream = S.stream_fields(prec);
         a.canon = e.canon;
+        a.canon_in = e.canon_in;
         a.canon_zero = e.canon_zero;
         return a;
     };
@@ -1062,6 +1080,7 @@ wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], co
         a.epi.clov = clov ? e[0].clov : 0;
         a.epi.coef = e[0].coef;
         a.canon = e[0].canon;
+        a.canon_in = e[0].canon_in;
         for (int j = 0; j < 4; ++j) {
             a.epi.X[j] = e[p].X[j].p;
             a.epi.Xn[j] = e[p].X[j].n;
@@ -1112,8 +1131,10 @@ wl_status blas(ExecSet &S, int op, int prec, const Field *f, int nf, const doubl
         WL_TRY(S.sys_table(prec, 0, s, &sysd));  // geometry and clover term, no links
     else
         WL_TRY(S.sys_table(-1, 0, s, &sysd));  // geometry only
+    // in memory order: these kernels share nothing between blocks, and in the hops'
+    // order of columns the 32^3x64 FP16 updates take 52 and 33 us instead of 49 and 30
     const Layout *L = nullptr;
-    WL_TRY(S.layout(kBlasBlock, &L));
+    WL_TRY(S.layout(kBlasBlock, &L, kLinearCol));
     BlasArgs a{};
     a.sys = sysd;
     a.vec = L->d_vec;
@@ -1344,22 +1365,30 @@ wl_status wilson_dslash(wl_gauge U, const double *in, double *out, int32_t nrhs,
     Epi e[2];
     e[0].canon = e[1].canon = out;
     if (parity >= 0) {
-        WL_TRY(S->field("dsl_in" + std::to_string(1 - parity), prec, &fi[1 - parity]));
         WL_TRY(coef_table(*S, {0, 0, 0, 0, 1.0}, &e[0].coef));
         e[0].canon_zero = 1;
-        WL_TRY(pack(*S, cin, 1 - parity, fi[1 - parity], s));
+        if (dslash_direct(*S, 1)) {
+            e[0].canon_in = in;
+        } else {
+            WL_TRY(S->field("dsl_in" + std::to_string(1 - parity), prec, &fi[1 - parity]));
+            WL_TRY(pack(*S, cin, 1 - parity, fi[1 - parity], s));
+        }
         WL_TRY(hop(*S, prec, recon, dagger, parity, Field(), fi[1 - parity], e[0], no_red(), s, false));
         return WL_OK;
     }
     const double *coef = nullptr;
     WL_TRY(coef_table(*S, {1.0, 0, 0, 0, -kappa}, &coef));
+    const bool direct = dslash_direct(*S, 2);
     for (int p = 0; p < 2; ++p) {
-        WL_TRY(S->field("dsl_in" + std::to_string(p), prec, &fi[p]));
+        if (!direct) WL_TRY(S->field("dsl_in" + std::to_string(p), prec, &fi[p]));
         e[p].coef = coef;
         e[p].nx = 1;
         e[p].X[0] = fi[p];
     }
-    WL_TRY(pack2(*S, cin, fi[0], fi[1], s));
+    if (direct)
+        e[0].canon_in = e[1].canon_in = in;
+    else
+        WL_TRY(pack2(*S, cin, fi[0], fi[1], s));
     const Field fo[2];
     return hop2(*S, prec, recon, dagger, fo, fi, e, s, false);
 }
@@ -1394,15 +1423,19 @@ wl_status wilson_clover_dslash(wl_gauge U, const double *in, double *out, int32_
     Epi e[2];
     const double *coef = nullptr;
     WL_TRY(coef_table(*S, {1.0, 0, 0, 0, -kappa}, &coef));
+    const bool direct = dslash_direct(*S, 2);
     for (int p = 0; p < 2; ++p) {
-        WL_TRY(S->field("dsl_in" + std::to_string(p), prec, &fi[p]));
+        if (!direct) WL_TRY(S->field("dsl_in" + std::to_string(p), prec, &fi[p]));
         e[p].coef = coef;
         e[p].nx = 1;
         e[p].clov = EPI_CLOV_X0;
         e[p].X[0] = fi[p];
         e[p].canon = out;
     }
-    WL_TRY(pack2(*S, cin, fi[0], fi[1], s));
+    if (direct)
+        e[0].canon_in = e[1].canon_in = in;
+    else
+        WL_TRY(pack2(*S, cin, fi[0], fi[1], s));
     const Field fo[2];
     return hop2(*S, prec, recon, dagger, fo, fi, e, s, false);
 }

@@ -116,6 +116,7 @@ struct SysEntry {
 // above kPencilLayout pencil layouts
 constexpr int kPairLayout = 1 << 16;
 constexpr int kPencilLayout = 1 << 17;
+constexpr int kLinearCol = 4095;  // column height that leaves the blocks of a time group in memory order
 
 // A set of systems (each a gauge handle with nrhs right-hand sides) whose
 // vectors share every field and every launch.
@@ -225,6 +226,9 @@ struct Epi {
     // reduction); canon_zero: with zeros on the other parity
     double *canon = nullptr;
     int canon_zero = 0;
+    // and its input, with X0 (nx <= 1), comes from this one instead of `in` and X
+    // (sets that take variant 11 without tuning)
+    const double *canon_in = nullptr;
 };
 
 RedSpec no_red();

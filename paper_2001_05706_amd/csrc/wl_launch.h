@@ -157,6 +157,8 @@ struct HopArgs {
     // this canonical FP64 field of all vectors instead of `out`; canon_zero:
     // with zeros on the other parity
     double *canon;
+    const double *canon_in;  // variant 11 with canon: the input (and X0, the input at the output
+                             // site) is read from this canonical field instead of `in`
     int32_t canon_zero;
     int32_t pad_;
     // CGNR iteration of small sets (k_hop_iter): the second field of a combined

@@ -1,6 +1,9 @@
 """Canonical <-> packed conversion at the edges of its blocks (128 and 256
 checkerboard sites) and from pointers aligned to a double only.
 
+Small lattices read and write the canonical field in the hop itself; WL_TUNE=0
+takes them through the packed fields as larger ones are, so both routes are run.
+
 With parity -1 and kappa = 0 a D-slash call packs its input and unpacks the
 epilogue's 1 * x + 0, so the output is the storage rounding of the input, bit for
 bit (the host model of tests/gpu_util.py; exact in FP64).  A single-parity hop
@@ -22,8 +25,10 @@ SHAPES = [(2, 2, 2, 2), (2, 6, 2, 10), (4, 4, 4, 4), (2, 2, 6, 22), (4, 4, 4, 8)
 @pytest.mark.parametrize("L", SHAPES)
 @pytest.mark.parametrize("prec", ["f64", "f32", "f16", "bf16"])
 @pytest.mark.parametrize("offset", [0, 1])
-def test_round_trip(L, prec, offset):
+@pytest.mark.parametrize("tune", ["1", "0"])
+def test_round_trip(L, prec, offset, tune, monkeypatch):
     w = need_gpu()
+    monkeypatch.setenv("WL_TUNE", tune)
     import torch
 
     nrhs = 2
@@ -46,8 +51,10 @@ def test_round_trip(L, prec, offset):
 
 @pytest.mark.parametrize("L", SHAPES)
 @pytest.mark.parametrize("parity", [0, 1])
-def test_other_parity_is_zero(L, parity):
+@pytest.mark.parametrize("tune", ["1", "0"])
+def test_other_parity_is_zero(L, parity, tune, monkeypatch):
     w = need_gpu()
+    monkeypatch.setenv("WL_TUNE", tune)
     import torch
 
     U, psi = li.haar_links(L, 13), li.gaussian_spinor(L, 14, nrhs=3)
@@ -59,3 +66,26 @@ def test_other_parity_is_zero(L, parity):
     assert np.array_equal(got == 0, ref == 0)
     assert np.abs(got - ref).max() <= 1e-13 * np.abs(ref).max() * 8  # 8 directions of FP64 products
     g.close()
+
+
+@pytest.mark.parametrize("L", [(2, 2, 2, 2), (4, 4, 4, 2), (2, 10, 6, 14)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16", "bf16"])
+@pytest.mark.parametrize("csw", [None, 1.3])
+def test_routes_agree(L, prec, csw, monkeypatch):
+    """The canonical field read in the hop and the packed one give the same bits."""
+    w = need_gpu()
+    U, psi = li.haar_links(L, 15), li.gaussian_spinor(L, 16, nrhs=3)
+    psi[1] = 0
+    for parity, dagger in [(-1, 0), (-1, 1)] + ([(0, 1), (1, 0)] if csw is None else []):
+        out = []
+        for tune in ("1", "0"):
+            monkeypatch.setenv("WL_TUNE", tune)
+            g = w.Gauge(L, to_dev(U))
+            o = to_dev(np.full_like(psi, np.nan))
+            if csw is None:
+                w.wilson_dslash(g, to_dev(psi), o, 3, 0.13, parity, dagger, prec, 12)
+            else:
+                w.wilson_clover_dslash(g, to_dev(psi), o, 3, 0.13, csw, dagger, prec, 12)
+            out.append(o.cpu().numpy())
+            g.close()
+        assert np.array_equal(out[0], out[1]), (parity, dagger)
