@@ -53,7 +53,8 @@
  *   WL_TUNE=0            no autotuning: every hop runs 256-thread blocks
  *   WL_TUNE_FORCE=v:b[:c] pin the hop launches whose tuner candidates hold
  *                        variant v with block size b (column height c, 4 by
- *                        default) -- for tests of each variant
+ *                        default, plus 256 n for time groups 2^n times as
+ *                        long) -- for tests of each variant
  *   WL_GRAPHS=0          solver iteration chunks launched kernel by kernel
  *                        instead of replayed from captured HIP graphs
  *   WL_STREAM_FIELDS=0|1 force the solver kernels' non-temporal field access

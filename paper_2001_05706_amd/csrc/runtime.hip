@@ -505,21 +505,24 @@ wl_status ExecSet::layout(int B, const Layout **out, int col)
         }
         // logical order (system, site block, rhs): right-hand sides sharing links
         // are adjacent.  Site blocks go in time groups of ceil(Lt / 8) slices
-        // (one XCD's contiguous share of the launch), and inside a group in
-        // columns of `col` z-planes swept along t, so a neighbour in t is `col`
-        // planes away in launch order rather than a whole slice: the spinors a
-        // wave's neighbours need are still in the XCD's L2 when they are read.
-        // (The tuner chooses the column height with the launch variant.)
+        // (one XCD's contiguous share of the launch) times a power of two, and
+        // inside a group in columns of z-planes swept along t, so a neighbour in t
+        // is a column's height of planes away in launch order rather than a whole
+        // slice: the spinors a wave's neighbours need are still in the XCD's L2
+        // when they are read.  A larger group gives an XCD fewer, longer columns:
+        // less of what it reads lies in another XCD's slices, more in the
+        // neighbouring columns.  (The tuner chooses both with the launch variant.)
         // (a pencil block b covers slices t0 .. t0 + T - 1 at the 64 positions
         // of chunk b % (slice / 64), t0 = T (b / (slice / 64)), and is ordered by
         // its first slice)
         const SysDesc &g = systems[i].g->geom;
-        const int plane = g.Lxh * g.L[1], slice = plane * g.L[2], tg = (g.L[3] + 7) / 8;
+        const int plane = g.Lxh * g.L[1], slice = plane * g.L[2];
+        const int tg = ((g.L[3] + 7) / 8) << col_groups(col), cz = col_height(col);
         std::vector<std::array<int, 5>> key(nb);
         for (int b = 0; b < nb; ++b) {
             const int cb0 = pencil ? (b / (slice / 64)) * T * slice + (b % (slice / 64)) * 64 : b * sites;
             const int t = cb0 / slice, z = (cb0 % slice) / plane;
-            key[b] = {t / tg, z / col, t, z, b};
+            key[b] = {t / tg, z / cz, t, z, b};
         }
         std::sort(key.begin(), key.end());
         for (int k = 0; k < nb; ++k)
@@ -717,14 +720,17 @@ int cfg_col(int c) { return (c >> 16) & 4095; }
 constexpr int kCfgSplit = 1 << 29;
 
 // Candidate configurations: every variant x block size x column height of 4 or
-// 16 z-planes (taller columns sweep longer runs of consecutive sites: FP64
+// 16 z-planes, for several right-hand sides also columns of 4 along all of t and
+// of 6 along half of it (12-RHS D-slash at 24^3x48, FP16 184 -> 165 us, FP32
+// 306 -> 292; with one vector within 1-2%) (taller columns sweep longer runs of consecutive sites: FP64
 // 32^3 x 64 D-slash 291 -> 278 us, FP32 116 -> 114 us; at 24^3 x 48 the height
 // changes little)
-std::vector<int> hop_candidates(int prec)
+std::vector<int> hop_candidates(int prec, bool many)
 {
     const bool half = prec == P_F16 || prec == P_BF16;
-    std::vector<int> c;
-    for (int col : {4, 16})
+    std::vector<int> c, cols = {4, 16};
+    if (many) cols.insert(cols.end(), {col_make(4, 3), col_make(6, 2)});
+    for (int col : cols)
         for (int v = 0; v < hop_variants(); ++v) {
             if (!hop_has_variant(prec, v)) continue;
             if ((v == 4 || v == 5) && !half) continue;  // four directions in flight: half precision only
@@ -768,6 +774,14 @@ static wl_status hop_layout(ExecSet &S, int cfg, const Layout **L)
     return S.layout(key, L, cfg_col(cfg));
 }
 
+// blocks of 64 sites of a set's vectors
+static int blocks64(const ExecSet &S)
+{
+    int n = 0;
+    for (auto &e : S.systems) n += e.nrhs * ((e.g->geom.Vh + 63) / 64);
+    return n;
+}
+
 // The candidates of a hop launch on this set: variants 6-8 need several
 // right-hand sides in a system, the clover epilogue the registers of the
 // two-direction variants (0 and 3) without LDS staging, and pencil blocks
@@ -783,10 +797,14 @@ static std::vector<int> hop_cands(const ExecSet &S, int prec, bool clov)
         slices64 = slices64 && (g.Lxh * g.L[1] * g.L[2]) % 64 == 0;
     }
     std::vector<int> cands;
-    for (int c : hop_candidates(prec)) {
+    for (int c : hop_candidates(prec, max_nrhs > 1)) {
         const int v = cfg_var(c);
         if (clov && (v == 1 || v == 2 || (v >= 8 && v <= 10))) continue;
         if (max_nrhs < 2 && v >= 6 && v <= 8) continue;
+        // large sets of several right-hand sides: variant 11 wins the tuner's repeated
+        // launches and loses among the others (12-RHS sign function at 16^3x32, 12288
+        // blocks of 64 sites, 61.8 ms with it and 60.5 without)
+        if (v == 11 && max_nrhs > 1 && blocks64(S) > 2048) continue;
         if (v == 9 || v == 10) {
             bool ok = slices64;
             for (auto &e : S.systems) ok = ok && e.g->geom.L[3] % (cfg_block(c) / 64) == 0;
@@ -825,13 +843,6 @@ static int plan_id(int prec, int recon, bool dag, bool clov, const Epi &e, bool 
 // at 1024 blocks FP64 already loses, 14.9 against 13.7).  Timed from the host,
 // launches this short cannot be told apart.
 constexpr int kSplitBlocks = 512;
-static int blocks64(const ExecSet &S)
-{
-    int n = 0;
-    for (auto &e : S.systems) n += e.nrhs * ((e.g->geom.Vh + 63) / 64);
-    return n;
-}
-
 static bool split_untimed(const ExecSet &S)
 {
     const char *tune = getenv("WL_TUNE");

@@ -116,7 +116,12 @@ struct SysEntry {
 // above kPencilLayout pencil layouts
 constexpr int kPairLayout = 1 << 16;
 constexpr int kPencilLayout = 1 << 17;
-constexpr int kLinearCol = 4095;  // column height that leaves the blocks of a time group in memory order
+// The block order of a layout: columns of `height` z-planes (1 to 255), in time
+// groups of ceil(Lt / 8) << groups slices
+constexpr int col_make(int height, int groups) { return height | groups << 8; }
+constexpr int col_height(int col) { return col & 255 ? col & 255 : 255; }
+constexpr int col_groups(int col) { return (col >> 8) & 3; }
+constexpr int kLinearCol = 255;  // leaves the blocks of a time group in memory order
 
 // A set of systems (each a gauge handle with nrhs right-hand sides) whose
 // vectors share every field and every launch.
@@ -155,7 +160,7 @@ public:
     // B - kPencilLayout consecutive time slices (every system's slices must
     // hold a multiple of 64 sites and its time extent be a multiple of the
     // slice count; WL_ERR_ARG otherwise)
-    // col: z-planes per column of the block order (see the definition)
+    // col: the block order (col_make; see the definition)
     wl_status layout(int B, const Layout **out, int col = 4);
     int32_t *d_active = nullptr;
     std::vector<int32_t> h_active;
@@ -316,7 +321,7 @@ int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream
                 const std::function<hipError_t(int)> &run, bool *settled = nullptr);
 bool capturing(hipStream_t s);
 std::string hop_key(const ExecSet &S, int prec, int recon, bool dag);
-std::vector<int> hop_candidates(int prec);
+std::vector<int> hop_candidates(int prec, bool many);  // many: several right-hand sides
 int cfg_make(int var, int block, int col);  // hop launch configuration: variant, block size, column height
 int cfg_var(int c);
 int cfg_block(int c);
