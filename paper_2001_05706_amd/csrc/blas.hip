@@ -548,11 +548,12 @@ __global__ __launch_bounds__(1024) void k_red_finalize(RedSpec r, const VecDesc 
 // The report of a chunk of k iterations: one block per vector, one wave per
 // history row, which sums the row's partials of the vector in a fixed order (or
 // takes the finished value).  The rows and the vector's flag go straight to
-// pinned host memory: a copy queued behind the chunk cost the solver a further
-// launch and its gap before the host could decide.
+// pinned host memory, where the host watches the vector's count: a copy queued
+// behind the chunk, or an event, cost the solver a further launch or packet and
+// its gap before the host could decide.
 __global__ __launch_bounds__(1024) void k_hist_report(const double *partials, size_t row, const VecDesc *vec,
                                                       const int32_t *active, int nvec, int k, const double *hist,
-                                                      int32_t *bad, double *host_hist, int32_t *host_bad)
+                                                      int32_t *bad, double *host_hist, int32_t *host_bad, Report rep)
 {
     const int v = blockIdx.x;
     if (active && !active[v]) return;
@@ -585,20 +586,22 @@ __global__ __launch_bounds__(1024) void k_hist_report(const double *partials, si
             if (!isfinite(s)) atomicOr(&s_bad, 1);
         }
     }
+    __threadfence_system();
     __syncthreads();
     if (threadIdx.x == 0) {
         bad[v] = s_bad;
         host_bad[v] = s_bad;
+        announce(rep, v);
     }
 }
 
 hipError_t launch_hist_report(const double *partials, size_t row, const VecDesc *vec, const int32_t *active, int nvec,
                               int k, const double *hist, int32_t *bad, double *host_hist, int32_t *host_bad,
-                              hipStream_t s)
+                              const Report &rep, hipStream_t s)
 {
     const int waves = k < 16 ? k : 16;
     hipLaunchKernelGGL(k_hist_report, dim3(nvec), dim3(64 * waves), 0, s, partials, row, vec, active, nvec, k, hist,
-                       bad, host_hist, host_bad);
+                       bad, host_hist, host_bad, rep);
     return hipGetLastError();
 }
 

@@ -33,6 +33,7 @@
 // M; <rhat, r> and |r|^2 in the x/r update.  A reliable update replaces r and
 // recomputes rho; a breakdown (zero <rhat, v> or |t|) or a non-finite value
 // restarts from the FP64 accumulator with rhat = r.
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -148,6 +149,7 @@ struct Cg {
         WL_TRY(hop(S, P_F64, recon, false, 1, t64, xh, first(c_plain), no_red(), s, use_active));
         RedSpec rr = red_spec(S, RED_STORE, S.scal(SC_RR));
         rr.host = S.dev_report(ExecSet::kRepRR);
+        rr.rep = S.rep(1);
         WL_TRY(hop(S, P_F64, recon, false, 0, rh, t64, second(c_res, 2, xh, bp), rr, s, use_active));
         return WL_OK;
     }
@@ -350,6 +352,16 @@ struct Cg {
     }
 };
 
+static double wait_limit()
+{
+    static const double limit = [] {
+        const char *v = getenv("WL_WAIT_TIMEOUT_S");
+        const double t = v ? atof(v) : 0.0;
+        return t > 0.0 ? t : 600.0;
+    }();
+    return limit;
+}
+
 // Waits for event e by polling it: the readbacks inside the solve loop are a
 // few hundred bytes that the host needs at once, and a blocking wait adds the
 // thread's wake-up to every one of them.  After the first few thousand polls
@@ -358,11 +370,7 @@ struct Cg {
 // no longer answers.
 static wl_status wait_spin(hipEvent_t e)
 {
-    static const double limit = [] {
-        const char *v = getenv("WL_WAIT_TIMEOUT_S");
-        const double t = v ? atof(v) : 0.0;
-        return t > 0.0 ? t : 600.0;
-    }();
+    const double limit = wait_limit();
     const auto t0 = std::chrono::steady_clock::now();
     for (long n = 0;; ++n) {
         const hipError_t q = hipEventQuery(e);
@@ -375,6 +383,32 @@ static wl_status wait_spin(hipEvent_t e)
                 return set_error(WL_ERR_HIP, "a readback did not complete within %.0f s", limit);
         }
     }
+}
+
+// Waits for the next report (which = 0: of a chunk, 1: of |r|^2) of every vector of
+// `need`, with the limits of wait_spin.
+static wl_status wait_report(ExecSet &S, int which, const std::vector<int> &need, hipStream_t s)
+{
+    const auto t0 = std::chrono::steady_clock::now();
+    const volatile unsigned long long *c = S.counts(which);
+    long n = 0;
+    for (int v = 0; v < S.nvec; ++v) {
+        if (!need[v]) continue;
+        const unsigned long long want = ++S.seen[which][v];
+        while (c[v] < want) {
+            if (++n < 65536) continue;
+            std::this_thread::yield();
+            if ((n & 1023) != 0) continue;
+            // a stream that has ended or failed without the report never makes it
+            const hipError_t q = hipStreamQuery(s);
+            if (q != hipErrorNotReady && c[v] < want)
+                return set_error(WL_ERR_HIP, "waiting for a report: %s", hipGetErrorString(q));
+            if (std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > wait_limit())
+                return set_error(WL_ERR_HIP, "a report did not arrive within %.0f s", wait_limit());
+        }
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+    return WL_OK;
 }
 
 static double now_s()
@@ -449,6 +483,8 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
         WL_HIP(hipEventRecord(S.rr_ev, s));
         WL_TRY(wait_spin(S.rr_ev));
     }
+    // everything queued so far has ended: the counts stand still
+    for (int w = 0; w < 2; ++w) S.seen[w].assign(S.counts(w), S.counts(w) + nv);
     std::vector<double> eta_n(nv), rmax(nv), last_true(nv), target(nv);
     std::vector<int> iters(nv, 0), updates(nv, 0), conv(nv, 0), done(nv, 0), stall(nv, 0);
     std::vector<int> zero_src(nv, 0);
@@ -526,6 +562,7 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                 Field ac[2] = {cg.xh, cg.xl};
                 WL_TRY(blas(S, BL_ACCUM, cg.sloppy, ac, 2, nullptr, no_red(), s));
                 WL_TRY(cg.residual64());
+                for (int v = 0; v < nv; ++v) S.seen[1][v] += S.h_active[v] != 0;  // a report nobody waits for
             }
             const int next = cg.sloppy == P_F32 ? P_F64 : P_F32;
             Field p_old = cg.p, v_old = cg.q, rhat_old = cg.rhat;
@@ -551,8 +588,9 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
             cg.use_graphs = graphs;
             first = false;
             // the chunk ended with the k history rows and the flags in the report
-            WL_HIP(hipEventRecord(S.rr_ev, s));
-            WL_TRY(wait_spin(S.rr_ev));
+            std::vector<int> need(nv);
+            for (int v = 0; v < nv; ++v) need[v] = !done[v];
+            WL_TRY(wait_report(S, 0, need, s));
             if (trace) {
                 double sc[ExecSet::SC_N];
                 for (int j = 0; j < ExecSet::SC_N; ++j)
@@ -625,7 +663,6 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                 for (int v = 0; v < nv; ++v) S.h_active[v] = upd[v];
                 WL_TRY(S.upload_active(s));
                 WL_TRY(cg.residual64());
-                WL_HIP(hipEventRecord(S.rr_ev, s));
                 // every updated vector that goes on (continued or restarted) needs
                 // r from the new residual, and for CGNR s = M^+ r: they are queued
                 // before the host has read it, so the GPU works while the host
@@ -634,7 +671,7 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                 WL_TRY(cg.refresh_s());
                 const double spec_bytes = g_bytes_acc - b0;
                 bool pre = true;
-                WL_TRY(wait_spin(S.rr_ev));
+                WL_TRY(wait_report(S, 1, upd, s));
                 bool stalled = false;
                 for (int v = 0; v < nv; ++v) {
                     if (!upd[v]) continue;
@@ -735,6 +772,7 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                red_spec(S, RED_STORE, S.scal(SC_RR)), s));
     RedSpec tr = red_spec(S, RED_ACCUM, S.scal(SC_RR));
     tr.host = S.dev_report(ExecSet::kRepRR);
+    tr.rep = S.rep(1);
     WL_TRY(hop(S, P_F64, 18, false, 1, cg.t64, cg.xh, cg.epi(cg.c_tres, 2, cg.xo, cg.eta_o, EPI_CLOV_X0), tr, s));
     WL_TRY(unpack2(S, x, cg.xh, cg.xo, s));
     WL_HIP(hipEventRecord(S.rr_ev, s));

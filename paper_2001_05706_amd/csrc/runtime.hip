@@ -357,6 +357,7 @@ ExecSet::~ExecSet()
     (void)hipFree(sc);
     (void)hipFree(hist);
     (void)hipFree(bad);
+    (void)hipFree(d_counts);
     (void)hipFree(hist_partials);
     (void)hipHostFree(h_report);
     (void)hipHostFree(h_masks);
@@ -401,11 +402,14 @@ wl_status ExecSet::init()
     WL_ALLOC(hist, sizeof(double) * kHist * nvec);
     WL_ALLOC(bad, sizeof(int32_t) * nvec);
     WL_ALLOC(hist_partials, sizeof(double) * kHist * max_pslots);
-    if (hipHostMalloc((void **)&h_report, sizeof(double) * (kRepBad + 1) * nvec, 0) != hipSuccess) {
+    WL_ALLOC(d_counts, 2 * sizeof(unsigned long long) * nvec);
+    WL_HIP(hipMemset(d_counts, 0, 2 * sizeof(unsigned long long) * nvec));
+    if (hipHostMalloc((void **)&h_report, sizeof(double) * kRepRows * nvec, 0) != hipSuccess) {
         (void)hipGetLastError();
         h_report = nullptr;
         return set_error(WL_ERR_NOMEM, "cannot allocate pinned host memory");
     }
+    std::fill(h_report, h_report + (size_t)kRepRows * nvec, 0.0);
     WL_HIP(hipHostGetDevicePointer((void **)&d_report, h_report, 0));
     if (hipHostMalloc((void **)&h_masks, sizeof(int32_t) * kMaskRing * nvec, 0) != hipSuccess) {
         (void)hipGetLastError();
@@ -1182,7 +1186,8 @@ wl_status hist_report(ExecSet &S, int k, bool deferred, hipStream_t s, int block
     const Layout *L = nullptr;
     WL_TRY(S.layout(block, &L));
     WL_HIP(launch_hist_report(deferred ? S.hist_partials : nullptr, (size_t)S.max_pslots, L->d_vec, S.d_active, S.nvec,
-                              k, S.hist, S.bad, S.dev_report(0), (int32_t *)S.dev_report(ExecSet::kRepBad), s));
+                              k, S.hist, S.bad, S.dev_report(0), (int32_t *)S.dev_report(ExecSet::kRepBad),
+                              S.rep(0), s));
     return WL_OK;
 }
 

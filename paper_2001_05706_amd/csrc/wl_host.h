@@ -188,6 +188,19 @@ public:
     double *h_report = nullptr, *d_report = nullptr;
     static constexpr int kHist = 64;
     static constexpr int kRepRR = kHist, kRepSc = kHist + 1, kRepBad = kHist + 1 + SC_COUNT;  // rows of nvec doubles
+    // counts of the reports made (see Report): of a chunk's history, of |r|^2
+    static constexpr int kRepCountHist = kRepBad + 1, kRepCountRR = kRepBad + 2, kRepRows = kRepBad + 3;
+    unsigned long long *d_counts = nullptr;                   // [2][nvec]
+    std::vector<unsigned long long> seen[2];                  // the reports the host has taken or knows of
+    Report rep(int which)
+    {
+        return Report{d_counts + (size_t)which * nvec,
+                      (unsigned long long *)dev_report(which == 0 ? kRepCountHist : kRepCountRR)};
+    }
+    const unsigned long long *counts(int which)
+    {
+        return (const unsigned long long *)report(which == 0 ? kRepCountHist : kRepCountRR);
+    }
     double *report(int row) { return h_report + (size_t)row * nvec; }
     double *dev_report(int row) { return d_report + (size_t)row * nvec; }
 

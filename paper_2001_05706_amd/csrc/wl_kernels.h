@@ -90,7 +90,7 @@ hipError_t launch_red_finalize(const RedSpec &r, const VecDesc *vec, const int32
 // summed; null: the rows are in hist[j * nvec + v]
 hipError_t launch_hist_report(const double *partials, size_t row, const VecDesc *vec, const int32_t *active, int nvec,
                               int k, const double *hist, int32_t *bad, double *host_hist, int32_t *host_bad,
-                              hipStream_t s);
+                              const Report &rep, hipStream_t s);
 // y (prec_dst) = x (prec_src), f = {y, x}
 hipError_t launch_convert(int prec_dst, int prec_src, const BlasArgs &a, int block, hipStream_t s);
 

@@ -74,6 +74,14 @@ enum RedMode {
     RM_OUT_X0 = 2,  // <out, X0>, |out|^2                   (3 values)
 };
 
+// How a kernel tells the waiting host that a vector's values are in pinned
+// memory: it raises the vector's count on the device and stores it to the host's
+// copy behind the values.
+struct Report {
+    unsigned long long *count;  // device, per vector
+    unsigned long long *host;   // pinned, per vector
+};
+
 struct RedSpec {
     int32_t kind;
     int32_t nv;          // values per site (1..3)
@@ -86,7 +94,8 @@ struct RedSpec {
     int32_t defer;       // 1: leave the partials for a later finishing pass (no finishing launch);
                          // 2 (a hop's alpha or beta): leave them for the consuming update if they are few
     int32_t pad_;
-    double *host;        // RED_STORE / RED_ACCUM: dst[v] also goes here (pinned host memory; null: off)
+    double *host;        // RED_STORE / RED_ACCUM: dst[v] also goes here (pinned host memory; null: off),
+    Report rep;          // announced here
 };
 
 // A reduction whose block partials are finished by the kernel that uses its result

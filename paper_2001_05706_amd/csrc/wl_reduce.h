@@ -60,6 +60,15 @@ __device__ __forceinline__ void block_sum_n(double *v, int nv)
         for (int k = 0; k < nv; ++k) v[k] = wave_sum(l < (int)(blockDim.x >> 6) ? lds[k][l] : 0.0);
 }
 
+// the values this thread (and, through a barrier behind their own system fences,
+// other threads) wrote to pinned memory are there before the count
+__device__ __forceinline__ void announce(const Report &r, int v)
+{
+    const unsigned long long n = r.count[v] + 1;
+    r.count[v] = n;
+    __hip_atomic_store(r.host + v, n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The values the finishing step of a reduction reads besides the sums
 // (loaded before the sums are complete, so that their latency overlaps).
 struct RedIn {
@@ -150,7 +159,10 @@ __device__ __forceinline__ void red_finalize(const RedSpec &r, int v, const doub
     }
 #undef WL_SC
     if (!finite && r.bad) r.bad[v] |= 1;
-    if (r.host) r.host[v] = r.dst[v];
+    if (r.host) {
+        r.host[v] = r.dst[v];
+        announce(r.rep, v);
+    }
 }
 
 // Called by every thread of the block (uniform control flow) with its own
