@@ -144,13 +144,17 @@ struct Cg {
     // rh = b' - M xh in FP64 with |rh|^2 into SC_RR and the host's report.  Links are rebuilt from 12
     // reals when the caller chose recon-12 (exact to rounding for SU(3)); the
     // final true residual always uses all 18.
-    wl_status residual64(bool use_active = true)
+    // sloppy_r: it is rounded to the sloppy residual rl instead of being stored in rh.
+    wl_status residual64(bool sloppy_r = false)
     {
+        const bool use_active = true;
         WL_TRY(hop(S, P_F64, recon, false, 1, t64, xh, first(c_plain), no_red(), s, use_active));
         RedSpec rr = red_spec(S, RED_STORE, S.scal(SC_RR));
         rr.host = S.dev_report(ExecSet::kRepRR);
         rr.rep = S.rep(1);
-        WL_TRY(hop(S, P_F64, recon, false, 0, rh, t64, second(c_res, 2, xh, bp), rr, s, use_active));
+        Epi e = second(c_res, 2, xh, bp);
+        if (sloppy_r && sloppy != P_F64) e.lo = rl;
+        WL_TRY(hop(S, P_F64, recon, false, 0, rh, t64, e, rr, s, use_active));
         return WL_OK;
     }
 
@@ -247,11 +251,11 @@ struct Cg {
     }
 
     // The part of a refresh common to continued and restarted vectors, for the
-    // vectors of the current mask: r = rh in the sloppy precision; CGNR also
-    // s = M^+ r, gamma = |s|^2
-    wl_status refresh_s()
+    // vectors of the current mask: r = rh in the sloppy precision (have_r: it is
+    // there already); CGNR also s = M^+ r, gamma = |s|^2
+    wl_status refresh_s(bool have_r = false)
     {
-        WL_TRY(convert(S, rl, rh, s));
+        if (!have_r) WL_TRY(convert(S, rl, rh, s));
         if (method != M_CGNR) return WL_OK;
         return apply_M(sloppy, recon, true, sv, rl, tl, red_spec(S, RED_GAMMA, nullptr));
     }
@@ -561,9 +565,15 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                 WL_TRY(S.upload_active(s));
                 Field ac[2] = {cg.xh, cg.xl};
                 WL_TRY(blas(S, BL_ACCUM, cg.sloppy, ac, 2, nullptr, no_red(), s));
-                WL_TRY(cg.residual64());
-                for (int v = 0; v < nv; ++v) S.seen[1][v] += S.h_active[v] != 0;  // a report nobody waits for
             }
+            // the residual of every vector that goes on, in FP64 (an update leaves it
+            // in the sloppy precision only)
+            for (int v = 0; v < nv; ++v) {
+                S.h_active[v] = !done[v];
+                S.seen[1][v] += S.h_active[v] != 0;  // a report nobody waits for
+            }
+            WL_TRY(S.upload_active(s));
+            WL_TRY(cg.residual64());
             const int next = cg.sloppy == P_F32 ? P_F64 : P_F32;
             Field p_old = cg.p, v_old = cg.q, rhat_old = cg.rhat;
             cg.sloppy = next;
@@ -662,13 +672,13 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                 }
                 for (int v = 0; v < nv; ++v) S.h_active[v] = upd[v];
                 WL_TRY(S.upload_active(s));
-                WL_TRY(cg.residual64());
+                WL_TRY(cg.residual64(true));
                 // every updated vector that goes on (continued or restarted) needs
                 // r from the new residual, and for CGNR s = M^+ r: they are queued
                 // before the host has read it, so the GPU works while the host
                 // decides (wasted only for vectors found converged)
                 const double b0 = g_bytes_acc;
-                WL_TRY(cg.refresh_s());
+                WL_TRY(cg.refresh_s(cg.sloppy != P_F64));
                 const double spec_bytes = g_bytes_acc - b0;
                 bool pre = true;
                 WL_TRY(wait_report(S, 1, upd, s));

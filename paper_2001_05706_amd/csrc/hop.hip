@@ -105,6 +105,26 @@ __device__ __forceinline__ void load_x(const HopArgs &a, const HopIO &f, int j, 
         load_spinor_raw<SP, false>(base, nrm, sd.stride, cb, x, nx);
 }
 
+// An FP64 result rounded to the field a.lo (as k_convert rounds; plain stores: the
+// next hop reads it).  A reliable update's residual is only wanted in the sloppy
+// precision: storing it in FP64 and converting it cost the 32^3x64 FP16 solve a
+// further 460 MB and a launch, about 90 us of each update's 750.
+__device__ __forceinline__ void store_lo(const HopArgs &a, const VecDesc &vd, const SysDesc &sd, int cb, const double o[24])
+{
+    float y[24];
+#pragma unroll
+    for (int k = 0; k < 24; ++k) y[k] = (float)o[k];
+    if (a.lo_prec == P_F32) {
+        store_spinor<P_F32>((float4 *)a.lo + (size_t)vd.site_off * 6, nullptr, sd.stride, cb, y);
+    } else {
+        uint4 *base = (uint4 *)a.lo + (size_t)vd.site_off * 3;
+        if (a.lo_prec == P_F16)
+            store_spinor<P_F16>(base, a.lo_norm + vd.site_off, sd.stride, cb, y);
+        else
+            store_spinor<P_BF16>(base, a.lo_norm + vd.site_off, sd.stride, cb, y);
+    }
+}
+
 // Everything after the hopping sum at one output site of one vector: the
 // linear-combination epilogue, the store, and the site's reduction values.
 // acc holds H psi (FP16/BF16: already multiplied by the system's c).  CANON:
@@ -172,7 +192,11 @@ __device__ __forceinline__ void hop_epilogue(const HopArgs &a, const HopIO &f, c
         for (int k = 0; k < 24; ++k) acc[k] = o[k];
         return;
     }
-    store_spinor<SP, true>((CH *)f.out + voff, f.out_norm ? f.out_norm + vd.site_off : nullptr, sd.stride, cb, o);
+    if (SP == P_F64 && a.lo) {
+        if constexpr (SP == P_F64) store_lo(a, vd, sd, cb, o);
+    } else {
+        store_spinor<SP, true>((CH *)f.out + voff, f.out_norm ? f.out_norm + vd.site_off : nullptr, sd.stride, cb, o);
+    }
     if (a.red.kind != RED_NONE) {
         if (a.red.mode == RM_NORM) {
             rv[0] = site_norm2(o);
@@ -1101,8 +1125,13 @@ void k_hop_split(HopArgs a)
         if (w < S::finishers && live) {
             void *out = (CH *)f.out + voff;
             if constexpr (SP == P_F64) {
-                st_out<true>(row_elem<double2>(out, 2 * w, sd.stride, cb), double2{o[0], o[1]});
-                st_out<true>(row_elem<double2>(out, 2 * w + 1, sd.stride, cb), double2{o[2], o[3]});
+                if (a.lo) {  // FP32 (the host offers this variant no half-precision one)
+                    st_out<false>(row_elem<float4>((float4 *)a.lo + (size_t)vd.site_off * 6, w, sd.stride, cb),
+                                  float4{(float)o[0], (float)o[1], (float)o[2], (float)o[3]});
+                } else {
+                    st_out<true>(row_elem<double2>(out, 2 * w, sd.stride, cb), double2{o[0], o[1]});
+                    st_out<true>(row_elem<double2>(out, 2 * w + 1, sd.stride, cb), double2{o[2], o[3]});
+                }
             } else {
                 st_out<true>(row_elem<float4>(out, w, sd.stride, cb), float4{o[0], o[1], o[2], o[3]});
             }
@@ -1354,6 +1383,7 @@ hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, int bloc
                                hipEvent_t e0, hipEvent_t e1)
 {
     if (a.canon_in && var != 11) return hipErrorInvalidValue;
+    if (a.lo && (SP != P_F64 || a.canon)) return hipErrorInvalidValue;
     switch (var) {
     case 0: return launch_hop_v<SP, GP, R, 0>(dag, clov, a, block, s, e0, e1);
     case 1: return launch_hop_v<SP, GP, R, 1>(dag, clov, a, block, s, e0, e1);
@@ -1373,6 +1403,7 @@ hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, int bloc
     case 11:
         if (block != 64) return hipErrorInvalidValue;  // 64 sites on 512 threads
         if (a.canon_in && (!a.canon || a.epi.nx > 1)) return hipErrorInvalidValue;
+        if (a.lo && a.lo_prec != P_F32) return hipErrorInvalidValue;
         if (a.canon_in)
             return clov ? launch_hop_split<SP, GP, R, EP_CLOVER_CANON | EP_DIRECT>(dag, a, s, e0, e1)
                         : launch_hop_split<SP, GP, R, EP_CANON | EP_DIRECT>(dag, a, s, e0, e1);

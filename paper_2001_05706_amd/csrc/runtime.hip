@@ -837,7 +837,7 @@ static Fold fold_of(const ExecSet &S, const Layout *L)
 static int plan_id(int prec, int recon, bool dag, bool clov, const Epi &e, bool red, bool twin)
 {
     return prec | (recon == 12) << 2 | (int)dag << 3 | (int)clov << 4 | (int)red << 5 | (int)twin << 6 |
-           (e.canon != nullptr) << 7 | e.nx << 8;
+           (e.canon != nullptr) << 7 | e.nx << 8 | (e.lo.p ? e.lo.prec : 0) << 11;
 }
 
 // Up to this many blocks of 64 sites a set's hop is variant 11 without timing it:
@@ -868,10 +868,12 @@ static bool dslash_direct(const ExecSet &S, int parities)
 // The launch configuration and block map of one kind of hop: from the set's plans
 // once the tuner has settled it (a D-slash call or a solver's eager launch spent
 // more host time on the tuner's key, the candidate list and the lookups than on
-// the launch), else from the tuner.  A pinned configuration is looked at anew
+// the launch), else from the tuner.  untimed: variant 11 exists for this kind, and
+// small sets take it without the tuner.  A pinned configuration is looked at anew
 // each time.
 template <class Key, class Cands, class Run>
-static wl_status hop_plan(ExecSet &S, int id, ExecSet::HopPlan *pl, hipStream_t s, Key key, Cands cands, Run run)
+static wl_status hop_plan(ExecSet &S, int id, bool untimed, ExecSet::HopPlan *pl, hipStream_t s, Key key, Cands cands,
+                          Run run)
 {
     const bool pinned = getenv("WL_TUNE_FORCE") != nullptr;
     if (!pinned) {
@@ -882,7 +884,7 @@ static wl_status hop_plan(ExecSet &S, int id, ExecSet::HopPlan *pl, hipStream_t 
         }
     }
     bool settled = false;
-    if (split_untimed(S)) {
+    if (untimed && split_untimed(S)) {
         pl->cfg = cfg_make(11, 64, 4);
         WL_TRY(hop_layout(S, pl->cfg, &pl->L));
         S.plans[id] = *pl;
@@ -933,17 +935,27 @@ wl_status hop(ExecSet &S, int prec, int recon, bool dag, int par, const Field &o
         a.canon = e.canon;
         a.canon_in = e.canon_in;
         a.canon_zero = e.canon_zero;
+        a.lo = e.lo.p;
+        a.lo_norm = e.lo.n;
+        a.lo_prec = e.lo.prec;
         return a;
     };
     // tuned per epilogue shape: a hop that also reads X fields and reduces may
     // prefer another variant than a plain one
     ExecSet::HopPlan pl{};
-    WL_TRY(hop_plan(S, plan_id(prec, recon, dag, clov, e, red.kind != RED_NONE, false), &pl, s,
+    WL_TRY(hop_plan(S, plan_id(prec, recon, dag, clov, e, red.kind != RED_NONE, false),
+                    !e.lo.p || e.lo.prec == P_F32, &pl, s,
                     [&]() {
                         return hop_key(S, prec, recon, dag) + (clov ? "/clov" : "") + "/x" + std::to_string(e.nx) +
-                               (red.kind != RED_NONE ? "/r" : "") + (e.canon ? "/canon" : "");
+                               (red.kind != RED_NONE ? "/r" : "") + (e.canon ? "/canon" : "") +
+                               (e.lo.p ? "/lo" + std::to_string(e.lo.prec) : std::string());
                     },
-                    [&]() { return hop_cands(S, prec, clov); },
+                    [&]() {
+                        std::vector<int> c = hop_cands(S, prec, clov);
+                        if (e.lo.p && e.lo.prec != P_F32)
+                            c.erase(std::remove_if(c.begin(), c.end(), [](int x) { return cfg_var(x) == 11; }), c.end());
+                        return c;
+                    },
                     [&](int c, const Layout *Lc) -> hipError_t {
                         // with the launch's own reduction: the partial slots it writes are
                         // rewritten by the launch that follows the tuning
@@ -952,6 +964,7 @@ wl_status hop(ExecSet &S, int prec, int recon, bool dag, int par, const Field &o
     const int B = cfg_block(pl.cfg), var = cfg_var(pl.cfg);
     const Layout *L = pl.L;
     const double bytes = hop_bytes(S, prec, recon, use_active) + blas_bytes(S, prec, e.nx, use_active) +
+                         (e.lo.p ? blas_bytes(S, e.lo.prec, 1, use_active) - blas_bytes(S, prec, 1, use_active) : 0) +
                          (clov ? ((e.clov & EPI_CLOV_X0) ? 1 : 0) + ((e.clov & EPI_CLOV_INV) ? 1 : 0) : 0) *
                              clover_bytes(S, prec, use_active);
     g_bytes_acc += bytes;
@@ -1119,7 +1132,7 @@ wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], co
         return r != hipSuccess ? r : launch_hop(prec, recon, dag, clov, var, mk(L, 1), B, s);
     };
     ExecSet::HopPlan pl{};
-    WL_TRY(hop_plan(S, plan_id(prec, recon, dag, clov, e[0], false, true), &pl, s,
+    WL_TRY(hop_plan(S, plan_id(prec, recon, dag, clov, e[0], false, true), true, &pl, s,
                     [&]() {
                         return hop_key(S, prec, recon, dag) + (clov ? "/clov" : "") + "/twin/x" +
                                std::to_string(e[0].nx) + (e[0].canon ? "/canon" : "");

@@ -240,6 +240,7 @@ struct Epi {
     int clov = 0;  // EPI_CLOV_* bits (act only on systems with a clover term)
     const double *coef = nullptr;  // device [nsys][5]
     Field X[4];
+    Field lo;  // FP64 hops: the result is rounded to this field instead of `out`
     // the result goes to this canonical field instead of `out` (one system, no
     // reduction); canon_zero: with zeros on the other parity
     double *canon = nullptr;

@@ -170,6 +170,12 @@ struct HopArgs {
                              // site) is read from this canonical field instead of `in`
     int32_t canon_zero;
     int32_t pad_;
+    // FP64 hops without canon (null: off): the result is rounded to this FP32, FP16
+    // or BF16 field instead of being stored in FP64
+    void *lo;
+    float *lo_norm;
+    int32_t lo_prec;
+    int32_t pad2_;
     // CGNR iteration of small sets (k_hop_iter): the second field of a combined
     // input, the updated fields beside `out`, the partials of |r|^2
     const void *in2;
