@@ -70,6 +70,7 @@ struct Cg {
 
     Field eta_e, eta_o, bp, xh, rh, t64, xo;  // FP64
     Field xl, rl, p, q, sv, tl;               // sloppy; BiCGStab: q = v, sv = s
+    Field p2;                                 // sloppy, CGNR only: every other direction
     Field tb, rhat;                           // sloppy, BiCGStab only: t, shadow residual
     const double *c_plain = nullptr, *c_bp = nullptr, *c_M = nullptr, *c_res = nullptr, *c_tres = nullptr;
 
@@ -87,6 +88,9 @@ struct Cg {
             WL_TRY(S.field("bi_t", sloppy, &tb));
             WL_TRY(S.field("bi_rhat", sloppy, &rhat));
         }
+        // (where memory is too short for p2, each iteration updates x by itself)
+        p2 = Field();
+        if (method == M_CGNR && !iter_fused(S, sloppy) && S.field("cg_p2", sloppy, &p2) != WL_OK) p2 = Field();
         return WL_OK;
     }
 
@@ -170,7 +174,7 @@ struct Cg {
     wl_status iterations(int k)
     {
         if (method != M_CGNR || !iter_fused(S, sloppy)) {
-            for (int j = 0; j < k; ++j) WL_TRY(iteration(j));
+            for (int j = 0; j < k; ++j) WL_TRY(iteration(j, !p2.p || (j == k - 1 && k % 2) ? 0 : 1 + j % 2));
             return hist_report(S, k, method == M_CGNR, s);
         }
         const Layout *lq = nullptr, *ls = nullptr;
@@ -197,7 +201,9 @@ struct Cg {
 
     // iteration j of a chunk in the sloppy precision; history row j receives |r|^2
     // (CGNR: its block partials are summed for the whole chunk by hist_finalize)
-    wl_status iteration(int j)
+    // pair (CGNR): 1, 2 for the first and second of two iterations that update x
+    // together (the first leaves its new direction in p2), 0 for one by itself
+    wl_status iteration(int j, int pair)
     {
         double *hist_row = S.hist + (size_t)j * S.nvec;
         if (method == M_BICGSTAB) {
@@ -228,7 +234,7 @@ struct Cg {
         // (few partials of alpha and beta are left to the updates that use them)
         RedSpec ra = red_spec(S, RED_ALPHA, nullptr), rb = red_spec(S, RED_BETA, nullptr);
         ra.defer = 2;
-        WL_TRY(apply_M(sloppy, recon, false, q, p, tl, ra));
+        WL_TRY(apply_M(sloppy, recon, false, q, pair == 2 ? p2 : p, tl, ra));
         const Layout *fold = S.fold;
         rb.defer = fold ? 2 : 0;
         Field f[2] = {rl, q};
@@ -237,17 +243,20 @@ struct Cg {
         rr.defer = 1;
         WL_TRY(blas(S, BL_R_UPDATE, sloppy, f, 2, S.scal(SC_ALPHA), rr, s, true, 0, 0, fold));
         WL_TRY(apply_M(sloppy, recon, true, sv, rl, tl, rb));
-        Field g[3] = {p, sv, xl};
-        WL_TRY(blas(S, BL_XPAY_X, sloppy, g, 3, S.scal(SC_BETA), no_red(), s, true, 0, 0, S.fold));
-        return WL_OK;
+        fold = S.fold;
+        const Field g0[3] = {p, sv, xl}, g1[3] = {p2, sv, p}, g2[4] = {p, sv, xl, p2};
+        if (pair == 1) return blas(S, BL_XPAY_1, sloppy, g1, 3, S.scal(SC_BETA), no_red(), s, true, 0, 0, fold);
+        if (pair == 2) return blas(S, BL_XPAY_2, sloppy, g2, 4, S.scal(SC_BETA), no_red(), s, true, 0, 0, fold);
+        return blas(S, BL_XPAY_X, sloppy, g0, 3, S.scal(SC_BETA), no_red(), s, true, 0, 0, fold);
     }
 
-    double iteration_bytes()
+    double chunk_bytes(int k)
     {
-        if (method == M_BICGSTAB)  // 4 hops (+3 epilogue reads), p (4), s (3), x/r (7)
-            return 4 * hop_bytes(S, sloppy, recon, true) + blas_bytes(S, sloppy, 3 + 4 + 3 + 7, true);
-        return 4 * hop_bytes(S, sloppy, recon, true) + 2 * blas_bytes(S, sloppy, 1, true) +
-               blas_bytes(S, sloppy, 3, true) + blas_bytes(S, sloppy, 5, true);
+        const double hops = 4.0 * k * hop_bytes(S, sloppy, recon, true), pass = blas_bytes(S, sloppy, 1, true);
+        if (method == M_BICGSTAB) return hops + k * (3 + 4 + 3 + 7) * pass;  // 3 epilogue reads, p, s, x/r
+        // 2 epilogue reads, r (3), x and p (9 for two iterations, 5 for one by itself)
+        const int pairs = p2.p ? k / 2 : 0;
+        return hops + (k * (2 + 3) + pairs * 9 + (k - 2 * pairs) * 5) * pass;
     }
 
     // The part of a refresh common to continued and restarted vectors, for the
@@ -350,7 +359,7 @@ struct Cg {
             if (ie != hipSuccess) return set_error(WL_ERR_HIP, "graph instantiation failed: %s", hipGetErrorString(ie));
             it = S.graphs.emplace(key, ex).first;
         }
-        g_bytes_acc += k * iteration_bytes();
+        g_bytes_acc += chunk_bytes(k);
         WL_HIP(hipGraphLaunch(it->second, s));
         return WL_OK;
     }

@@ -21,7 +21,7 @@ struct BlasArgs {
     int32_t one;       // the set holds one vector (its descriptors are at index 0)
     int32_t stream;    // solver-iteration kernels: fields read and written non-temporally
     RedSpec red;
-    Fold fold;         // BL_R_UPDATE, BL_XPAY_X, BL_BICG_S, BL_BICG_XR: alpha, beta or omega
+    Fold fold;         // BL_R_UPDATE, BL_XPAY_*, BL_BICG_S, BL_BICG_XR: alpha, beta or omega
                        // is still the producing hop's block partials
 };
 
@@ -80,6 +80,9 @@ enum BlasOp {
     // CGNR iteration with the solution update moved into the direction update:
     BL_R_UPDATE = 17,  // r -= alpha q; |r|^2                                               f = {r, q},    s0 = alpha
     BL_XPAY_X = 18,    // x += alpha p; p = s + beta p (alpha from its slot)                  f = {p, s, x}, s0 = beta
+    // two iterations' solution updates in one pass over x:
+    BL_XPAY_1 = 19,    // p2 = s + beta p, alpha set aside                                    f = {p2, s, p}, s0 = beta
+    BL_XPAY_2 = 20,    // x += alpha_1 p + alpha p2; p = s + beta p2                          f = {p, s, x, p2}, s0 = beta
 };
 hipError_t launch_blas(int op, int prec, const BlasArgs &a, int block, hipStream_t s);
 // fixed-order sum of each active vector's block partials and the reduction's finishing step

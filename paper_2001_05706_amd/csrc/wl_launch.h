@@ -41,7 +41,8 @@ WL_HD int xcd_remap(int h, int nb)
 // Per-vector scalar slots of a set: scalar `slot` of vector v lives at
 // sc[slot * nvec + v].  Complex scalars use two slots (re, im).
 enum ScSlot {
-    SC_ALPHA = 0, SC_BETA, SC_GAM, SC_GAMP /* gamma of the previous step */, SC_QQ, SC_RR, SC_ETA, SC_TMP,
+    SC_ALPHA = 0, SC_BETA, SC_GAM, SC_GAMP /* gamma of the previous step */,
+    SC_ALPP /* alpha of the previous step */, SC_QQ, SC_RR, SC_ETA, SC_TMP,
     SC_RHO_RE, SC_RHO_IM,      // BiCGStab rho = <rhat, r>
     SC_RHOP_RE, SC_RHOP_IM,    // rho of the previous iteration
     SC_AL_RE, SC_AL_IM,        // complex alpha
