@@ -152,8 +152,8 @@ __global__ __launch_bounds__(256) void k_xpay_x(BlasArgs a)
 
 // The same step of two iterations with one pass over x: the first only forms the
 // new direction, beside the old one, and the second adds both directions to x.
-// Nine field passes instead of ten: at 32^3x64 in FP16 86 us instead of 96 for the
-// pair, at 24^3x48 in FP32 with 12 sources 595 instead of 658.
+// Nine field passes instead of ten: at 32^3x64 in FP16 85 us instead of 96 for the
+// pair, at 24^3x48 in FP32 with 12 sources 594 instead of 658.
 template <int P, bool ONE = false, bool NT = false>
 __global__ __launch_bounds__(256) void k_xpay_1(BlasArgs a)
 {
@@ -189,8 +189,11 @@ __global__ __launch_bounds__(256) void k_xpay_2(BlasArgs a)
     const T be = (T)(a.fold.vec ? fold_beta(a.fold, vi, bm.lblk) : a.s0[vi]);
     if (!live) return;
 #pragma unroll
+    for (int k = 0; k < 24; ++k) x[k] += al1 * p[k];
+    round_spinor<P>(x);  // the iterates of the one-by-one form, which decide when a solve restarts
+#pragma unroll
     for (int k = 0; k < 24; ++k) {
-        x[k] = fmadd(al, p2[k], fmadd(al1, p[k], x[k]));
+        x[k] += al * p2[k];
         p[k] = s[k] + be * p2[k];
     }
     store_spinor<P, NT>(vbase<P>(a.f[2], vd), nbase(a.fn[2], vd), sd.stride, cb, x);
