@@ -12,10 +12,10 @@
 //   M^+ = 1 - kappa^2 D_oe^+ D_eo^+ (dagger hops in the same order).
 // Iteration (sloppy precision; alpha, beta, gamma stay on the device):
 //   q = M p, alpha = gamma / |q|^2; r -= alpha q (|r|^2 fused);
-//   s = M^+ r, gamma' = |s|^2, beta = gamma'/gamma; x += alpha p and
-//   p = s + beta p in one pass over p.
-// The host reads only the |r|^2 history, once per chunk of iterations.  A
-// chunk is captured once as a HIP graph and replayed.  When the sloppy
+//   s = M^+ r, gamma' = |s|^2, beta = gamma'/gamma; p = s + beta p and, once for
+//   two iterations, x += alpha_1 p_1 + alpha_2 p_2 in one pass.
+// The host reads only the |r|^2 history, once per chunk of iterations, from
+// pinned memory that the reporting kernel writes.  A chunk is captured once as a HIP graph and replayed.  When the sloppy
 // residual of a right-hand side has fallen by `delta` since its last update
 // (or reached the tolerance, or maxiter) the FP64 accumulator takes x_lo and
 // the residual b' - M x is recomputed in FP64 (reliable update); p is kept

@@ -1,7 +1,7 @@
 // hop.hip -- the single-parity Wilson hopping kernel (the D-slash of Table 2)
 // with a fused linear-combination epilogue and optional fused |out|^2.
 //
-// One thread per output site of one vector.  Per direction the neighbour
+// One thread per output site of one vector (variant 11: eight, one a direction).  Per direction the neighbour
 // spinor is spin-projected to two components (12 flop), both are multiplied
 // by the link (2 x 66 flop) rebuilt from 12 reals when recon = 12, and the
 // result is spin-reconstructed into the accumulator (24 flop): 1320 flop per

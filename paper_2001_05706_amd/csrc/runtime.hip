@@ -788,9 +788,9 @@ static int blocks64(const ExecSet &S)
 
 // The candidates of a hop launch on this set: variants 6-8 need several
 // right-hand sides in a system, the clover epilogue the registers of the
-// two-direction variants (0 and 3) without LDS staging, and pencil blocks
-// (9, 10) time slices of a multiple of 64 sites and a time extent that their
-// slice count divides.
+// two-direction variants (0 and 3) without LDS staging or the one direction per
+// wave of variant 11, and pencil blocks (9, 10) time slices of a multiple of 64
+// sites and a time extent that their slice count divides.
 static std::vector<int> hop_cands(const ExecSet &S, int prec, bool clov)
 {
     int max_nrhs = 0;
