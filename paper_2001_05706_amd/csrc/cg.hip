@@ -90,7 +90,10 @@ struct Cg {
         }
         // (where memory is too short for p2, each iteration updates x by itself)
         p2 = Field();
-        if (method == M_CGNR && !iter_fused(S, sloppy) && S.field("cg_p2", sloppy, &p2) != WL_OK) p2 = Field();
+        if (method == M_CGNR && !iter_fused(S, sloppy) && S.field("cg_p2", sloppy, &p2) != WL_OK) {
+            clear_error();
+            p2 = Field();
+        }
         return WL_OK;
     }
 
