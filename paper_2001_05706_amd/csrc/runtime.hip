@@ -703,9 +703,18 @@ double blas_bytes(const ExecSet &S, int prec, int passes, bool use_active)
     return b;
 }
 
+// What a set's hop candidates and their times depend on: the extents (pencil blocks
+// tile some lattices of a volume and not others) and right-hand sides of its systems
 static std::string set_sig(const ExecSet &S)
 {
-    return std::to_string(S.nvec) + ":" + std::to_string(S.total_sites);
+    std::string sig;
+    for (auto &e : S.systems) {
+        const int32_t *L = e.g->geom.L;
+        char t[80];
+        snprintf(t, sizeof(t), "%s%dx%dx%dx%d*%d", sig.empty() ? "" : "+", L[0], L[1], L[2], L[3], e.nrhs);
+        sig += t;
+    }
+    return sig;
 }
 
 std::string hop_key(const ExecSet &S, int prec, int recon, bool dag)
