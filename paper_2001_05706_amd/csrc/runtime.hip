@@ -842,11 +842,10 @@ static Fold fold_of(const ExecSet &S, const Layout *L)
     return Fold{L->d_vec, S.partials, S.sc, S.bad, S.nvec, 0};
 }
 
-// A kind of hop launch of a set, as an index into its plans
-static int plan_id(int prec, int recon, bool dag, bool clov, const Epi &e, bool red, bool twin)
+int plan_id(int prec, int recon, bool dag, bool clov, const Epi &e, bool red, bool twin)
 {
     return prec | (recon == 12) << 2 | (int)dag << 3 | (int)clov << 4 | (int)red << 5 | (int)twin << 6 |
-           (e.canon != nullptr) << 7 | e.nx << 8 | (e.lo.p ? e.lo.prec : 0) << 11;
+           (e.canon != nullptr) << 7 | e.nx << 8 | (e.lo.p ? e.lo.prec : 0) << 11 | (e.canon_in != nullptr) << 13;
 }
 
 // Up to this many blocks of 64 sites a set's hop is variant 11 without timing it:
@@ -877,12 +876,12 @@ static bool dslash_direct(const ExecSet &S, int parities)
 // The launch configuration and block map of one kind of hop: from the set's plans
 // once the tuner has settled it (a D-slash call or a solver's eager launch spent
 // more host time on the tuner's key, the candidate list and the lookups than on
-// the launch), else from the tuner.  untimed: variant 11 exists for this kind, and
-// small sets take it without the tuner.  A pinned configuration is looked at anew
-// each time.
+// the launch), else from the tuner.  direct: the input is canonical, which only
+// variant 11 reads; untimed: variant 11 exists for this kind, and small sets take it
+// without the tuner.  A pinned configuration is looked at anew each time.
 template <class Key, class Cands, class Run>
-static wl_status hop_plan(ExecSet &S, int id, bool untimed, ExecSet::HopPlan *pl, hipStream_t s, Key key, Cands cands,
-                          Run run)
+static wl_status hop_plan(ExecSet &S, int id, bool direct, bool untimed, ExecSet::HopPlan *pl, hipStream_t s, Key key,
+                          Cands cands, Run run)
 {
     const bool pinned = getenv("WL_TUNE_FORCE") != nullptr;
     if (!pinned) {
@@ -893,7 +892,7 @@ static wl_status hop_plan(ExecSet &S, int id, bool untimed, ExecSet::HopPlan *pl
         }
     }
     bool settled = false;
-    if (untimed && split_untimed(S)) {
+    if (direct || (untimed && split_untimed(S))) {
         pl->cfg = cfg_make(11, 64, 4);
         WL_TRY(hop_layout(S, pl->cfg, &pl->L));
         S.plans[id] = *pl;
@@ -952,7 +951,7 @@ wl_status hop(ExecSet &S, int prec, int recon, bool dag, int par, const Field &o
     // tuned per epilogue shape: a hop that also reads X fields and reduces may
     // prefer another variant than a plain one
     ExecSet::HopPlan pl{};
-    WL_TRY(hop_plan(S, plan_id(prec, recon, dag, clov, e, red.kind != RED_NONE, false),
+    WL_TRY(hop_plan(S, plan_id(prec, recon, dag, clov, e, red.kind != RED_NONE, false), e.canon_in != nullptr,
                     !e.lo.p || e.lo.prec == P_F32, &pl, s,
                     [&]() {
                         return hop_key(S, prec, recon, dag) + (clov ? "/clov" : "") + "/x" + std::to_string(e.nx) +
@@ -1141,7 +1140,7 @@ wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], co
         return r != hipSuccess ? r : launch_hop(prec, recon, dag, clov, var, mk(L, 1), B, s);
     };
     ExecSet::HopPlan pl{};
-    WL_TRY(hop_plan(S, plan_id(prec, recon, dag, clov, e[0], false, true), true, &pl, s,
+    WL_TRY(hop_plan(S, plan_id(prec, recon, dag, clov, e[0], false, true), e[0].canon_in != nullptr, true, &pl, s,
                     [&]() {
                         return hop_key(S, prec, recon, dag) + (clov ? "/clov" : "") + "/twin/x" +
                                std::to_string(e[0].nx) + (e[0].canon ? "/canon" : "");

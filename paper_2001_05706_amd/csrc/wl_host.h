@@ -334,6 +334,8 @@ wl_status defl_axpy(ExecSet &S, const Deflation &D, int prec, const Field y[2], 
 int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream_t s,
                 const std::function<hipError_t(int)> &run, bool *settled = nullptr);
 bool capturing(hipStream_t s);
+// a kind of hop launch of a set, as an index into its plans
+int plan_id(int prec, int recon, bool dag, bool clov, const Epi &e, bool red, bool twin);
 std::string hop_key(const ExecSet &S, int prec, int recon, bool dag);
 std::vector<int> hop_candidates(int prec, bool many);  // many: several right-hand sides
 int cfg_make(int var, int block, int col);  // hop launch configuration: variant, block size, column height

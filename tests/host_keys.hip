@@ -1,5 +1,6 @@
-// host_keys.hip -- the tuner key of a set, as a host function, for the CPU test
-// of what a key tells apart.  Test infrastructure only; linked with libwilson.so.
+// host_keys.hip -- the tuner key of a set and the plan index of a hop, as host
+// functions, for the CPU tests of what they tell apart.  Test infrastructure only;
+// linked with libwilson.so.
 #include <cstring>
 
 #include "../paper_2001_05706_amd/csrc/wl_host.h"
@@ -37,4 +38,16 @@ extern "C" int hop_key_of(int n, const int32_t *L, const int32_t *nrhs, char *ou
     if ((int)k.size() >= size) return 1;
     strcpy(out, k.c_str());
     return 0;
+}
+
+// The plan index of the D-slash call's hop (twin: of both parities) that reads the
+// canonical input itself (direct) or a packed one
+extern "C" int plan_id_of(int prec, int nx, int twin, int direct)
+{
+    double canon[1] = {0};
+    Epi e;
+    e.nx = nx;
+    e.canon = canon;
+    e.canon_in = direct ? canon : nullptr;
+    return plan_id(prec, 12, false, false, e, false, twin != 0);
 }

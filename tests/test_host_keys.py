@@ -1,4 +1,4 @@
-"""What the tuner's key of a hop tells apart (CPU): a configuration found on one
+"""What the tuner's key and the plan index of a hop tell apart (CPU): a configuration found on one
 set is used for every set of the same key, so sets whose candidates differ need
 different keys.  Pencil blocks need the time extent to be a multiple of their
 slices and time slices of whole waves, and some variants several right-hand sides
@@ -16,12 +16,17 @@ PKG = os.path.join(os.path.dirname(HERE), "paper_2001_05706_amd")
 
 
 @pytest.fixture(scope="module")
-def key(tmp_path_factory):
+def keys(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("keys") / "libkeys.so")
     cmd = ["/opt/rocm/bin/hipcc", "--offload-arch=gfx950", "-O1", "-std=c++17", "-fPIC", "-shared", "-w",
            os.path.join(HERE, "host_keys.hip"), "-o", out, "-L" + PKG, "-l:libwilson.so", "-Wl,-rpath," + PKG]
     subprocess.run(cmd, check=True, capture_output=True)
-    lib = ctypes.CDLL(out)
+    return ctypes.CDLL(out)
+
+
+@pytest.fixture(scope="module")
+def key(keys):
+    lib = keys
 
     def of(*systems):
         L = np.array([s[0] for s in systems], dtype=np.int32)
@@ -51,3 +56,10 @@ def test_keys_differ(key, a, b):
 def test_keys_agree_for_the_same_shape(key):
     s = [((8, 8, 8, 16), 2), ((4, 4, 4, 8), 1)]
     assert key(*s) == key(*s)
+
+
+@pytest.mark.parametrize("prec", range(4))
+def test_plans_differ_where_only_variant_11_can_serve(keys, prec):
+    """Of a D-slash call that reads the canonical input in the hop and one that packs it."""
+    ids = [keys.plan_id_of(prec, nx, twin, direct) for nx in (0, 1) for twin in (0, 1) for direct in (0, 1)]
+    assert len(set(ids)) == len(ids)
