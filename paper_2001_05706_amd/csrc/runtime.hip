@@ -1408,7 +1408,9 @@ wl_status wilson_dslash(wl_gauge U, const double *in, double *out, int32_t nrhs,
         if (dslash_direct(*S, 1)) {
             e[0].canon_in = in;
         } else {
-            WL_TRY(S->field("dsl_in" + std::to_string(1 - parity), prec, &fi[1 - parity]));
+            // (both parities' fields: a later call with the other one may be captured,
+            // where nothing can be allocated)
+            for (int p = 0; p < 2; ++p) WL_TRY(S->field("dsl_in" + std::to_string(p), prec, &fi[p]));
             WL_TRY(pack(*S, cin, 1 - parity, fi[1 - parity], s));
         }
         WL_TRY(hop(*S, prec, recon, dagger, parity, Field(), fi[1 - parity], e[0], no_red(), s, false));

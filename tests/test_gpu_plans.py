@@ -29,3 +29,30 @@ def test_plan_of_a_packed_call_is_not_a_direct_calls(prec, recon, parity, monkey
                 out.append(from_dev(o, psi.shape))
         g.close()
         assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
+
+
+@pytest.mark.parametrize("prec,recon", [("f64", 18), ("f32", 12), ("bf16", 12)])
+@pytest.mark.parametrize("L,nrhs", [((8, 8, 8, 16), 9), ((8, 8, 8, 16), 1)])  # 576 and 64 blocks of 64 sites
+def test_other_parity_first_met_under_capture(L, nrhs, prec, recon):
+    """A call with one output parity prepares the set for either: the other one can
+    be captured, and its replays follow the input."""
+    import torch
+
+    w = need_gpu()
+    g = w.Gauge(L, to_dev(li.haar_links(L, 34)))
+    a, b = (to_dev(li.gaussian_spinor(L, 35 + i, nrhs=nrhs)) for i in range(2))
+    inp, out, ref = a.clone(), torch.empty_like(a), torch.empty_like(a)
+    w.wilson_dslash(g, inp, out, nrhs, 0.12, 0, 0, prec, recon)
+    torch.cuda.synchronize()
+    graph, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=s):
+        w.wilson_dslash(g, inp, out, nrhs, 0.12, 1, 0, prec, recon)
+    for src in (a, b, a):
+        inp.copy_(src)
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        w.wilson_dslash(g, inp, ref, nrhs, 0.12, 1, 0, prec, recon)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+    g.close()
