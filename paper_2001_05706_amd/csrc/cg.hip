@@ -70,7 +70,7 @@ struct Cg {
 
     Field eta_e, eta_o, bp, xh, rh, t64, xo;  // FP64
     Field xl, rl, p, q, sv, tl;               // sloppy; BiCGStab: q = v, sv = s
-    Field p2;                                 // sloppy, CGNR only: every other direction
+    Field p2;                                 // sloppy, CGNR only: every other direction, within a chunk
     Field tb, rhat;                           // sloppy, BiCGStab only: t, shadow residual
     const double *c_plain = nullptr, *c_bp = nullptr, *c_M = nullptr, *c_res = nullptr, *c_tres = nullptr;
 
@@ -88,12 +88,11 @@ struct Cg {
             WL_TRY(S.field("bi_t", sloppy, &tb));
             WL_TRY(S.field("bi_rhat", sloppy, &rhat));
         }
-        // (where memory is too short for p2, each iteration updates x by itself)
-        p2 = Field();
-        if (method == M_CGNR && !iter_fused(S, sloppy) && S.field("cg_p2", sloppy, &p2) != WL_OK) {
-            clear_error();
-            p2 = Field();
-        }
+        // p2 lies in t64, which holds nothing between two updates: a site of t64 has 192
+        // bytes, one of p2 at most that, its norm included
+        p2.prec = sloppy;
+        p2.p = t64.p;
+        p2.n = rl.n ? (float *)((char *)t64.p + S.total_sites * (size_t)nchunks(sloppy) * wl::chunk_bytes(sloppy)) : nullptr;
         return WL_OK;
     }
 
@@ -177,7 +176,7 @@ struct Cg {
     wl_status iterations(int k)
     {
         if (method != M_CGNR || !iter_fused(S, sloppy)) {
-            for (int j = 0; j < k; ++j) WL_TRY(iteration(j, !p2.p || (j == k - 1 && k % 2) ? 0 : 1 + j % 2));
+            for (int j = 0; j < k; ++j) WL_TRY(iteration(j, j == k - 1 && k % 2 ? 0 : 1 + j % 2));
             return hist_report(S, k, method == M_CGNR, s);
         }
         const Layout *lq = nullptr, *ls = nullptr;
@@ -258,7 +257,7 @@ struct Cg {
         const double hops = 4.0 * k * hop_bytes(S, sloppy, recon, true), pass = blas_bytes(S, sloppy, 1, true);
         if (method == M_BICGSTAB) return hops + k * (3 + 4 + 3 + 7) * pass;  // 3 epilogue reads, p, s, x/r
         // 2 epilogue reads, r (3), x and p (9 for two iterations, 5 for one by itself)
-        const int pairs = p2.p ? k / 2 : 0;
+        const int pairs = iter_fused(S, sloppy) ? 0 : k / 2;
         return hops + (k * (2 + 3) + pairs * 9 + (k - 2 * pairs) * 5) * pass;
     }
 
