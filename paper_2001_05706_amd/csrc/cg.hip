@@ -159,7 +159,7 @@ struct Cg {
         rr.host = S.dev_report(ExecSet::kRepRR);
         rr.rep = S.rep(1);
         Epi e = second(c_res, 2, xh, bp);
-        if (sloppy_r && sloppy != P_F64) e.lo = rl;
+        if (sloppy_r) e.lo = rl;
         WL_TRY(hop(S, P_F64, recon, false, 0, rh, t64, e, rr, s, use_active));
         return WL_OK;
     }
@@ -576,15 +576,9 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                 WL_TRY(S.upload_active(s));
                 Field ac[2] = {cg.xh, cg.xl};
                 WL_TRY(blas(S, BL_ACCUM, cg.sloppy, ac, 2, nullptr, no_red(), s));
+                for (int v = 0; v < nv; ++v) S.seen[1][v] += S.h_active[v] != 0;  // a report nobody waits for
+                WL_TRY(cg.residual64());
             }
-            // the residual of every vector that goes on, in FP64 (an update leaves it
-            // in the sloppy precision only)
-            for (int v = 0; v < nv; ++v) {
-                S.h_active[v] = !done[v];
-                S.seen[1][v] += S.h_active[v] != 0;  // a report nobody waits for
-            }
-            WL_TRY(S.upload_active(s));
-            WL_TRY(cg.residual64());
             const int next = cg.sloppy == P_F32 ? P_F64 : P_F32;
             Field p_old = cg.p, v_old = cg.q, rhat_old = cg.rhat;
             cg.sloppy = next;
@@ -683,13 +677,17 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                 }
                 for (int v = 0; v < nv; ++v) S.h_active[v] = upd[v];
                 WL_TRY(S.upload_active(s));
-                WL_TRY(cg.residual64(true));
+                // where the precision may be raised (a second stall in a row, or a
+                // non-finite iterate) the residual is kept in FP64: a raise starts from it
+                bool keep = anybad || cg.sloppy == P_F64;
+                for (int v = 0; v < nv; ++v) keep = keep || (upd[v] && stall[v] > 0);
+                WL_TRY(cg.residual64(!keep));
                 // every updated vector that goes on (continued or restarted) needs
                 // r from the new residual, and for CGNR s = M^+ r: they are queued
                 // before the host has read it, so the GPU works while the host
                 // decides (wasted only for vectors found converged)
                 const double b0 = g_bytes_acc;
-                WL_TRY(cg.refresh_s(cg.sloppy != P_F64));
+                WL_TRY(cg.refresh_s(!keep));
                 const double spec_bytes = g_bytes_acc - b0;
                 bool pre = true;
                 WL_TRY(wait_report(S, 1, upd, s));

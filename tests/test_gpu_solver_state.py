@@ -3,7 +3,8 @@ import numpy as np
 import pytest
 
 import lattice_inputs as li
-from tests.gpu_util import need_gpu, to_dev
+import oracle
+from tests.gpu_util import from_dev, need_gpu, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -27,3 +28,50 @@ def test_cgnr_needs_no_field_that_bicgstab_does_not():
     g.close()
     # block maps, launch plans and graphs come to a few MiB; one field is 64
     assert used < V // 2 * 192 // 2
+
+
+@pytest.mark.parametrize("sloppy", ["bf16", "f16", "f32"])
+def test_hops_of_an_escalated_solve(sloppy):
+    """Raising the sloppy precision costs the hops of its restart and no others: the
+    FP64 residual of the update that found the stagnation is still there."""
+    w = need_gpu()
+    L = (8, 8, 8, 8)
+    g = w.Gauge(L, to_dev(li.near_identity_links(L, 0.3, 1002)))
+    eta = to_dev(li.gaussian_spinor(L, 2002))
+    x = to_dev(np.zeros((1, 4096, 4, 3), dtype=complex))
+    w.wl_prof_read()
+    w.wl_prof_enable(True)
+    try:
+        _, info = w.wilson_cg(g, eta, x, 1, 0.1245, 1e-10, 5000, sloppy, 12, 0.9)
+    finally:
+        w.wl_prof_enable(False)
+        launches = w.wl_prof_read()[0]
+        g.close()
+    info = info[0]
+    assert info["precision_escalations"] > 0, info
+    # b' and the first s = M^+ r; four an iteration; the FP64 residual and s an update;
+    # s in the raised precision; odd sites and the true residual
+    want = 1 + 2 + 4 * info["iters"] + 4 * info["reliable_updates"] + 2 * info["precision_escalations"] + 3
+    assert launches == want, (launches, want, info)
+
+
+@pytest.mark.parametrize("sloppy", ["bf16", "f16", "f32"])
+def test_escalation_of_a_batch(sloppy):
+    """Systems that stall at different times: the others are folded in and their
+    residuals formed anew, and every later report is the one waited for."""
+    w = need_gpu()
+    Ls, nrhs, kappa = [(8, 8, 8, 8), (4, 6, 2, 8), (6, 4, 4, 10)], [1, 3, 2], [0.1245, 0.12, 0.122]
+    U = [li.near_identity_links(L, 0.3, 1002 + i) for i, L in enumerate(Ls)]
+    eta = [li.gaussian_spinor(L, 2002 + i, nrhs=n) for i, (L, n) in enumerate(zip(Ls, nrhs))]
+    eta[1][1] = 0
+    g = [w.Gauge(L, to_dev(u)) for L, u in zip(Ls, U)]
+    x = [to_dev(np.zeros_like(e)) for e in eta]
+    _, info = w.wilson_cg_multi(g, [to_dev(e) for e in eta], x, nrhs, kappa, 1e-10, 5000, sloppy, 12, 0.9)
+    for h in g:
+        h.close()
+    assert info[0]["precision_escalations"] > 0
+    for L, u, e, v, k in zip(Ls, U, eta, x, kappa):
+        psi = from_dev(v, e.shape)
+        for r in range(e.shape[0]):
+            res = e[r:r + 1] - oracle.wilson(L, u, psi[r:r + 1], k)
+            assert np.linalg.norm(res) <= 1.0001e-10 * np.linalg.norm(e[r:r + 1])
