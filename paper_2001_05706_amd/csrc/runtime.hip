@@ -1592,7 +1592,12 @@ wl_status wl_bench_dslash(wl_gauge U, wl_prec prec, int32_t recon, int32_t nrhs,
         st = hop(*S, prec, recon, false, parity, fout[0], fin[0], e, no_red(), s, false);
         const std::string key = hop_key(*S, prec, recon, false) + "/x0";
         const std::vector<int> cands = hop_cands(*S, prec, false);
-        cfg = tuned_block(key, cands, s, [](int) { return hipSuccess; });
+        // the configuration that this hop took (a small set's comes without the tuner)
+        const auto pl = S->plans.find(plan_id(prec, recon, false, false, e, false, false));
+        if (pl != S->plans.end() && !getenv("WL_TUNE_FORCE"))
+            cfg = pl->second.cfg;
+        else
+            cfg = tuned_block(key, cands, s, [](int) { return hipSuccess; });
         if (st == WL_OK && nsets > 1) {
             // cold protocol: the configuration is tuned on launches that rotate
             // through the operand sets, as the timed loop's do

@@ -56,3 +56,17 @@ def test_other_parity_first_met_under_capture(L, nrhs, prec, recon):
         torch.cuda.synchronize()
         assert torch.equal(out, ref)
     g.close()
+
+
+def test_bench_dslash_times_the_hops_configuration(capfd, monkeypatch):
+    """A small set's hop takes its variant without the tuner, and so does the
+    measurement of it: nothing untimed goes into the tuner's table."""
+    w = need_gpu()
+    monkeypatch.setenv("WL_DEBUG", "1")
+    L = (4, 4, 6, 10)
+    g = w.Gauge(L, to_dev(li.haar_links(L, 33)))
+    capfd.readouterr()
+    for prec, recon in CASES:
+        assert w.wl_bench_dslash(g, prec, recon, 1, 0, 1, 10) > 0
+    g.close()
+    assert "[wl tune]" not in capfd.readouterr().err
