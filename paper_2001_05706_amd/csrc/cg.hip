@@ -507,8 +507,10 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
         eta_n[v] = std::sqrt(hsc[SC_ETA * nv + v]);
         const double r = std::sqrt(hsc[SC_RR * nv + v]);
         target[v] = tol * eta_n[v];
-        if (!std::isfinite(eta_n[v]) || !std::isfinite(r))
+        if (!std::isfinite(eta_n[v]) || !std::isfinite(r)) {
+            WL_HIP(hipStreamSynchronize(s));  // r = b' may still be under way
             return set_error(WL_ERR_NONFINITE, "non-finite source or initial guess (rhs %d)", v);
+        }
         if (eta_n[v] == 0.0) {
             zero_src[v] = 1;
             done[v] = conv[v] = 1;

@@ -75,3 +75,22 @@ def test_escalation_of_a_batch(sloppy):
         for r in range(e.shape[0]):
             res = e[r:r + 1] - oracle.wilson(L, u, psi[r:r + 1], k)
             assert np.linalg.norm(res) <= 1.0001e-10 * np.linalg.norm(e[r:r + 1])
+
+
+def test_a_refused_source_leaves_nothing_running():
+    import torch
+
+    w = need_gpu()
+    L = (24, 24, 24, 32)
+    V = L[0] * L[1] * L[2] * L[3]
+    g = w.Gauge(L, to_dev(li.near_identity_links(L, 0.3, 45)))
+    eta = torch.ones(4 * V * 24, dtype=torch.float64, device="cuda")
+    x = torch.zeros_like(eta)
+    busy = []
+    eta[7] = float("nan")
+    for _ in range(5):
+        st, _ = w.wilson_cg(g, eta, x, 4, 0.12, 1e-8, 100, "f16", 12, check=False)
+        busy.append(not torch.cuda.current_stream().query())
+        assert st == 7  # WL_ERR_NONFINITE
+    g.close()
+    assert not any(busy)
