@@ -850,10 +850,19 @@ int plan_id(int prec, int recon, bool dag, bool clov, const Epi &e, bool red, bo
 
 // Up to this many blocks of 64 sites a set's hop is variant 11 without timing it:
 // all its blocks are resident at once, and the hop lasts as long as its chain of
-// latencies (512 blocks, FP32 16^4: 4.5 us against 7.1 for the best per-site
-// variant; 32 blocks: 3.5 against 6.6; 12 RHS of 8^4, 384 blocks: 4.4 against 10.6;
-// at 1024 blocks FP64 already loses, 14.9 against 13.7).  Timed from the host,
-// launches this short cannot be told apart.
+// latencies.  Against the best per-site variant, us: 512 blocks (16^4) FP64 recon-18
+// 9.4 and 10.4, FP32 4.6 and 6.3, FP16 4.7 and 5.5, BF16 4.5 and 5.9; 144 blocks 5.1
+// and 7.5, 3.8 and 5.6, 4.1 and 5.4, 4.0 and 5.7; with reductions, an iteration of
+// CGNR at 512 blocks FP64 78.4 and 79.0, FP32 48.4 and 49.5, FP16 49.6 and 50.2, with a
+// clover term FP16 54.6 and 55.1; 12 RHS of 8^4 (384 blocks, FP32) 4.4 and 10.6; at 576
+// blocks FP64 already loses, 12.6 and 11.5.  Timed from the host, launches this short
+// cannot be told apart.
+// A launch of both parities counts the blocks of one: FP64 operator at 512 24.2 and
+// 23.8, FP32 18.6 and 20.1, FP16 16.8 and 17.7, FP64 sign function (a pair of hops) 19.4
+// and 22.4.  Not with a clover term, where the finishing waves' rows of A take longer
+// than the chain once blocks queue: it wins at 256 (FP64 17.8 and 20.5, FP32 16.9 and
+// 19.3, FP16 15.5 and 17.2) and loses at 448 (FP16 19.4 and 18.5, BF16 19.6 and 18.8) and
+// 512 (19.9 and 18.8, 20.1 and 19.1), so that launch counts both parities' blocks.
 constexpr int kSplitBlocks = 512;
 static bool split_untimed(const ExecSet &S)
 {
@@ -1140,7 +1149,8 @@ wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], co
         return r != hipSuccess ? r : launch_hop(prec, recon, dag, clov, var, mk(L, 1), B, s);
     };
     ExecSet::HopPlan pl{};
-    WL_TRY(hop_plan(S, plan_id(prec, recon, dag, clov, e[0], false, true), e[0].canon_in != nullptr, true, &pl, s,
+    const bool untimed = !clov || 2 * blocks64(S) <= kSplitBlocks;
+    WL_TRY(hop_plan(S, plan_id(prec, recon, dag, clov, e[0], false, true), e[0].canon_in != nullptr, untimed, &pl, s,
                     [&]() {
                         return hop_key(S, prec, recon, dag) + (clov ? "/clov" : "") + "/twin/x" +
                                std::to_string(e[0].nx) + (e[0].canon ? "/canon" : "");

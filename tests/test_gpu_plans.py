@@ -70,3 +70,24 @@ def test_bench_dslash_times_the_hops_configuration(capfd, monkeypatch):
         assert w.wl_bench_dslash(g, prec, recon, 1, 0, 1, 10) > 0
     g.close()
     assert "[wl tune]" not in capfd.readouterr().err
+
+
+@pytest.mark.parametrize("L,nrhs,tuned", [((8, 8, 8, 8), 8, 0), ((8, 8, 8, 8), 9, 1), ((16, 16, 16, 16), 1, 1)])
+def test_clover_operator_counts_both_parities(L, nrhs, tuned, capfd, monkeypatch):
+    """256, 288 and 512 blocks of 64 sites a parity: one launch of both takes variant
+    11 without the tuner up to 512 blocks in all; the Wilson operator counts one parity."""
+    import torch
+
+    w = need_gpu()
+    monkeypatch.setenv("WL_DEBUG", "1")
+    V = L[0] * L[1] * L[2] * L[3]
+    gen = torch.Generator(device="cuda").manual_seed(37)
+    psi = torch.randn(nrhs * V * 24, generator=gen, dtype=torch.float64, device="cuda")
+    out = torch.empty_like(psi)
+    g = w.Gauge(L, to_dev(li.near_identity_links(L, 0.3, 36)))
+    capfd.readouterr()
+    w.wilson_dslash(g, psi, out, nrhs, 0.12, -1, 0, "f16", 12)
+    assert capfd.readouterr().err.count("[wl tune]") == 0
+    w.wilson_clover_dslash(g, psi, out, nrhs, 0.12, 1.0, 0, "f16", 12)
+    assert capfd.readouterr().err.count("[wl tune]") == tuned
+    g.close()
