@@ -55,6 +55,8 @@
  *                        variant v with block size b (column height c, 4 by
  *                        default, plus 256 n for time groups 2^n times as
  *                        long) -- for tests of each variant
+ *   WL_CHUNK=k           solver chunks of k iterations (1 to 64) instead of the
+ *                        length that the convergence rate suggests -- for tests
  *   WL_GRAPHS=0          solver iteration chunks launched kernel by kernel
  *                        instead of replayed from captured HIP graphs
  *   WL_STREAM_FIELDS=0|1 force the solver kernels' non-temporal field access

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) void k_r_update(BlasArgs a)
     const T al = (T)(a.fold.vec ? fold_alpha(a.fold, vi, bm.lblk) : a.s0[vi]);
     if (live) {
 #pragma unroll
-        for (int k = 0; k < 24; ++k) r[k] -= al * q[k];
+        for (int k = 0; k < 24; ++k) r[k] = fmadd(-al, q[k], r[k]);
         // r is the neighbour input of the next hop (of M^+)
         store_spinor<P, kNextHopNT<P, NT>>(vbase<P>(a.f[0], vd), nbase(a.fn[0], vd), sd.stride, cb, r);
         nrm = site_norm2(r);
@@ -142,8 +142,8 @@ __global__ __launch_bounds__(256) void k_xpay_x(BlasArgs a)
     if (!live) return;
 #pragma unroll
     for (int k = 0; k < 24; ++k) {
-        x[k] += al * p[k];
-        p[k] = s[k] + be * p[k];
+        x[k] = fmadd(al, p[k], x[k]);
+        p[k] = fmadd(be, p[k], s[k]);
     }
     store_spinor<P, NT>(vbase<P>(a.f[2], vd), nbase(a.fn[2], vd), sd.stride, cb, x);
     // p is the neighbour input of the next hop (of M)
@@ -152,7 +152,9 @@ __global__ __launch_bounds__(256) void k_xpay_x(BlasArgs a)
 
 // The same step of two iterations with one pass over x: the first only forms the
 // new direction, beside the old one, and the second adds both directions to x.
-// Nine field passes instead of ten: at 32^3x64 in FP16 85 us instead of 96 for the
+// The fused multiply-adds are written out: the compiler's choice of the product to
+// fuse differed between these kernels where an operand is a half-precision word
+// times its norm.  Nine field passes instead of ten: at 32^3x64 in FP16 85 us instead of 96 for the
 // pair, at 24^3x48 in FP32 with 12 sources 594 instead of 658.
 template <int P, bool ONE = false, bool NT = false>
 __global__ __launch_bounds__(256) void k_xpay_1(BlasArgs a)
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(256) void k_xpay_1(BlasArgs a)
     if (bm.lblk == 0 && threadIdx.x == 0) a.fold.sc[SC_ALPP * a.nvec + vi] = al;
     if (!live) return;
 #pragma unroll
-    for (int k = 0; k < 24; ++k) p[k] = s[k] + be * p[k];
+    for (int k = 0; k < 24; ++k) p[k] = fmadd(be, p[k], s[k]);
     store_spinor<P, kNextHopNT<P, NT>>(vbase<P>(a.f[0], vd), nbase(a.fn[0], vd), sd.stride, cb, p);
 }
 
@@ -189,12 +191,12 @@ __global__ __launch_bounds__(256) void k_xpay_2(BlasArgs a)
     const T be = (T)(a.fold.vec ? fold_beta(a.fold, vi, bm.lblk) : a.s0[vi]);
     if (!live) return;
 #pragma unroll
-    for (int k = 0; k < 24; ++k) x[k] += al1 * p[k];
+    for (int k = 0; k < 24; ++k) x[k] = fmadd(al1, p[k], x[k]);
     round_spinor<P>(x);  // the iterates of the one-by-one form, which decide when a solve restarts
 #pragma unroll
     for (int k = 0; k < 24; ++k) {
-        x[k] += al * p2[k];
-        p[k] = s[k] + be * p2[k];
+        x[k] = fmadd(al, p2[k], x[k]);
+        p[k] = fmadd(be, p2[k], s[k]);
     }
     store_spinor<P, NT>(vbase<P>(a.f[2], vd), nbase(a.fn[2], vd), sd.stride, cb, x);
     store_spinor<P, kNextHopNT<P, NT>>(vbase<P>(a.f[0], vd), nbase(a.fn[0], vd), sd.stride, cb, p);

@@ -455,6 +455,8 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
     cg.sloppy = sloppy;
     const char *ge = getenv("WL_GRAPHS");
     cg.use_graphs = !(ge && ge[0] == '0');
+    const char *ce = getenv("WL_CHUNK");
+    const int fixed = ce && atoi(ce) >= 1 && atoi(ce) <= ExecSet::kHist ? atoi(ce) : 0;
     const bool trace = getenv("WL_DEBUG") != nullptr;  // per-chunk solver trace on stderr
     WL_TRY(cg.setup());
     const int nv = S.nvec;
@@ -543,7 +545,7 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
             for (int v = 0; v < nv; ++v) start[v] = !done[v];
             WL_TRY(cg.refresh(none, start));
         }
-        int k = 4;
+        int k = fixed ? fixed : 4;
         bool first = true;
         // FP16/BF16 recurrences drift faster: shorter chunks, so updates are not late
         auto kmax = [&]() { return cg.sloppy == P_F16 || cg.sloppy == P_BF16 ? 8.0 : 32.0; };
@@ -775,7 +777,9 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
             if (!left) break;
             WL_TRY(S.upload_active(s));
             // next chunk spans about one reliable-update interval (less in half precision)
-            if (nrate > 0 && rate / nrate > 1e-3) {
+            if (fixed) {
+                k = fixed;
+            } else if (nrate > 0 && rate / nrate > 1e-3) {
                 const double want = kfrac() * std::log10(1.0 / delta) / (rate / nrate);
                 k = round_chunk(std::min(kmax(), std::max(2.0, want)));
             } else {
