@@ -57,6 +57,9 @@
  *                        long) -- for tests of each variant
  *   WL_CHUNK=k           solver chunks of k iterations (1 to 64) instead of the
  *                        length that the convergence rate suggests -- for tests
+ *   WL_KEEP_RESIDUAL=1   solvers store the FP64 residual of every update and
+ *                        convert it -- for tests (by default the hop rounds it
+ *                        to the sloppy precision where nothing else reads it)
  *   WL_GRAPHS=0          solver iteration chunks launched kernel by kernel
  *                        instead of replayed from captured HIP graphs
  *   WL_STREAM_FIELDS=0|1 force the solver kernels' non-temporal field access
@@ -66,7 +69,7 @@
  *                        it returns WL_ERR_HIP (default 600)
  *   WL_DEBUG=1           tuner choices and a per-chunk solver trace on stderr
  * None of them changes a result beyond floating-point rounding order:
- * WL_GRAPHS and WL_STREAM_FIELDS give bit-identical solves; a launch
+ * WL_GRAPHS, WL_STREAM_FIELDS and WL_KEEP_RESIDUAL give bit-identical solves; a launch
  * configuration can change the grouping of the reductions' partial sums.
  */
 #ifndef WILSON_MI355X_H

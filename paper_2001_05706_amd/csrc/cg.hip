@@ -455,8 +455,9 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
     cg.sloppy = sloppy;
     const char *ge = getenv("WL_GRAPHS");
     cg.use_graphs = !(ge && ge[0] == '0');
-    const char *ce = getenv("WL_CHUNK");
+    const char *ce = getenv("WL_CHUNK"), *ke = getenv("WL_KEEP_RESIDUAL");
     const int fixed = ce && atoi(ce) >= 1 && atoi(ce) <= ExecSet::kHist ? atoi(ce) : 0;
+    const bool keep_all = ke && ke[0] == '1';
     const bool trace = getenv("WL_DEBUG") != nullptr;  // per-chunk solver trace on stderr
     WL_TRY(cg.setup());
     const int nv = S.nvec;
@@ -683,7 +684,7 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                 WL_TRY(S.upload_active(s));
                 // where the precision may be raised (a second stall in a row, or a
                 // non-finite iterate) the residual is kept in FP64: a raise starts from it
-                bool keep = anybad || cg.sloppy == P_F64;
+                bool keep = keep_all || anybad || cg.sloppy == P_F64;
                 for (int v = 0; v < nv; ++v) keep = keep || (upd[v] && stall[v] > 0);
                 WL_TRY(cg.residual64(!keep));
                 // every updated vector that goes on (continued or restarted) needs

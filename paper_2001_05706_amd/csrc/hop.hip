@@ -118,9 +118,13 @@ __device__ __forceinline__ void store_lo(const HopArgs &a, const VecDesc &vd, co
         store_spinor<P_F32>((float4 *)a.lo + (size_t)vd.site_off * 6, nullptr, sd.stride, cb, y);
     } else {
         uint4 *base = (uint4 *)a.lo + (size_t)vd.site_off * 3;
-        if (a.lo_prec == P_F16)
+        if (a.lo_prec == P_F16) {
+            // FP16 rounds the exact product y / m once, BF16 the FP32 product: kept
+            // apart, or the compiler forms products for both ahead of the branch
+#pragma unroll
+            for (int k = 0; k < 24; ++k) asm("" : "+v"(y[k]));
             store_spinor<P_F16>(base, a.lo_norm + vd.site_off, sd.stride, cb, y);
-        else
+        } else
             store_spinor<P_BF16>(base, a.lo_norm + vd.site_off, sd.stride, cb, y);
     }
 }

@@ -1,5 +1,6 @@
 """Forms of one solver step that must give the same bits: the solution updated in
-each iteration and once for two, at chunk lengths that end in either."""
+each iteration and once for two, at chunk lengths that end in either; the FP64
+residual rounded by its hop and stored and converted."""
 import numpy as np
 import pytest
 
@@ -65,3 +66,21 @@ def test_four_launch_iteration_at_every_chunk_end(prec, tol, k, monkeypatch):
     assert a[1] == b[1] and {i for i, _ in a[1]} == {0, (10 + k - 1) // k * k}
     for x, y in zip(a[0], b[0]):
         assert np.linalg.norm(x - y) <= tol * np.linalg.norm(y)
+
+
+@pytest.mark.parametrize("cfg", ["3:256", "0:64", "11:64"])
+@pytest.mark.parametrize("prec,recon", [("f32", 18), ("f32", 12), ("f16", 12), ("bf16", 12)])
+@pytest.mark.parametrize("method,csw", [("multi", None), ("wilson_bicgstab", None), ("wilson_clover_cg", 1.0)])
+def test_residual_rounded_in_the_hop(prec, recon, method, csw, cfg, monkeypatch):
+    """(variant 11 rounds to FP32 only: half precision keeps the other configurations)"""
+    if cfg == "11:64" and prec in ("f16", "bf16"):
+        pytest.skip("not a candidate: the tuner would choose")
+    w = need_gpu()
+    monkeypatch.setenv("WL_TUNE_FORCE", cfg)
+    runs = []
+    for keep in "01":
+        monkeypatch.setenv("WL_KEEP_RESIDUAL", keep)
+        runs.append(solve(w, method, prec, recon, 1e-10, 500, 0.1, csw))
+    assert runs[0][1] == runs[1][1] and max(u for _, u in runs[0][1]) >= 3
+    for a, b in zip(runs[0][0], runs[1][0]):
+        assert np.array_equal(a.view(np.float64), b.view(np.float64))
