@@ -51,10 +51,11 @@
  *
  * Environment (read at each call; none is needed for normal use):
  *   WL_TUNE=0            no autotuning: every hop runs 256-thread blocks
- *   WL_TUNE_FORCE=v:b[:c] pin the hop launches whose tuner candidates hold
- *                        variant v with block size b (column height c, 4 by
- *                        default, plus 256 n for time groups 2^n times as
- *                        long) -- for tests of each variant
+ *   WL_TUNE_FORCE=v:b[:c[:s]] pin the hop launches whose tuner candidates hold
+ *                        variant v with block size b -- for tests of each
+ *                        variant (c: column height, 4 by default and 255 at most,
+ *                        plus 256 n for time groups 2^n times as long; s = 1:
+ *                        whole-lattice operators in two launches)
  *   WL_CHUNK=k           solver chunks of k iterations (1 to 64) instead of the
  *                        length that the convergence rate suggests -- for tests
  *   WL_KEEP_RESIDUAL=1   solvers store the FP64 residual of every update and

@@ -135,15 +135,16 @@ int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream
                 const std::function<hipError_t(int)> &run, bool *settled)
 {
     if (settled) *settled = false;
-    // WL_TUNE_FORCE=<variant>:<block>[:<column height>] pins every hop launch
-    // whose candidates hold that variant and block size (tests of each
-    // variant; column height 4 by default, any height >= 1 accepted)
+    // WL_TUNE_FORCE=<variant>:<block>[:<column>[:<split>]] pins every hop launch whose
+    // candidates hold that variant and block size (tests of each variant); column: a
+    // block order of col_make, heights of 1 to 255 (default 4); split 1: whole-lattice
+    // operators take their parities in two launches
     const char *force = getenv("WL_TUNE_FORCE");
     if (force && key.compare(0, 4, "hop/") == 0) {
-        int v = -1, b = -1, col = 4;
-        if (sscanf(force, "%d:%d:%d", &v, &b, &col) >= 2 && col >= 1 && col < 4096)
+        int v = -1, b = -1, col = 4, split = 0;
+        if (sscanf(force, "%d:%d:%d:%d", &v, &b, &col, &split) >= 2 && col >= 1 && col < 4096)
             for (int x : cands)
-                if (cfg_var(x) == v && cfg_block(x) == b) return cfg_make(v, b, col);
+                if (cfg_var(x) == v && cfg_block(x) == b) return cfg_make(v, b, col) | (split == 1 ? kCfgSplit : 0);
     }
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -729,8 +730,6 @@ int cfg_make(int var, int block, int col) { return var | (block << 4) | (col << 
 int cfg_var(int c) { return c & 15; }
 int cfg_block(int c) { return (c >> 4) & 4095; }
 int cfg_col(int c) { return (c >> 16) & 4095; }
-// whole-lattice operators (hop2): the parities in two launches instead of one
-constexpr int kCfgSplit = 1 << 29;
 
 // Candidate configurations: every variant x block size x column height of 4 or
 // 16 z-planes, for several right-hand sides also columns of 4 along all of t and

@@ -338,6 +338,7 @@ bool capturing(hipStream_t s);
 int plan_id(int prec, int recon, bool dag, bool clov, const Epi &e, bool red, bool twin);
 std::string hop_key(const ExecSet &S, int prec, int recon, bool dag);
 std::vector<int> hop_candidates(int prec, bool many);  // many: several right-hand sides
+constexpr int kCfgSplit = 1 << 29;  // whole-lattice operators (hop2): the parities in two launches instead of one
 int cfg_make(int var, int block, int col);  // hop launch configuration: variant, block size, column height
 int cfg_var(int c);
 int cfg_block(int c);

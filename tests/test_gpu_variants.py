@@ -240,3 +240,31 @@ def test_pencil_variant_two_systems(second, force):
         for r in range(e.shape[0]):
             tr = np.linalg.norm(e[r] - oracle.wilson(L, U, p[r], kappa)) / np.linalg.norm(e[r])
             assert tr <= 1e-10, (second, L, r, tr)
+
+
+@pytest.mark.parametrize("cfg", ["3:256:772", "3:256:518", "8:256:772", "7:128:518", "6:256:772:1", "3:64:4:1",
+                                 "8:768:518:1", "11:64:4:1", "9:128:772", "10:256:518:1"])
+def test_block_orders_and_split_launches_leave_the_same_bits(cfg, monkeypatch):
+    """Columns of 4 in time groups of 8 times the length (772 = 4 + 3 * 256), of 6 in
+    groups of 4 times (518 = 6 + 2 * 256), and whole-lattice operators in two launches,
+    against variant 3 in the plain order: same D-slash and sign function bit for bit.
+    (The pinned configuration replaces the tuner where it is a candidate, else both
+    runs are the tuner's.)"""
+    w = need_gpu()
+    L = (8, 4, 4, 16)  # time slices of 64 sites
+    U, psi = li.haar_links(L, 47), li.gaussian_spinor(L, 48, nrhs=1 if cfg[0] in "9" or cfg[:2] == "10" else 5)
+    n = psi.shape[0]
+    for prec, recon in CASES:
+        res = []
+        for c in ("3:256", cfg):
+            monkeypatch.setenv("WL_TUNE_FORCE", c)
+            out = [run_dslash(w, L, U, psi, 0.13, p, d, prec, recon) for p, d in [(0, 0), (-1, 0), (-1, 1)]]
+            if prec in ("f64", "f32"):
+                g = w.Gauge(L, to_dev(U))
+                o = to_dev(np.zeros_like(psi))
+                w.overlap_sign_cheb(g, to_dev(psi), o, n, 1.5, 8, 0.003, 1.0, 42.25, prec, recon)
+                out.append(from_dev(o, psi.shape))
+                g.close()
+            res.append(out)
+        for a, b in zip(*res):
+            assert np.array_equal(a.view(np.float64), b.view(np.float64)), (prec, recon)
