@@ -89,3 +89,34 @@ def test_routes_agree(L, prec, csw, monkeypatch):
             out.append(o.cpu().numpy())
             g.close()
         assert np.array_equal(out[0], out[1]), (parity, dagger)
+
+
+@pytest.mark.parametrize("L", SHAPES)
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16", "bf16"])
+@pytest.mark.parametrize("parity", [-1, 0, 1])
+def test_unpack(L, prec, parity):
+    """The unpacking kernels, which wilson_dslash_noalloc still uses, on pointers
+    aligned to a double: both parities of a packed field with kappa = 0 (the input as
+    storage leaves it), or one parity, as the call that stores the canonical field in
+    the hop gives it, and zeros on the other."""
+    w = need_gpu()
+    import torch
+
+    nrhs = 2
+    psi = li.gaussian_spinor(L, 17, nrhs=nrhs)
+    n = psi.size * 2
+    inp = torch.zeros(n + 1, dtype=torch.float64, device="cuda")[1:]
+    out = torch.full((n + 3,), float("nan"), dtype=torch.float64, device="cuda")
+    ref = torch.full((n,), float("nan"), dtype=torch.float64, device="cuda")
+    inp.copy_(torch.from_numpy(psi.view(np.float64).reshape(-1)))
+    g = w.Gauge(L, to_dev(li.haar_links(L, 18)))
+    w.wilson_dslash_noalloc(g, inp, out[1:1 + n], nrhs, 0.0, parity, 0, prec, 12)
+    w.wilson_dslash(g, inp, ref, nrhs, 0.0, parity, 0, prec, 12)
+    got, want = out.cpu().numpy(), ref.cpu().numpy()
+    assert np.array_equal(got[1:1 + n], want)
+    if parity < 0:
+        q = psi.astype(np.complex64).astype(np.complex128) if prec == "f32" else psi
+        q = quantize_spinor(psi, prec) if prec in ("f16", "bf16") else q
+        assert np.array_equal(want, q.view(np.float64).reshape(-1))
+    assert np.isnan(got[0]) and np.isnan(got[1 + n:]).all()  # nothing written outside the field
+    g.close()
