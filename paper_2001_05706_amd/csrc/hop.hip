@@ -49,7 +49,7 @@ namespace wl {
 //      slices hold a multiple of 64 sites)
 //  11: the eight directions of 64 sites on the eight waves of a block (k_hop_split)
 // Variants 4 and 5 exist for FP16/BF16 storage only (FP32 and FP64 operands of
-// four directions do not fit the registers); for those they repeat variant 3.
+// four directions do not fit the registers).
 template <int SP, int VAR> struct HopVar {
     static constexpr bool half = SP == P_F16 || SP == P_BF16;
     static constexpr int fence = VAR == 0 || VAR == 3 || VAR == 6 || VAR == 9
@@ -657,7 +657,6 @@ template <int SP> struct SplitHop {
     static constexpr int per_wave = half ? 8 : 4;   // reals of a site that one wave finishes: whole chunk rows
     static constexpr int finishers = 24 / per_wave;
     static constexpr int buf = 8 * rows * 64;       // T's of the products
-    static constexpr int canon_row = sizeof(T) == 4 ? 24 : 26;
     static constexpr int waves = SP == P_F64 ? 4 : 8;  // per SIMD
 };
 
@@ -693,20 +692,11 @@ __device__ __forceinline__ void split_store(void *base, int stride, int cb, int 
     }
 }
 
-// U P v of direction MU, DIR for a neighbour's FP32 or FP64 spinor v
-template <int SP, int MU, int DIR, bool DAG, class T>
-__device__ __forceinline__ void split_multiply(const T v[24], bool flip, const cpx<T> u[3][3], T *out)
+// The products U h0, U h1 (U^+ for DIR < 0) into the lane's column of `out`
+template <int DIR, class T>
+__device__ __forceinline__ void split_put(const cpx<T> u[3][3], const cpx<T> h0[3], const cpx<T> h1[3], T *out)
 {
-    constexpr int SG = (DIR > 0) == DAG ? +1 : -1;
-    cpx<T> h0[3], h1[3], g[3];
-    project<MU, SG>(v, h0, h1);
-    if (flip) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            h0[c] = {-h0[c].re, -h0[c].im};
-            h1[c] = {-h1[c].re, -h1[c].im};
-        }
-    }
+    cpx<T> g[3];
     su3_mul<(DIR < 0), T>(u, h0, g);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -719,6 +709,30 @@ __device__ __forceinline__ void split_multiply(const T v[24], bool flip, const c
         out[(6 + 2 * c) * 64] = g[c].re;
         out[(7 + 2 * c) * 64] = g[c].im;
     }
+}
+
+// The projected spinor of a neighbour's FP32 or FP64 one, negated behind an antiperiodic boundary
+template <int MU, int SG, class T>
+__device__ __forceinline__ void split_project(const T v[24], bool flip, cpx<T> h0[3], cpx<T> h1[3])
+{
+    project<MU, SG>(v, h0, h1);
+    if (flip) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            h0[c] = {-h0[c].re, -h0[c].im};
+            h1[c] = {-h1[c].re, -h1[c].im};
+        }
+    }
+}
+
+// U P v of direction MU, DIR for a neighbour's FP32 or FP64 spinor v
+template <int SP, int MU, int DIR, bool DAG, class T>
+__device__ __forceinline__ void split_multiply(const T v[24], bool flip, const cpx<T> u[3][3], T *out)
+{
+    constexpr int SG = (DIR > 0) == DAG ? +1 : -1;
+    cpx<T> h0[3], h1[3];
+    split_project<MU, SG>(v, flip, h0, h1);
+    split_put<DIR>(u, h0, h1, out);
 }
 
 // Site `lex` of the canonical field `base`, rounded as packing it rounds: FP64 and
@@ -746,7 +760,7 @@ __device__ __forceinline__ void split_product(const SysDesc &sd, const HopSite &
     constexpr int SG = (DIR > 0) == DAG ? +1 : -1;
     bool flip;
     const int ncb = neighbour<MU, DIR>(sd, st, cb, flip);
-    cpx<T> h0[3], h1[3], g[3], u[3][3];
+    cpx<T> h0[3], h1[3], u[3][3];
     T f;
     if constexpr (DIRECT) {
         // the neighbour is the site of its pair with the x of its own parity
@@ -759,32 +773,14 @@ __device__ __forceinline__ void split_product(const SysDesc &sd, const HopSite &
             project_half<SP, MU, SG>(q, h0, h1);
             f = (flip ? -m : m) * (T)hs.scale;
         } else {
-            project<MU, SG>(v, h0, h1);
-            if (flip) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    h0[c] = {-h0[c].re, -h0[c].im};
-                    h1[c] = {-h1[c].re, -h1[c].im};
-                }
-            }
+            split_project<MU, SG>(v, flip, h0, h1);
             f = 1;
         }
     } else {
         f = project_neighbour<SP, MU, SG>(hs, ncb, flip, h0, h1);
         hop_link<GP, R, MU, DIR, false>(hs, parity, cb, ncb, u);
     }
-    su3_mul<(DIR < 0), T>(u, h0, g);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        out[(2 * c) * 64] = g[c].re;
-        out[(2 * c + 1) * 64] = g[c].im;
-    }
-    su3_mul<(DIR < 0), T>(u, h1, g);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        out[(6 + 2 * c) * 64] = g[c].re;
-        out[(7 + 2 * c) * 64] = g[c].im;
-    }
+    split_put<DIR>(u, h0, h1, out);
     if constexpr (SplitHop<SP>::half) out[12 * 64] = f;
 }
 
@@ -1147,7 +1143,7 @@ void k_hop_split(HopArgs a)
         const unsigned long long slots = __ballot(st.x & 1);  // the same in every wave
         if (w < S::finishers) {
 #pragma unroll
-            for (int i = 0; i < PW; ++i) site[lane * S::canon_row + w * PW + i] = o[i];
+            for (int i = 0; i < PW; ++i) site[lane * kStageRow<T> + w * PW + i] = o[i];
         }
         __syncthreads();
         const int ns = min(64, sd.Vh - bm.lblk * 64);
@@ -1158,7 +1154,7 @@ void k_hop_split(HopArgs a)
                 const int e = i * 512 + (int)threadIdx.x, j = e / 24, r = e % 24;
                 const int k = r < 12 ? r : r - 12;
                 const bool mine = (int)((slots >> j) & 1) == (r >= 12);
-                const T *p = site + j * S::canon_row + 2 * k;
+                const T *p = site + j * kStageRow<T> + 2 * k;
                 if (j < ns) st_canon(base + 2 * e, mine ? (double)p[0] : 0.0, mine ? (double)p[1] : 0.0);
             }
         } else {
@@ -1166,7 +1162,7 @@ void k_hop_split(HopArgs a)
             for (int i = 0; i < 2; ++i) {
                 const int e = i * 512 + (int)threadIdx.x, j = e / 12, k = e % 12;
                 if (j < ns) {
-                    const T *p = site + j * S::canon_row + 2 * k;
+                    const T *p = site + j * kStageRow<T> + 2 * k;
                     st_canon(base + 48 * j + 24 * (int)((slots >> j) & 1) + 2 * k, (double)p[0], (double)p[1]);
                 }
             }
@@ -1374,7 +1370,7 @@ template <int SP, int GP, int R, int EP>
 static hipError_t launch_hop_split(bool dag, const HopArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
     using S = SplitHop<SP>;
-    const unsigned lds = (unsigned)(S::buf + (EP != EP_WILSON ? 64 * S::canon_row : 0)) * (unsigned)sizeof(typename S::T);
+    const unsigned lds = (unsigned)(S::buf + (EP != EP_WILSON ? 64 * kStageRow<typename S::T> : 0)) * (unsigned)sizeof(typename S::T);
     if (dag)
         dispatch(k_hop_split<SP, GP, R, true, EP>, a, 512, s, e0, e1, lds);
     else
@@ -1393,10 +1389,16 @@ hipError_t launch_hop_t(int var, bool dag, bool clov, const HopArgs &a, int bloc
     case 1: return launch_hop_v<SP, GP, R, 1>(dag, clov, a, block, s, e0, e1);
     case 2: return launch_hop_v<SP, GP, R, 2>(dag, clov, a, block, s, e0, e1);
     case 3: return launch_hop_v<SP, GP, R, 3>(dag, clov, a, block, s, e0, e1);
-    case 4: return launch_hop_v<SP, GP, R, 4>(dag, clov, a, block, s, e0, e1);
-    case 5: return launch_hop_v<SP, GP, R, 5>(dag, clov, a, block, s, e0, e1);
+    case 4:
+        if constexpr (SplitHop<SP>::half) return launch_hop_v<SP, GP, R, 4>(dag, clov, a, block, s, e0, e1);
+        return hipErrorInvalidValue;
+    case 5:
+        if constexpr (SplitHop<SP>::half) return launch_hop_v<SP, GP, R, 5>(dag, clov, a, block, s, e0, e1);
+        return hipErrorInvalidValue;
     case 6: return launch_hop_v<SP, GP, R, 6>(dag, clov, a, block, s, e0, e1);
-    case 7: return launch_hop_v<SP, GP, R, 7>(dag, clov, a, block, s, e0, e1);
+    case 7:
+        if constexpr (SP != P_F64) return launch_hop_v<SP, GP, R, 7>(dag, clov, a, block, s, e0, e1);
+        return hipErrorInvalidValue;
     case 8:
         if constexpr (SP != P_F64) {
             if (clov || block % 64 != 0 || block > 1024) return hipErrorInvalidValue;
@@ -1470,8 +1472,14 @@ WL_HOP_EXTERN(P_F16, P_F16, 12);
 WL_HOP_EXTERN(P_BF16, P_BF16, 12);
 #undef WL_HOP_EXTERN
 
-// (FP64 has no variants 8-10, which stage FP32 or half-precision data in LDS)
-bool hop_has_variant(int prec, int var) { return var >= 0 && var < kHopVariants && !(prec == P_F64 && var >= 8 && var <= 10); }
+// 4 and 5 are for half precision; FP64 has no variants 8-10, which stage FP32 or
+// half-precision data in LDS, and no 7: its two FP64 accumulators fit only at 2 waves
+// per SIMD (12-RHS recon-12 D-slash 700 us against 672 for variants 3 and 6)
+bool hop_has_variant(int prec, int var)
+{
+    if (var == 4 || var == 5) return prec == P_F16 || prec == P_BF16;
+    return var >= 0 && var < kHopVariants && !(prec == P_F64 && var >= 7 && var <= 10);
+}
 int hop_variants() { return kHopVariants; }
 
 hipError_t launch_hop(int prec, int recon, bool dag, bool clov, int var, const HopArgs &a, int block, hipStream_t s,

@@ -739,22 +739,17 @@ int cfg_col(int c) { return (c >> 16) & 4095; }
 // changes little)
 std::vector<int> hop_candidates(int prec, bool many)
 {
-    const bool half = prec == P_F16 || prec == P_BF16;
     std::vector<int> c, cols = {4, 16};
     if (many) cols.insert(cols.end(), {col_make(4, 3), col_make(6, 2)});
     for (int col : cols)
         for (int v = 0; v < hop_variants(); ++v) {
             if (!hop_has_variant(prec, v)) continue;
-            if ((v == 4 || v == 5) && !half) continue;  // four directions in flight: half precision only
             // variants 6 and 8: 4 or 8 (8: also 12 or 16) right-hand sides per block
             if (v == 6 || v == 8) {
                 for (int b : {256, 512, 768, 1024})
                     if (v == 8 || b <= 512) c.push_back(cfg_make(v, b, col));
                 continue;
             }
-            // two FP64 accumulators fit only at 2 waves per SIMD, where variant 7 measured
-            // slower than 3 and 6 (12-RHS recon-12 D-slash: 700 us against 672 us)
-            if (v == 7 && prec == P_F64) continue;
             // pencil blocks of 2, 4 or 8 time slices
             if (v == 9 || v == 10) {
                 for (int b : {128, 256, 512}) c.push_back(cfg_make(v, b, col));
