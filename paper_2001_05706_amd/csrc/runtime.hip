@@ -130,6 +130,7 @@ bool capturing(hipStream_t s)
 
 static std::mutex g_tune_mu;
 static std::map<std::string, int> g_tuned;
+constexpr size_t kTuneAll = 80, kTuneWide = 6, kTuneAgain = 16, kTuneFinal = 6;
 
 int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream_t s,
                 const std::function<hipError_t(int)> &run, bool *settled)
@@ -171,55 +172,68 @@ int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream
         (void)hipEventDestroy(e0);
         return fallback;
     }
-    // two sweeps over the candidates, each candidate scored by its faster sweep
-    // (a single short sweep picks among near-equal candidates by noise)
+    // Sweeps in which a candidate is launched once to warm up and then a few times
+    // between events.  Up to kTuneAll candidates (sets of one right-hand side) are all
+    // taken.  Of more, the first sweep takes every variant and block size in the plain
+    // block order, one launch for both parities, and the second the other orders and forms
+    // of the best kTuneWide of those, which they change by less than variants differ.  The
+    // best kTuneAgain of all are swept again, since one short sweep picks among near-equal
+    // ones by noise (a candidate has its faster score).  Launches of over 0.1 ms are told
+    // apart by fewer repeats.  A process's first call pays for all of them: with every
+    // candidate in two full sweeps the first 12-RHS operator at 24^3x48 took 2.5 s, the
+    // first 12-source solve there 5.4 s and the first 12-RHS sign function at 16^3x32
+    // 0.90 s; now 0.36, 2.2 and 0.14 s, in configurations of the same speed.
     std::vector<float> score(cands.size(), 1e30f);
-    for (int sweep = 0; sweep < 2; ++sweep)
-        for (size_t i = 0; i < cands.size(); ++i) {
-            const int B = cands[i];
-            if (sweep > 0 && score[i] >= 1e30f) continue;  // failed in the first sweep
-            if (run(B) != hipSuccess) {  // warm-up; a failed launch rules the candidate out
-                (void)hipGetLastError();
-                continue;
-            }
-            (void)hipEventRecord(e0, s);
-            const int reps = 3;
-            bool ok = true;
-            for (int r = 0; r < reps; ++r) ok = ok && run(B) == hipSuccess;
-            (void)hipEventRecord(e1, s);
-            (void)hipEventSynchronize(e1);
-            float ms = 0.f;
-            if (ok && hipEventElapsedTime(&ms, e0, e1) == hipSuccess) score[i] = std::min(score[i], ms);
+    float least = 1e30f;
+    int launches = 0;
+    auto time = [&](size_t i, int reps) {
+        const int c = cands[i];
+        if (run(c) != hipSuccess) {  // a failed launch rules the candidate out
+            (void)hipGetLastError();
+            return 1e30f;
         }
-    // a final round among the four best of the sweeps: three interleaved trials
+        if (least > 0.1f && least < 1e30f) reps = (reps + 1) / 2;
+        (void)hipEventRecord(e0, s);
+        bool ok = true;
+        for (int r = 0; r < reps; ++r) ok = ok && run(c) == hipSuccess;
+        (void)hipEventRecord(e1, s);
+        (void)hipEventSynchronize(e1);
+        launches += 1 + reps;
+        float ms = 0.f;
+        if (!ok || hipEventElapsedTime(&ms, e0, e1) != hipSuccess) return 1e30f;
+        least = std::min(least, ms / reps);
+        return ms / reps;
+    };
+    auto best_of = [&](size_t n) {  // the n best candidates so far
+        std::vector<size_t> v;
+        for (size_t i = 0; i < cands.size(); ++i)
+            if (score[i] < 1e30f) v.push_back(i);
+        std::sort(v.begin(), v.end(), [&](size_t x, size_t y) { return score[x] < score[y]; });
+        if (v.size() > n) v.resize(n);
+        return v;
+    };
+    auto plain = [&](size_t i) {
+        return cands.size() <= kTuneAll || (cfg_col(cands[i]) == 4 && !(cands[i] & kCfgSplit));
+    };
+    for (size_t i = 0; i < cands.size(); ++i)
+        if (plain(i)) score[i] = time(i, 3);
+    const std::vector<size_t> wide = best_of(kTuneWide);
+    for (size_t i = 0; i < cands.size(); ++i)
+        for (size_t j : wide)
+            if (!plain(i) && cfg_var(cands[i]) == cfg_var(cands[j]) && cfg_block(cands[i]) == cfg_block(cands[j]))
+                score[i] = time(i, 3);
+    for (size_t i : best_of(kTuneAgain)) score[i] = std::min(score[i], time(i, 3));
+    // a final round among the best kTuneFinal of the sweeps: three interleaved trials
     // of 8 launches each, every finalist scored by its fastest trial (3-launch
     // sweeps cannot order candidates that lie within a few per cent)
-    std::vector<size_t> top;
-    for (size_t i = 0; i < cands.size(); ++i)
-        if (score[i] < 1e30f) top.push_back(i);
-    std::sort(top.begin(), top.end(), [&](size_t x, size_t y) { return score[x] < score[y]; });
-    if (top.size() > 4) top.resize(4);
+    const std::vector<size_t> top = best_of(kTuneFinal);
     std::vector<float> fin(top.size(), 1e30f);
     for (int trial = 0; trial < 3 && top.size() > 1; ++trial)
-        for (size_t j = 0; j < top.size(); ++j) {
-            const int c = cands[top[j]];
-            if (run(c) != hipSuccess) {
-                (void)hipGetLastError();
-                continue;
-            }
-            (void)hipEventRecord(e0, s);
-            const int reps = 8;
-            bool ok = true;
-            for (int r = 0; r < reps; ++r) ok = ok && run(c) == hipSuccess;
-            (void)hipEventRecord(e1, s);
-            (void)hipEventSynchronize(e1);
-            float ms = 0.f;
-            if (ok && hipEventElapsedTime(&ms, e0, e1) == hipSuccess) fin[j] = std::min(fin[j], ms / reps);
-        }
+        for (size_t j = 0; j < top.size(); ++j) fin[j] = std::min(fin[j], time(top[j], 8));
     int best = fallback;
     float best_ms = 1e30f;
     for (size_t j = 0; j < top.size(); ++j) {
-        const float m = top.size() > 1 ? fin[j] : score[top[j]] / 3;
+        const float m = top.size() > 1 ? fin[j] : score[top[j]];
         if (m < best_ms) {
             best_ms = m;
             best = cands[top[j]];
@@ -227,7 +241,9 @@ int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    if (getenv("WL_DEBUG")) fprintf(stderr, "[wl tune] %s -> %d (%.4f ms per launch)\n", key.c_str(), best, best_ms);
+    if (getenv("WL_DEBUG"))
+        fprintf(stderr, "[wl tune] %s -> %d (%.4f ms per launch; %zu candidates, %d launches)\n", key.c_str(), best,
+                best_ms, cands.size(), launches);
     std::lock_guard<std::mutex> lk(g_tune_mu);
     g_tuned[key] = best;
     if (settled) *settled = true;
