@@ -824,9 +824,13 @@ static std::vector<int> hop_cands(const ExecSet &S, int prec, bool clov)
         const int v = cfg_var(c);
         if (clov && (v == 1 || v == 2 || (v >= 8 && v <= 10))) continue;
         if (max_nrhs < 2 && v >= 6 && v <= 8) continue;
-        // large sets of several right-hand sides: variant 11 wins the tuner's repeated
-        // launches and loses among the others (12-RHS sign function at 16^3x32, 12288
-        // blocks of 64 sites, 61.8 ms with it and 60.5 without)
+        // large sets of several right-hand sides: in the tuner's repeated launches variant
+        // 11 ties or wins, and among the others it loses (hop alone, CGNR iteration, us, 11
+        // and the best other: 16^4 x 6, 3072 blocks of 64 sites, FP32 14.6 and 13.9, 144.7
+        // and 138.1; 16^3x32 x 4, 4096, FP64 39.2 and 40.6, 316.9 and 307.5; 16^4 x 12,
+        // 6144, FP32 26.1 and 27.4, 263.4 and 252.0; 24^3x48 x 2, 10368, FP64 135.9 and
+        // 141.0, 986.7 and 967.9).  At 2048 blocks it depends (16^3x32 x 2 FP64 176.5 and
+        // 180.2, FP32 110.4 and 107.8; 8^3x16 x 32 FP32 103.7 and 100.8)
         if (v == 11 && max_nrhs > 1 && blocks64(S) > 2048) continue;
         if (v == 9 || v == 10) {
             bool ok = slices64;
@@ -840,12 +844,25 @@ static std::vector<int> hop_cands(const ExecSet &S, int prec, bool clov)
 }
 
 
-// The most block partials of a vector that a consuming update sums itself
-// instead of waiting for a finishing launch (4.5 us and its gap).  Every block of
-// the update reads all of them: with up to 2048 that hides behind its field loads
-// (CGNR: 4^4 FP64 1485 -> 1350 us, 16^3x32 FP32 4440 -> 4230, 32^3x64 FP16 33.0 ->
-// 32.8 ms); with 16384 (64-site blocks at 32^3x64) the FP16 solve took 36.8 ms.
+// A consuming update sums the block partials of a vector itself, instead of waiting for
+// a finishing launch (4.5 us and its gap), where they are few: every block of the update
+// reads all of them, which hides behind its field loads up to a point.  Iterations,
+// finishing launches against sums in the update, us: 16^3x32 (256 blocks of the update),
+// 256 partials, CGNR FP32 72.7 and 69.6, FP16 59.3 and 56.4, BiCGStab FP16 82.7 and 76.4;
+// 24^3x48 (1296 blocks), 1296 partials, 265.8 and 259.7, 167.2 and 164.2, 207.2 and 204.7;
+// 5184 partials 257.9 and 258.3, 167.6 and 171.7, 207.6 and 210.8; 32^3x64 (4096 blocks),
+// 1024 partials 841 and 830, 459.5 and 459.7, 577 and 586; 2048 partials 849 and 852, 457
+// and 461, 577 and 588; 16384 partials 850 and 928, 459 and 516, 579 and 678.  So the line
+// is on the reads, partials times blocks: below 4 M it pays in every format and solver
+// (kFoldPartials bounds the serial part, the loop of one block).
 constexpr int kFoldPartials = 2048;
+constexpr size_t kFoldReads = (size_t)1 << 22;
+static bool fold_pays(const ExecSet &S, const Layout &L)
+{
+    int update = 0;  // blocks of an update of the largest vector
+    for (auto &e : S.systems) update = std::max(update, (e.g->geom.Vh + kBlasBlock - 1) / kBlasBlock);
+    return L.max_nblk <= kFoldPartials && (size_t)L.max_nblk * update < kFoldReads;
+}
 
 static Fold fold_of(const ExecSet &S, const Layout *L)
 {
@@ -1037,7 +1054,7 @@ wl_status hop(ExecSet &S, int prec, int recon, bool dag, int par, const Field &o
     }
     // few partials are summed by the kernel that needs the scalar, in each of its
     // blocks while its field loads are under way
-    S.fold = red.kind != RED_NONE && red.defer == 2 && L->max_nblk <= kFoldPartials ? L : nullptr;
+    S.fold = red.kind != RED_NONE && red.defer == 2 && fold_pays(S, *L) ? L : nullptr;
     if (red.kind != RED_NONE && !S.fold)
         WL_HIP(launch_red_finalize(red, L->d_vec, use_active ? S.d_active : nullptr, S.nvec, s));
     return WL_OK;
