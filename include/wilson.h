@@ -339,8 +339,11 @@ wl_status wl_bench_copy(int64_t bytes, int32_t reps, int32_t mode, double *secon
  * start/end HIP events that the dispatch itself records (dispatch to
  * completion), and its blocks store readings of the device's constant-rate
  * steady clock at their start and end, whose span (first block start to last
- * block end) is the kernel's own duration.  Solvers run without graphs while
- * timing is on.  wl_prof_read returns launches, total event milliseconds,
+ * block end) is the kernel's own duration.  While timing is on, solvers run
+ * without graphs, small CGNR solves in the six-launch iteration, and
+ * whole-lattice operators in one launch a parity: hop launches of one
+ * parity, in the configurations those forms are tuned to, are what it
+ * times.  wl_prof_read returns launches, total event milliseconds,
  * algorithmic GB and total kernel milliseconds of the timed launches since
  * the last read and resets the counters. */
 wl_status wl_prof_enable(int32_t on);

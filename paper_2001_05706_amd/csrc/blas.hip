@@ -154,8 +154,8 @@ __global__ __launch_bounds__(256) void k_xpay_x(BlasArgs a)
 // new direction, beside the old one, and the second adds both directions to x.
 // The fused multiply-adds are written out: the compiler's choice of the product to
 // fuse differed between these kernels where an operand is a half-precision word
-// times its norm.  Nine field passes instead of ten: at 32^3x64 in FP16 85 us instead of 96 for the
-// pair, at 24^3x48 in FP32 with 12 sources 594 instead of 658.
+// times its norm.  Nine field passes instead of ten: at 32^3x64 in FP16 85 us instead
+// of 96 for the pair, at 24^3x48 in FP32 with 12 sources 594 instead of 658.
 template <int P, bool ONE = false, bool NT = false>
 __global__ __launch_bounds__(256) void k_xpay_1(BlasArgs a)
 {

@@ -15,12 +15,12 @@
 //   s = M^+ r, gamma' = |s|^2, beta = gamma'/gamma; p = s + beta p and, once for
 //   two iterations, x += alpha_1 p_1 + alpha_2 p_2 in one pass.
 // The host reads only the |r|^2 history, once per chunk of iterations, from
-// pinned memory that the reporting kernel writes.  A chunk is captured once as a HIP graph and replayed.  When the sloppy
-// residual of a right-hand side has fallen by `delta` since its last update
-// (or reached the tolerance, or maxiter) the FP64 accumulator takes x_lo and
-// the residual b' - M x is recomputed in FP64 (reliable update); p is kept
-// and s, gamma are recomputed from the new residual.  Two updates in a row
-// that fail to halve the FP64 residual raise the sloppy precision one step.
+// pinned memory that the reporting kernel writes.  A chunk is captured once as a HIP
+// graph and replayed.  When the sloppy residual of a right-hand side has fallen by
+// `delta` since its last update (or reached the tolerance, or maxiter) the FP64
+// accumulator takes x_lo and the residual b' - M x is recomputed in FP64 (reliable
+// update); p is kept and s, gamma are recomputed from the new residual.  Two updates in
+// a row that fail to halve the FP64 residual raise the sloppy precision one step.
 // Finally psi_o = eta_o + kappa D_oe psi_e and the true residual
 // |eta - D psi| / |eta| is computed in FP64 with the whole-lattice operator.
 //
@@ -147,10 +147,11 @@ struct Cg {
         return WL_OK;
     }
 
-    // rh = b' - M xh in FP64 with |rh|^2 into SC_RR and the host's report.  Links are rebuilt from 12
-    // reals when the caller chose recon-12 (exact to rounding for SU(3)); the
-    // final true residual always uses all 18.
-    // sloppy_r: it is rounded to the sloppy residual rl instead of being stored in rh.
+    // rh = b' - M xh in FP64 with |rh|^2 into SC_RR and the host's report.  Links are
+    // rebuilt from 12 reals when the caller chose recon-12 (exact to rounding for SU(3));
+    // the final true residual always uses all 18.
+    // sloppy_r (not where the sloppy precision is FP64): it is rounded to the sloppy
+    // residual rl instead of being stored in rh.
     wl_status residual64(bool sloppy_r = false)
     {
         const bool use_active = true;
@@ -202,7 +203,7 @@ struct Cg {
     }
 
     // iteration j of a chunk in the sloppy precision; history row j receives |r|^2
-    // (CGNR: its block partials are summed for the whole chunk by hist_finalize)
+    // (CGNR: its block partials are summed for the whole chunk by hist_report)
     // pair (CGNR): 1, 2 for the first and second of two iterations that update x
     // together (the first leaves its new direction in p2), 0 for one by itself
     wl_status iteration(int j, int pair)

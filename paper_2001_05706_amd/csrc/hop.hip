@@ -1,10 +1,10 @@
 // hop.hip -- the single-parity Wilson hopping kernel (the D-slash of Table 2)
 // with a fused linear-combination epilogue and optional fused |out|^2.
 //
-// One thread per output site of one vector (variant 11: eight, one a direction).  Per direction the neighbour
-// spinor is spin-projected to two components (12 flop), both are multiplied
-// by the link (2 x 66 flop) rebuilt from 12 reals when recon = 12, and the
-// result is spin-reconstructed into the accumulator (24 flop): 1320 flop per
+// One thread per output site of one vector (variant 11: eight, one a direction).
+// Per direction the neighbour spinor is spin-projected to two components (12 flop),
+// both are multiplied by the link (2 x 66 flop) rebuilt from 12 reals when recon = 12,
+// and the result is spin-reconstructed into the accumulator (24 flop): 1320 flop per
 // site.  Each link is used once per hop and right-hand side; neighbour
 // spinors are shared by up to 8 output sites through L2, which the XCD-aware
 // block order keeps on one die.
@@ -108,7 +108,7 @@ __device__ __forceinline__ void load_x(const HopArgs &a, const HopIO &f, int j, 
 // An FP64 result rounded to the field a.lo (as k_convert rounds; plain stores: the
 // next hop reads it).  A reliable update's residual is only wanted in the sloppy
 // precision: storing it in FP64 and converting it cost the 32^3x64 FP16 solve a
-// further 460 MB and a launch, about 90 us of each update's 750.
+// further 400 MB (201 written, 201 read) and a launch, about 90 us of each update's 750.
 __device__ __forceinline__ void store_lo(const HopArgs &a, const VecDesc &vd, const SysDesc &sd, int cb, const double o[24])
 {
     float y[24];

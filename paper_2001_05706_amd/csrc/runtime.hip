@@ -748,11 +748,13 @@ int cfg_block(int c) { return (c >> 4) & 4095; }
 int cfg_col(int c) { return (c >> 16) & 4095; }
 
 // Candidate configurations: every variant x block size x column height of 4 or
-// 16 z-planes, for several right-hand sides also columns of 4 along all of t and
-// of 6 along half of it (12-RHS D-slash at 24^3x48, FP16 184 -> 165 us, FP32
-// 306 -> 292; with one vector within 1-2%) (taller columns sweep longer runs of consecutive sites: FP64
-// 32^3 x 64 D-slash 291 -> 278 us, FP32 116 -> 114 us; at 24^3 x 48 the height
-// changes little)
+// 16 z-planes (taller columns sweep longer runs of consecutive sites: FP64 32^3 x 64
+// D-slash 291 -> 278 us, FP32 116 -> 114 us; at 24^3 x 48 the height changes little).
+// For several right-hand sides also columns of 4 along all of t and of 6 along half of
+// it: best of columns of 4, those and these, us, 12 RHS FP32 at 24^3x48 298, 302 and 293,
+// at 20^3x40 121, 117 and 120, 4 RHS at 32^4 145, 139 and 144, at 24x24x28x48 110, 106
+// and 105, 12 RHS at 16^3x32 50.4, 49.2 and 50.2, at 12^3x24 17.6, 18.0 and 17.6; FP16
+// and FP64 within 2% in all of these, and so is one vector.
 std::vector<int> hop_candidates(int prec, bool many)
 {
     std::vector<int> c, cols = {4, 16};
@@ -1119,10 +1121,11 @@ wl_status hop2(ExecSet &S, int prec, int recon, bool dag, const Field out[2], co
                hipStream_t s, bool use_active)
 {
     // one launch for both output parities, which share their operands (see
-    // HopArgs::twin).  With several vectors the tuner decides between one launch
-    // and two: the parities' fields then compete for the XCD's L2 (FP32 recon-12,
-    // one launch against two: 4 RHS at 24^3x48 455 and 500 us a call, 12 RHS
-    // 1347 and 1319, the 12-RHS sign function at 16^3x32 60.7 and 64.0 ms).
+    // HopArgs::twin).  With several vectors the tuner decides between one launch and two:
+    // the parities' fields then compete for the XCD's L2.  The best of each, FP32 recon-12:
+    // operator at 24^3x48 with 1 RHS 102 us and 122, 4 RHS 454 and 423, 12 RHS 1310 and
+    // 1299, 12 RHS at 16^3x32 242 and 229; sign function of degree 20 there 6.75 ms and
+    // 7.23, 4 RHS at 24^3x48 12.5 and 13.2.
     // Different epilogue shapes and kernel timing take two.
     const bool clov = e[0].clov != 0 && S.has_clover;
     if (prof().on || e[0].nx != e[1].nx || e[0].g5 != e[1].g5 || e[0].coef != e[1].coef ||
