@@ -68,13 +68,11 @@ def test_four_launch_iteration_at_every_chunk_end(prec, tol, k, monkeypatch):
         assert np.linalg.norm(x - y) <= tol * np.linalg.norm(y)
 
 
-@pytest.mark.parametrize("cfg", ["3:256", "0:64", "11:64"])
-@pytest.mark.parametrize("prec,recon", [("f32", 18), ("f32", 12), ("f16", 12), ("bf16", 12)])
+@pytest.mark.parametrize("prec,recon,cfg", [(p, r, c) for p, r in [("f32", 18), ("f32", 12), ("f16", 12), ("bf16", 12)]
+                                            for c in ("3:256", "0:64", "11:64") if p == "f32" or c != "11:64"])
 @pytest.mark.parametrize("method,csw", [("multi", None), ("wilson_bicgstab", None), ("wilson_clover_cg", 1.0)])
 def test_residual_rounded_in_the_hop(prec, recon, method, csw, cfg, monkeypatch):
-    """(variant 11 rounds to FP32 only: half precision keeps the other configurations)"""
-    if cfg == "11:64" and prec in ("f16", "bf16"):
-        pytest.skip("not a candidate: the tuner would choose")
+    """(variant 11 rounds to FP32 only)"""
     w = need_gpu()
     monkeypatch.setenv("WL_TUNE_FORCE", cfg)
     runs = []
