@@ -602,7 +602,8 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
             return WL_OK;
         };
         while (true) {
-            // the first chunk runs eagerly: it tunes launch shapes and builds layouts before capture
+            // the first chunk of a precision runs eagerly: it tunes launch shapes and builds
+            // layouts before capture
             const bool graphs = cg.use_graphs;
             if (first) cg.use_graphs = false;
             WL_TRY(cg.chunk(k));
@@ -741,6 +742,7 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
                 if ((stalled || anybad) && cg.sloppy != P_F64) {
                     WL_TRY(escalate(anybad ? "non-finite sloppy iterate" : "stagnation", upd));
                     pre = false;  // r and s are formed anew in the raised precision
+                    first = true;
                     WL_HIP(hipMemsetAsync(S.bad, 0, sizeof(int32_t) * nv, s));
                     // every vector restarts its search direction in the new precision
                     for (int v = 0; v < nv; ++v)

@@ -94,3 +94,27 @@ def test_a_refused_source_leaves_nothing_running():
         assert st == 7  # WL_ERR_NONFINITE
     g.close()
     assert not any(busy)
+
+
+@pytest.mark.parametrize("method,csw", [("wilson_cg", None), ("wilson_bicgstab", None), ("wilson_clover_cg", 1.0)])
+@pytest.mark.parametrize("sloppy", ["f16", "bf16"])
+def test_raise_to_a_precision_that_another_handle_has_tuned(sloppy, method, csw, monkeypatch):
+    """The raised precision's configurations are known before this handle has met them:
+    their block maps are made outside the capture of its chunks.  (A source of 1e30
+    overflows FP16's and BF16's FP32 squares, which raises the precision.)"""
+    w = need_gpu()
+    L, nrhs = (8, 8, 8, 16), 9  # 576 blocks of 64 sites: tuned
+    U, eta = to_dev(li.near_identity_links(L, 0.3, 46)), li.gaussian_spinor(L, 47, nrhs=nrhs)
+
+    def solve(prec, scale):
+        g, x = w.Gauge(L, U), to_dev(np.zeros_like(eta))
+        a = (g, to_dev(eta * scale), x, nrhs, 0.12) + (() if csw is None else (csw,)) + (1e-10, 1000, prec, 12)
+        _, info = getattr(w, method)(*a)
+        g.close()
+        return info
+
+    for prec in ("f32", "f64"):
+        assert all(i["converged"] for i in solve(prec, 1.0))
+    monkeypatch.setenv("WL_TUNE_FORCE", "4:128:5")  # half precision only: its block maps are no other's
+    info = solve(sloppy, 1e30)
+    assert all(i["converged"] and i["precision_escalations"] >= 1 for i in info), info
