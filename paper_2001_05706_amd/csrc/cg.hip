@@ -352,6 +352,7 @@ struct Cg {
             s = user;
             g_bytes_acc = saved;
             if (st != WL_OK) {
+                if (ce != hipSuccess) (void)hipGetLastError();
                 if (g) (void)hipGraphDestroy(g);
                 return st;
             }

@@ -25,6 +25,8 @@ wl_status set_error(wl_status s, const char *fmt, ...)
     va_start(ap, fmt);
     vsnprintf(t_err, sizeof(t_err), fmt, ap);
     va_end(ap);
+    // reported here: left in the runtime, the next launch of any library would return it
+    if (s == WL_ERR_HIP) (void)hipGetLastError();
     return s;
 }
 
@@ -381,6 +383,7 @@ ExecSet::~ExecSet()
     for (auto &e : mask_ev)
         if (e) (void)hipEventDestroy(e);
     if (rr_ev) (void)hipEventDestroy(rr_ev);
+    (void)hipGetLastError();  // a set that could not be made inside a capture cannot be freed there either
 }
 
 #define WL_ALLOC(ptr, bytes)                                                              \

@@ -113,3 +113,56 @@ def test_first_call_times_a_bounded_number_of_launches(capfd, monkeypatch):
     g.close()
     assert len(found) == 2 and max(int(c) for c, _ in found) >= 200
     assert all(int(n) <= 40 * 4 + 6 * 7 * 4 + 16 * 4 + 6 * 3 * 9 for _, n in found)
+
+
+def hip():
+    import ctypes
+
+    h = ctypes.CDLL("libamdhip64.so")
+    for f, a in (("hipStreamCreateWithFlags", [ctypes.c_void_p, ctypes.c_uint]),
+                 ("hipStreamBeginCapture", [ctypes.c_void_p, ctypes.c_int]),
+                 ("hipStreamEndCapture", [ctypes.c_void_p, ctypes.c_void_p]),
+                 ("hipGraphDestroy", [ctypes.c_void_p]), ("hipStreamDestroy", [ctypes.c_void_p])):
+        getattr(h, f).argtypes = a
+    return h
+
+
+class Capture:
+    """A capture on a stream of its own (thread-local mode, as torch's graphs use at
+    its strictest: nothing may be allocated or copied synchronously)."""
+
+    def __init__(self):
+        import ctypes
+
+        self.h, self.s, self.g = hip(), ctypes.c_void_p(), ctypes.c_void_p()
+        assert self.h.hipStreamCreateWithFlags(ctypes.byref(self.s), 1) == 0
+
+    def __enter__(self):
+        assert self.h.hipStreamBeginCapture(self.s, 1) == 0
+        return self
+
+    def __exit__(self, *a):
+        import ctypes
+
+        self.ended = self.h.hipStreamEndCapture(self.s, ctypes.byref(self.g))
+        self.h.hipGetLastError()
+        if self.g:
+            self.h.hipGraphDestroy(self.g)
+        self.h.hipStreamDestroy(self.s)
+
+
+def test_a_failed_call_leaves_no_error_behind():
+    """A call that cannot be captured (its fields do not exist yet) says so; the
+    runtime's last error, which the next launch of any library would report, is clear."""
+    w = need_gpu()
+    L = (8, 8, 8, 16)
+    psi = to_dev(li.gaussian_spinor(L, 51, nrhs=9))
+    out = psi.clone()
+    g = w.Gauge(L, to_dev(li.haar_links(L, 50)))
+    with Capture() as c:
+        with pytest.raises(w.WilsonError):
+            w.wilson_dslash(g, psi, out, 9, 0.12, 0, 0, "f32", 12, stream=c.s.value)
+        left = c.h.hipPeekAtLastError()
+    w.wilson_dslash(g, psi, out, 9, 0.12, 0, 0, "f32", 12)
+    g.close()
+    assert left == 0
