@@ -792,14 +792,17 @@ std::vector<int> hop_candidates(int prec, bool many)
 // the block layout a hop launch configuration runs on: variant 6 and 8 blocks
 // hold B / 64 right-hand sides of 64 sites each, variant 7 blocks B sites of
 // two right-hand sides
-static wl_status hop_layout(ExecSet &S, int cfg, const Layout **L)
+static int hop_layout_key(int cfg)
 {
     const int var = cfg_var(cfg), B = cfg_block(cfg);
-    const int key = var == 6 || var == 8 ? -(B / 64)
-                    : var == 7           ? kPairLayout + B
-                    : var == 9 || var == 10 ? kPencilLayout + B / 64
-                                         : B;
-    return S.layout(key, L, cfg_col(cfg));
+    return var == 6 || var == 8    ? -(B / 64)
+           : var == 7              ? kPairLayout + B
+           : var == 9 || var == 10 ? kPencilLayout + B / 64
+                                   : B;
+}
+static wl_status hop_layout(ExecSet &S, int cfg, const Layout **L)
+{
+    return S.layout(hop_layout_key(cfg), L, cfg_col(cfg));
 }
 
 // blocks of 64 sites of a set's vectors
@@ -946,6 +949,12 @@ static wl_status hop_plan(ExecSet &S, int id, bool direct, bool untimed, ExecSet
                               return run(c, L);
                           },
                           &settled);
+    if (!S.layouts.count({hop_layout_key(pl->cfg), cfg_col(pl->cfg)}) && capturing(s)) {
+        // a configuration that another handle has tuned, its block map not made here yet:
+        // in a capture the hop runs on the packing kernels' map
+        pl->cfg = cfg_make(0, kBlasBlock, 4);
+        settled = false;
+    }
     WL_TRY(hop_layout(S, pl->cfg, &pl->L));
     if (settled && !pinned) S.plans[id] = *pl;
     return WL_OK;

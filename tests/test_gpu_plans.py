@@ -166,3 +166,41 @@ def test_a_failed_call_leaves_no_error_behind():
     w.wilson_dslash(g, psi, out, 9, 0.12, 0, 0, "f32", 12)
     g.close()
     assert left == 0
+
+
+@pytest.mark.parametrize("clover", [False, True])
+@pytest.mark.parametrize("prec,recon", [("f64", 18), ("f32", 12), ("f16", 12)])
+def test_adjoint_first_met_under_capture(prec, recon, clover, monkeypatch):
+    """A set that has run the operator can capture its adjoint, also in a configuration
+    whose block map it has not made (here a pinned one; else one that another handle of
+    the shape has tuned)."""
+    import torch
+
+    w = need_gpu()
+    L, nrhs = (8, 8, 8, 16), 9
+    g = w.Gauge(L, to_dev(li.haar_links(L, 52)))
+    a, b = (to_dev(li.gaussian_spinor(L, 53 + i, nrhs=nrhs)) for i in range(2))
+    inp, out, ref = a.clone(), torch.empty_like(a), torch.empty_like(a)
+
+    def call(dagger, o):
+        if clover:
+            w.wilson_clover_dslash(g, inp, o, nrhs, 0.12, 1.0, dagger, prec, recon)
+        else:
+            w.wilson_dslash(g, inp, o, nrhs, 0.12, -1, dagger, prec, recon)
+
+    call(0, out)
+    torch.cuda.synchronize()
+    graph, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    monkeypatch.setenv("WL_TUNE_FORCE", "3:64:5")
+    with torch.cuda.graph(graph, stream=s):
+        call(1, out)
+    monkeypatch.delenv("WL_TUNE_FORCE")
+    for src in (a, b, a):
+        inp.copy_(src)
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        call(1, ref)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+    g.close()
