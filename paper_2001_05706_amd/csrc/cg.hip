@@ -45,16 +45,6 @@
 
 namespace wl {
 
-static hipStream_t capture_stream()
-{
-    static hipStream_t cs = nullptr;
-    if (!cs && hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) {
-        (void)hipGetLastError();
-        cs = nullptr;
-    }
-    return cs;
-}
-
 enum { M_CGNR = 0, M_BICGSTAB = 1 };
 
 struct Cg {
@@ -342,6 +332,7 @@ struct Cg {
             WL_TRY(S.sys_table(sloppy, recon, s, &tab));
             hipStream_t cs = capture_stream();
             if (!cs) return set_error(WL_ERR_HIP, "cannot create the capture stream");
+            std::lock_guard<std::mutex> lk(capture_mutex());
             const double saved = g_bytes_acc;
             hipStream_t user = s;
             s = cs;
@@ -617,7 +608,8 @@ wl_status run_cg(ExecSet &S, const double *const *eta, double *const *x, int rec
             if (trace) {
                 double sc[ExecSet::SC_N];
                 for (int j = 0; j < ExecSet::SC_N; ++j)
-                    WL_HIP(hipMemcpy(&sc[j], S.scal(j), sizeof(double), hipMemcpyDeviceToHost));
+                    WL_HIP(hipMemcpyAsync(&sc[j], S.scal(j), sizeof(double), hipMemcpyDeviceToHost, s));
+                WL_HIP(hipStreamSynchronize(s));
                 fprintf(stderr, "[wl cg] chunk k=%d prec=%d rhs0: |r| %.3e -> %.3e  alpha %.3e beta %.3e gamma %.3e bad %d\n",
                         k, cg.sloppy, std::sqrt(hp[0]), std::sqrt(hp[(size_t)(k - 1) * nv]), sc[SC_ALPHA],
                         sc[SC_BETA], sc[SC_GAM], (int)hbad[0]);

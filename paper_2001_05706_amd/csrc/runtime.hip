@@ -50,6 +50,56 @@ bool device_range_ok(const void *p, size_t bytes)
     return (const char *)p + bytes <= (const char *)base + size;
 }
 
+// ------------------------------------------------------------------ set-up copies
+
+// A stream of the library's own per device and purpose (0: set-up copies, 1: captures)
+static hipStream_t own_stream(int purpose)
+{
+    static std::mutex mu;
+    static std::map<std::pair<int, int>, hipStream_t> streams;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+    std::lock_guard<std::mutex> lk(mu);
+    hipStream_t &st = streams[{dev, purpose}];
+    if (!st && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) {
+        (void)hipGetLastError();
+        st = nullptr;
+    }
+    return st;
+}
+
+hipStream_t capture_stream() { return own_stream(1); }
+
+std::mutex &capture_mutex()
+{
+    static std::mutex mu;
+    return mu;
+}
+
+// (a failure waits too: what was queued before it may still read the caller's memory)
+static hipError_t setup_end(hipStream_t s, hipError_t e, bool wait)
+{
+    if (e == hipSuccess) return wait ? hipStreamSynchronize(s) : e;
+    (void)hipStreamSynchronize(s);
+    return e;
+}
+
+hipError_t setup_copy(void *dst, const void *src, size_t bytes, bool wait)
+{
+    hipStream_t s = own_stream(0);
+    if (!s) return hipErrorNotInitialized;
+    const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+    return setup_end(s, e, wait);
+}
+
+hipError_t setup_zero(void *dst, size_t bytes, bool wait)
+{
+    hipStream_t s = own_stream(0);
+    if (!s) return hipErrorNotInitialized;
+    const hipError_t e = hipMemsetAsync(dst, 0, bytes, s);
+    return setup_end(s, e, wait);
+}
+
 // ------------------------------------------------------------------ precision helpers
 
 int spinor_site_bytes(int prec)
@@ -423,7 +473,6 @@ wl_status ExecSet::init()
     WL_ALLOC(bad, sizeof(int32_t) * nvec);
     WL_ALLOC(hist_partials, sizeof(double) * kHist * max_pslots);
     WL_ALLOC(d_counts, 2 * sizeof(unsigned long long) * nvec);
-    WL_HIP(hipMemset(d_counts, 0, 2 * sizeof(unsigned long long) * nvec));
     if (hipHostMalloc((void **)&h_report, sizeof(double) * kRepRows * nvec, 0) != hipSuccess) {
         (void)hipGetLastError();
         h_report = nullptr;
@@ -438,10 +487,11 @@ wl_status ExecSet::init()
     }
     for (auto &e : mask_ev) WL_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     WL_HIP(hipEventCreateWithFlags(&rr_ev, hipEventDisableTiming));
-    WL_HIP(hipMemcpy(d_active, h_active.data(), sizeof(int32_t) * nvec, hipMemcpyHostToDevice));
-    WL_HIP(hipMemset(sc, 0, sizeof(double) * SC_N * nvec));
-    WL_HIP(hipMemset(bad, 0, sizeof(int32_t) * nvec));
-    WL_HIP(hipMemset(hist, 0, sizeof(double) * kHist * nvec));
+    WL_HIP(setup_copy(d_active, h_active.data(), sizeof(int32_t) * nvec, false));
+    WL_HIP(setup_zero(sc, sizeof(double) * SC_N * nvec, false));
+    WL_HIP(setup_zero(bad, sizeof(int32_t) * nvec, false));
+    WL_HIP(setup_zero(hist, sizeof(double) * kHist * nvec, false));
+    WL_HIP(setup_zero(d_counts, 2 * sizeof(unsigned long long) * nvec));
     return WL_OK;
 }
 
@@ -482,7 +532,7 @@ wl_status ExecSet::sys_table(int prec, int recon, hipStream_t s, const SysDesc *
     }
     SysDesc *d = nullptr;
     WL_ALLOC(d, sizeof(SysDesc) * h.size());
-    WL_HIP(hipMemcpy(d, h.data(), sizeof(SysDesc) * h.size(), hipMemcpyHostToDevice));
+    WL_HIP(setup_copy(d, h.data(), sizeof(SysDesc) * h.size()));
     d_sys[key] = d;
     *out = d;
     return WL_OK;
@@ -558,8 +608,8 @@ wl_status ExecSet::layout(int B, const Layout **out, int col)
     if (ps > max_pslots) return set_error(WL_ERR_ARG, "block size %d below the supported minimum", B);
     WL_ALLOC(L.d_vec, sizeof(VecDesc) * hv.size());
     WL_ALLOC(L.d_map, sizeof(BlkMap) * map.size());
-    WL_HIP(hipMemcpy(L.d_vec, hv.data(), sizeof(VecDesc) * hv.size(), hipMemcpyHostToDevice));
-    WL_HIP(hipMemcpy(L.d_map, map.data(), sizeof(BlkMap) * map.size(), hipMemcpyHostToDevice));
+    WL_HIP(setup_copy(L.d_vec, hv.data(), sizeof(VecDesc) * hv.size(), false));
+    WL_HIP(setup_copy(L.d_map, map.data(), sizeof(BlkMap) * map.size()));
     layouts[lkey] = L;
     *out = &layouts[lkey];
     return WL_OK;
@@ -595,14 +645,15 @@ wl_status ExecSet::field(const std::string &name, int prec, Field *out)
     f.prec = prec;
     const size_t bytes = total_sites * (size_t)nchunks(prec) * chunk_bytes(prec);
     WL_ALLOC(f.p, bytes);
-    WL_HIP(hipMemset(f.p, 0, bytes));
-    if (prec == P_F16 || prec == P_BF16) {
+    const bool half = prec == P_F16 || prec == P_BF16;
+    WL_HIP(setup_zero(f.p, bytes, !half));
+    if (half) {
         if (hipMalloc((void **)&f.n, total_sites * sizeof(float)) != hipSuccess) {
             (void)hipGetLastError();
             (void)hipFree(f.p);
             return set_error(WL_ERR_NOMEM, "cannot allocate norms");
         }
-        WL_HIP(hipMemset(f.n, 0, total_sites * sizeof(float)));
+        WL_HIP(setup_zero(f.n, total_sites * sizeof(float)));
     }
     fields[key] = f;
     *out = f;
@@ -657,7 +708,7 @@ wl_status coef_table(ExecSet &S, const std::vector<double> &c, const double **ou
     }
     double *d = nullptr;
     WL_ALLOC(d, sizeof(double) * c.size());
-    WL_HIP(hipMemcpy(d, c.data(), sizeof(double) * c.size(), hipMemcpyHostToDevice));
+    WL_HIP(setup_copy(d, c.data(), sizeof(double) * c.size()));
     S.coefs[c] = d;
     *out = d;
     return WL_OK;
@@ -1426,6 +1477,7 @@ wl_status wl_gauge_create(const wl_geom *geom, const double *U_dev, void *stream
 void wl_gauge_destroy(wl_gauge U)
 {
     if (!U) return;
+    std::lock_guard<std::mutex> lk(capture_mutex());  // neither this nor freeing may meet a capture
     (void)hipDeviceSynchronize();
     drop_sets_of(U);
     delete U;
@@ -1607,7 +1659,7 @@ wl_status wl_bench_dslash(wl_gauge U, wl_prec prec, int32_t recon, int32_t nrhs,
             h.gauge = lcopy[k];
         }
         if (hipMalloc((void **)&dsys[k], sizeof(SysDesc)) != hipSuccess ||
-            hipMemcpy(dsys[k], &h, sizeof(SysDesc), hipMemcpyHostToDevice) != hipSuccess) {
+            setup_copy(dsys[k], &h, sizeof(SysDesc)) != hipSuccess) {
             (void)hipGetLastError();
             st = set_error(WL_ERR_NOMEM, "cannot allocate descriptor");
             break;

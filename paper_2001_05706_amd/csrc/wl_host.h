@@ -8,6 +8,7 @@
 #include <functional>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -33,6 +34,16 @@ void clear_error();
         wl_status s_ = (expr);            \
         if (s_ != WL_OK) return s_;       \
     } while (0)
+
+// Copies to and clearing of device memory that have ended when they return, on a stream
+// of the library's own: a synchronous copy uses the legacy stream, which the runtime
+// refuses while any stream of the process is captured, and ends that capture
+// (wait false: by the end of the next one that waits)
+hipError_t setup_copy(void *dst, const void *src, size_t bytes, bool wait = true);
+hipError_t setup_zero(void *dst, size_t bytes, bool wait = true);
+// the stream that solver chunks are captured on, by one thread at a time
+hipStream_t capture_stream();
+std::mutex &capture_mutex();
 
 // true if [p, p + bytes) lies inside one device allocation
 bool device_range_ok(const void *p, size_t bytes);
