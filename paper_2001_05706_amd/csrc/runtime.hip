@@ -776,9 +776,10 @@ double blas_bytes(const ExecSet &S, int prec, int passes, bool use_active)
 
 // What a set's hop candidates and their times depend on: the extents (pencil blocks
 // tile some lattices of a volume and not others) and right-hand sides of its systems
-static std::string set_sig(const ExecSet &S)
+static const std::string &set_sig(const ExecSet &S)
 {
-    std::string sig;
+    std::string &sig = S.sig;
+    if (!sig.empty()) return sig;
     for (auto &e : S.systems) {
         const int32_t *L = e.g->geom.L;
         char t[80];

@@ -235,6 +235,7 @@ public:
         const Layout *L;
     };
     std::map<int, HopPlan> plans;
+    mutable std::string sig;  // see set_sig
     const Layout *fold = nullptr;  // set by hop: the layout of partials left for the consumer
     int max_pslots = 0;
 };
