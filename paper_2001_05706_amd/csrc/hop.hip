@@ -692,11 +692,20 @@ __device__ __forceinline__ void split_store(void *base, int stride, int cb, int 
     }
 }
 
-// The products U h0, U h1 (U^+ for DIR < 0) into the lane's column of `out`
-template <int DIR, class T>
-__device__ __forceinline__ void split_put(const cpx<T> u[3][3], const cpx<T> h0[3], const cpx<T> h1[3], T *out)
+// U P v of direction MU, DIR for a neighbour's FP32 or FP64 spinor v
+template <int SP, int MU, int DIR, bool DAG, class T>
+__device__ __forceinline__ void split_multiply(const T v[24], bool flip, const cpx<T> u[3][3], T *out)
 {
-    cpx<T> g[3];
+    constexpr int SG = (DIR > 0) == DAG ? +1 : -1;
+    cpx<T> h0[3], h1[3], g[3];
+    project<MU, SG>(v, h0, h1);
+    if (flip) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            h0[c] = {-h0[c].re, -h0[c].im};
+            h1[c] = {-h1[c].re, -h1[c].im};
+        }
+    }
     su3_mul<(DIR < 0), T>(u, h0, g);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -709,30 +718,6 @@ __device__ __forceinline__ void split_put(const cpx<T> u[3][3], const cpx<T> h0[
         out[(6 + 2 * c) * 64] = g[c].re;
         out[(7 + 2 * c) * 64] = g[c].im;
     }
-}
-
-// The projected spinor of a neighbour's FP32 or FP64 one, negated behind an antiperiodic boundary
-template <int MU, int SG, class T>
-__device__ __forceinline__ void split_project(const T v[24], bool flip, cpx<T> h0[3], cpx<T> h1[3])
-{
-    project<MU, SG>(v, h0, h1);
-    if (flip) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            h0[c] = {-h0[c].re, -h0[c].im};
-            h1[c] = {-h1[c].re, -h1[c].im};
-        }
-    }
-}
-
-// U P v of direction MU, DIR for a neighbour's FP32 or FP64 spinor v
-template <int SP, int MU, int DIR, bool DAG, class T>
-__device__ __forceinline__ void split_multiply(const T v[24], bool flip, const cpx<T> u[3][3], T *out)
-{
-    constexpr int SG = (DIR > 0) == DAG ? +1 : -1;
-    cpx<T> h0[3], h1[3];
-    split_project<MU, SG>(v, flip, h0, h1);
-    split_put<DIR>(u, h0, h1, out);
 }
 
 // Site `lex` of the canonical field `base`, rounded as packing it rounds: FP64 and
@@ -760,7 +745,7 @@ __device__ __forceinline__ void split_product(const SysDesc &sd, const HopSite &
     constexpr int SG = (DIR > 0) == DAG ? +1 : -1;
     bool flip;
     const int ncb = neighbour<MU, DIR>(sd, st, cb, flip);
-    cpx<T> h0[3], h1[3], u[3][3];
+    cpx<T> h0[3], h1[3], g[3], u[3][3];
     T f;
     if constexpr (DIRECT) {
         // the neighbour is the site of its pair with the x of its own parity
@@ -773,14 +758,32 @@ __device__ __forceinline__ void split_product(const SysDesc &sd, const HopSite &
             project_half<SP, MU, SG>(q, h0, h1);
             f = (flip ? -m : m) * (T)hs.scale;
         } else {
-            split_project<MU, SG>(v, flip, h0, h1);
+            project<MU, SG>(v, h0, h1);
+            if (flip) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    h0[c] = {-h0[c].re, -h0[c].im};
+                    h1[c] = {-h1[c].re, -h1[c].im};
+                }
+            }
             f = 1;
         }
     } else {
         f = project_neighbour<SP, MU, SG>(hs, ncb, flip, h0, h1);
         hop_link<GP, R, MU, DIR, false>(hs, parity, cb, ncb, u);
     }
-    split_put<DIR>(u, h0, h1, out);
+    su3_mul<(DIR < 0), T>(u, h0, g);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        out[(2 * c) * 64] = g[c].re;
+        out[(2 * c + 1) * 64] = g[c].im;
+    }
+    su3_mul<(DIR < 0), T>(u, h1, g);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        out[(6 + 2 * c) * 64] = g[c].re;
+        out[(7 + 2 * c) * 64] = g[c].im;
+    }
     if constexpr (SplitHop<SP>::half) out[12 * 64] = f;
 }
 
