@@ -633,9 +633,13 @@ wl_status ExecSet::buffer(const std::string &name, size_t bytes, void **out)
     return WL_OK;
 }
 
+static std::string field_key(const std::string &name, int prec) { return name + "#" + std::to_string(prec); }
+
+bool ExecSet::has_field(const std::string &name, int prec) const { return fields.count(field_key(name, prec)) != 0; }
+
 wl_status ExecSet::field(const std::string &name, int prec, Field *out)
 {
-    const std::string key = name + "#" + std::to_string(prec);
+    const std::string key = field_key(name, prec);
     auto it = fields.find(key);
     if (it != fields.end()) {
         *out = it->second;
@@ -1510,15 +1514,20 @@ wl_status wilson_dslash(wl_gauge U, const double *in, double *out, int32_t nrhs,
     if (parity >= 0) {
         WL_TRY(coef_table(*S, {0, 0, 0, 0, 1.0}, &e[0].coef));
         e[0].canon_zero = 1;
-        if (dslash_direct(*S, 1)) {
+        const bool direct = dslash_direct(*S, 1);
+        if (direct) {
             e[0].canon_in = in;
         } else {
-            // (both parities' fields: a later call with the other one may be captured,
-            // where nothing can be allocated)
-            for (int p = 0; p < 2; ++p) WL_TRY(S->field("dsl_in" + std::to_string(p), prec, &fi[p]));
+            WL_TRY(S->field("dsl_in" + std::to_string(1 - parity), prec, &fi[1 - parity]));
             WL_TRY(pack(*S, cin, 1 - parity, fi[1 - parity], s));
         }
         WL_TRY(hop(*S, prec, recon, dagger, parity, Field(), fi[1 - parity], e[0], no_red(), s, false));
+        // the other parity's field too: a later call with it may be captured, where nothing
+        // can be allocated (behind the launches: in front it moves the links of a lattice
+        // that just fits the last-level cache; without memory for it this call is done)
+        const std::string spare = "dsl_in" + std::to_string(parity);
+        if (!direct && !S->has_field(spare, prec) && !capturing(s) && S->field(spare, prec, &fi[parity]) != WL_OK)
+            clear_error();
         return WL_OK;
     }
     const double *coef = nullptr;

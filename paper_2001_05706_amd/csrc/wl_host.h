@@ -220,6 +220,7 @@ public:
 
     // fields by name, allocated on first use
     wl_status field(const std::string &name, int prec, Field *out);
+    bool has_field(const std::string &name, int prec) const;
     // device scratch by name, grown on demand (contents not kept across growth)
     wl_status buffer(const std::string &name, size_t bytes, void **out);
     std::map<std::string, std::pair<void *, size_t>> bufs;
