@@ -182,7 +182,8 @@ bool capturing(hipStream_t s)
 
 static std::mutex g_tune_mu;
 static std::map<std::string, int> g_tuned;
-constexpr size_t kTuneAll = 80, kTuneWide = 6, kTuneAgain = 16, kTuneFinal = 6;
+constexpr size_t kTuneWide = 6, kTuneAgain = 16, kTuneFinal = 6;
+constexpr float kTuneShort = 0.025f;  // ms
 
 int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream_t s,
                 const std::function<hipError_t(int)> &run, bool *settled)
@@ -225,16 +226,19 @@ int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream
         return fallback;
     }
     // Sweeps in which a candidate is launched once to warm up and then a few times
-    // between events.  Up to kTuneAll candidates (sets of one right-hand side) are all
-    // taken.  Of more, the first sweep takes every variant and block size in the plain
-    // block order, one launch for both parities, and the second the other orders and forms
-    // of the best kTuneWide of those, which they change by less than variants differ.  The
-    // best kTuneAgain of all are swept again, since one short sweep picks among near-equal
-    // ones by noise (a candidate has its faster score).  Launches of over 0.1 ms are told
-    // apart by fewer repeats.  A process's first call pays for all of them: with every
-    // candidate in two full sweeps the first 12-RHS operator at 24^3x48 took 2.5 s, the
-    // first 12-source solve there 5.4 s and the first 12-RHS sign function at 16^3x32
-    // 0.90 s; now 0.36, 2.2 and 0.14 s, in configurations of the same speed.
+    // between events, each scored by its fastest.  All candidates are swept twice: a
+    // first reading can be 20% off (variant 11 at 32^3x64 in FP16 0.103 ms, 0.085 when
+    // repeated), and a candidate dropped for it is a slower choice for good.  A process's
+    // first call pays for the launches, though, and several right-hand sides have up to
+    // 288 candidates: where their launches are longer than kTuneShort (and variant 11 is
+    // no longer offered), the first sweep takes every variant and block size in the plain
+    // block order, one launch for both parities, the second the other orders and forms of
+    // the best kTuneWide of those, which they change by less than variants differ, and the
+    // third the best kTuneAgain of all.  Launches of over 0.1 ms are told apart by fewer
+    // repeats.  With every candidate in two full sweeps the first 12-RHS operator at
+    // 24^3x48 took 2.5 s, the first 12-source solve there 5.4 s and the first 12-RHS sign
+    // function at 16^3x32 0.90 s; now 0.37, 1.7 and 0.15 s, in configurations of the same
+    // speed.
     std::vector<float> score(cands.size(), 1e30f);
     float least = 1e30f;
     int launches = 0;
@@ -264,17 +268,23 @@ int tuned_block(const std::string &key, const std::vector<int> &cands, hipStream
         if (v.size() > n) v.resize(n);
         return v;
     };
-    auto plain = [&](size_t i) {
-        return cands.size() <= kTuneAll || (cfg_col(cands[i]) == 4 && !(cands[i] & kCfgSplit));
-    };
+    auto plain = [&](size_t i) { return cfg_col(cands[i]) == 4 && !(cands[i] & kCfgSplit); };
+    const bool many = std::any_of(cands.begin(), cands.end(), [](int c) { return col_groups(cfg_col(c)) > 0; });
     for (size_t i = 0; i < cands.size(); ++i)
         if (plain(i)) score[i] = time(i, 3);
-    const std::vector<size_t> wide = best_of(kTuneWide);
-    for (size_t i = 0; i < cands.size(); ++i)
-        for (size_t j : wide)
-            if (!plain(i) && cfg_var(cands[i]) == cfg_var(cands[j]) && cfg_block(cands[i]) == cfg_block(cands[j]))
-                score[i] = time(i, 3);
-    for (size_t i : best_of(kTuneAgain)) score[i] = std::min(score[i], time(i, 3));
+    if (many && least > kTuneShort) {
+        const std::vector<size_t> wide = best_of(kTuneWide);
+        for (size_t i = 0; i < cands.size(); ++i)
+            for (size_t j : wide)
+                if (!plain(i) && cfg_var(cands[i]) == cfg_var(cands[j]) && cfg_block(cands[i]) == cfg_block(cands[j]))
+                    score[i] = time(i, 3);
+        for (size_t i : best_of(kTuneAgain)) score[i] = std::min(score[i], time(i, 3));
+    } else {
+        for (size_t i = 0; i < cands.size(); ++i)
+            if (!plain(i)) score[i] = time(i, 3);
+        for (size_t i = 0; i < cands.size(); ++i)
+            if (score[i] < 1e30f) score[i] = std::min(score[i], time(i, 3));
+    }
     // a final round among the best kTuneFinal of the sweeps: three interleaved trials
     // of 8 launches each, every finalist scored by its fastest trial (3-launch
     // sweeps cannot order candidates that lie within a few per cent)

@@ -95,17 +95,21 @@ def test_clover_operator_counts_both_parities(L, nrhs, tuned, capfd, monkeypatch
 
 def test_first_call_times_a_bounded_number_of_launches(capfd, monkeypatch):
     """The block orders and split forms of several right-hand sides make 288 candidates
-    of a whole-lattice operator; the tuner tries them for the best few variants only.
-    Of at most 40 variants and block sizes 4 launches each, 7 further forms of 6 of them
-    and 16 again likewise, and 6 finalists in 3 trials of 9."""
+    of a whole-lattice operator; where launches are long, the tuner tries them for the
+    best few variants only.  Of at most 40 variants and block sizes 4 launches each, 7
+    further forms of 6 of them and 16 again likewise, and 6 finalists in 3 trials of 9."""
     import re
+
+    import torch
 
     w = need_gpu()
     monkeypatch.setenv("WL_DEBUG", "1")
-    L, nrhs = (8, 6, 10, 16), 12  # 720 blocks of 64 sites a parity: tuned
-    psi = to_dev(li.gaussian_spinor(L, 38, nrhs=nrhs))
-    out = psi.clone()
-    g = w.Gauge(L, to_dev(li.haar_links(L, 39)))
+    L, nrhs = (16, 16, 16, 20), 12
+    V = 16 * 16 * 16 * 20
+    gen = torch.Generator(device="cuda").manual_seed(38)
+    psi = torch.randn(nrhs * V * 24, generator=gen, dtype=torch.float64, device="cuda")
+    out = torch.empty_like(psi)
+    g = w.Gauge(L, to_dev(li.near_identity_links(L, 0.3, 39)))
     capfd.readouterr()
     w.wilson_dslash(g, psi, out, nrhs, 0.12, -1, 0, "f32", 12)
     w.wilson_dslash(g, psi, out, nrhs, 0.12, 0, 0, "f32", 12)
